@@ -264,55 +264,70 @@ __global__ void __launch_bounds__(NT) k_mg_prolong(const MgLevelDev* __restrict_
   }
 }
 
-// z = Ainv r on each instance's coarsest level (dense, row-major): one wave
-// per (row, block of 8 columns), the lanes splitting the row's entries
-__global__ void __launch_bounds__(NT) k_mg_coarse(const MgLevelDev* __restrict__ co, int ncol) {
+// z = Ainv r on each instance's coarsest level (dense, symmetric), on the FP64
+// matrix cores: a workgroup of sixteen waves takes 16 rows and all columns (NCT
+// tiles of 16), each wave a sixteenth of the contraction; the partial tiles are
+// added in LDS.  The pass is bound by reading Ainv, which is read once for all
+// columns.  As Ainv is symmetric, rows i0 .. i0 + 15 of a contraction index j
+// are taken from its row j, 128 consecutive bytes (lane layout of
+// k_moments_mfma).  Measured, against a wave per row and 8 columns that read
+// Ainv again for every 8: 1154 -> 54 us at 4,096 unknowns x 36 columns
+// (670 MB -> 134 MB read), 15.8 -> 14.6 us at 1,979 x 4
+constexpr int MC_W = 16;   // waves of a workgroup
+template <int NCT>
+__global__ void __launch_bounds__(64 * MC_W) k_mg_coarse(const MgLevelDev* __restrict__ co, int ncol) {
   const MgLevelDev& L = co[blockIdx.y];
-  if (L.done && *L.done) return;
   const int64_t n = L.N;
+  const int64_t i0 = (int64_t)blockIdx.x * 16;
+  if (i0 >= n || (L.done && *L.done)) return;
+  __shared__ double lds[MC_W][256];
+  typedef double dvec4c_t __attribute__((ext_vector_type(4)));
   const auto* Ainv = gbl(L.cinv);
   const auto* r = gbl((const double*)L.r);
   auto* z = gblw(L.z);
-  const int lane = threadIdx.x & 63;
-  const int ncb = (ncol + 7) / 8;
-  const int64_t items = n * ncb;
-  for (int64_t w = ((int64_t)blockIdx.x * NT + threadIdx.x) >> 6; w < items; w += ((int64_t)gridDim.x * NT) >> 6) {
-    const int64_t i = w / ncb;
-    const int c0 = (int)(w - i * ncb) * 8;
-    double acc[8];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int64_t ia = i0 + li < n ? i0 + li : n - 1;   // rows past the end are computed and not stored
+  // this wave's contraction range, in steps of 4
+  const int64_t steps = (n + 3) / 4, per = (steps + MC_W - 1) / MC_W;
+  const int64_t s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
+  dvec4c_t acc[NCT];
 #pragma unroll
-    for (int v = 0; v < 8; ++v) acc[v] = 0.0;
-    // four strides of 64 per round, their loads in flight together
-    int64_t j = lane;
-    for (; j + 192 < n; j += 256) {
-      double a[4], rv[4][8];
+  for (int u = 0; u < NCT; ++u) acc[u] = dvec4c_t{0.0, 0.0, 0.0, 0.0};
+  constexpr int U = NCT <= 2 ? 8 : 4;   // steps whose loads are in flight together
+  for (int64_t st = s0; st < s1; st += U) {
+    double av[U], bv[U][NCT];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = Ainv[i * n + j + 64 * u];
+    for (int h = 0; h < U; ++h) {
+      const int64_t j = 4 * (st + h) + lk;
+      const bool ok = st + h < s1 && j < n;
+      const int64_t jc = ok ? j : n - 1;   // in-bounds load, weight zero
+      const double a = Ainv[jc * n + ia];
+      av[h] = ok ? a : 0.0;
 #pragma unroll
-        for (int v = 0; v < 8; ++v) rv[u][v] = c0 + v < ncol ? r[(j + 64 * u) * ncol + c0 + v] : 0.0;
+      for (int u = 0; u < NCT; ++u) {
+        const int c = 16 * u + li;
+        const double b = r[jc * ncol + (c < ncol ? c : 0)];
+        bv[h][u] = c < ncol ? b : 0.0;
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 8; ++v) acc[v] += a[u] * rv[u][v];
-    }
-    for (; j < n; j += 64) {
-      const double a = Ainv[i * n + j];
-#pragma unroll
-      for (int v = 0; v < 8; ++v)
-        if (c0 + v < ncol) acc[v] += a * r[j * ncol + c0 + v];
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
+    for (int h = 0; h < U; ++h)
 #pragma unroll
-      for (int v = 0; v < 8; ++v) acc[v] += __shfl_xor(acc[v], off, 64);
-    if (lane < 8 && c0 + lane < ncol) {
-      double out = 0.0;
+      for (int u = 0; u < NCT; ++u) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[h], bv[h][u], acc[u], 0, 0, 0);
+  }
 #pragma unroll
-      for (int v = 0; v < 8; ++v)
-        if (v == lane) out = acc[v];
-      z[i * ncol + c0 + lane] = out;
+  for (int u = 0; u < NCT; ++u) {
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) lds[wave][(4 * v + lk) * 16 + li] = acc[u][v];
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      double t = 0.0;
+#pragma unroll
+      for (int w = 0; w < MC_W; ++w) t += lds[w][threadIdx.x];
+      const int64_t i = i0 + (threadIdx.x >> 4);
+      const int c = 16 * u + (int)(threadIdx.x & 15);
+      if (i < n && c < ncol) z[i * ncol + c] = t;
     }
   }
 }
@@ -454,8 +469,14 @@ void mg_vcycle(const MgDev& mg, int ni, int ncol, const MgLevel0Ops& ops, hipStr
                          mg.lv[l], mg.lv[l + 1], ncol, cw, tres);
     }
   }
-  hipLaunchKernelGGL(k_mg_coarse, dim3(nblocks(mg.max_coarse * ((ncol + 7) / 8) * 64, NT, 4096), ni), dim3(NT), 0, s,
-                     mg.coarse, ncol);
+  {
+    const dim3 g((unsigned)((mg.max_coarse + 15) / 16), ni);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, dim3(64 * MC_W), 0, s, mg.coarse, ncol); };
+    if (ncol <= 16) go(k_mg_coarse<1>);
+    else if (ncol <= 32) go(k_mg_coarse<2>);
+    else if (ncol <= 48) go(k_mg_coarse<3>);
+    else go(k_mg_coarse<4>);
+  }
   for (int l = nl - 2; l >= 0; --l) {
     if (wide_p && ncol > 32)
       hipLaunchKernelGGL((k_mg_prolong_v<4, 16>), dim3(xcd_grid(mg.max_n[l], NT / 16, 16384), ni), dim3(NT), 0, s,
