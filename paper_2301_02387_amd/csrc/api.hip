@@ -337,11 +337,12 @@ static void krylov_alloc(mh_op* op, Krylov& K, int m_max, int nblk) {
   const size_t ni = op->ni;
   K.m_max = m_max;
   K.H = op->alloc<double>(ni * 2 * (m_max + 1) * m_max);
-  K.hcur = op->alloc<double>(ni * 2 * (m_max + 1));
   K.scal = op->alloc<double>(ni * 8);
   K.y = op->alloc<double>(ni * 2 * m_max);
   K.nblk = nblk;
   K.part = op->alloc<double>(ni * (size_t)nblk * (2 * (m_max + 1) + 1) + 64);
+  K.part2 = op->alloc<double>(ni * (size_t)nblk * (2 * (m_max + 1) + 1) + 64);
+  K.sums = op->alloc<double>(ni * (size_t)(2 * (m_max + 1) + 1));
 }
 
 // Per-instance Chebyshev coefficients for `iters` iterations from that
@@ -1190,12 +1191,10 @@ static void ensure_krylov(mh_op* op, int m) {
   for (int j = 0; j <= m; ++j) op->V.push_back(op->alloc<double>(len));
   op->Vdev = op->alloc<double*>(m + 1);
   HIPCHK(hipMemcpy(op->Vdev, op->V.data(), (m + 1) * sizeof(double*), hipMemcpyHostToDevice));
-  // enough workgroups to keep the memory system busy (the dot and update passes
-  // stream whole vectors), about 8192 over a batch (grid.y = instance)
-  int64_t nb = std::min<int64_t>(2048, std::max<int64_t>(1, (op->B.mx.NE * op->n + 255) / 256));
-  if (op->ni > 1) nb = std::min<int64_t>(nb, std::max<int64_t>(8, 8192 / op->ni));
-  const int nblk = (int)nb;
+  int nblk = 1, fold = 0;
+  krylov_grid(op->B.mx.NE * op->n, op->ni, &nblk, &fold);
   krylov_alloc(op, op->K, m, nblk);
+  op->K.fold = fold;
   op->m_alloc = m;
 }
 
@@ -1209,17 +1208,13 @@ static int arnoldi(mh_op* op, double* phi, double tau_re, double tau_im, int m, 
   ensure_krylov(op, m);
   Krylov K = op->K;
   K.m_max = op->m_alloc;
-  launch_norm_init(B, phi, K, m, s);
-  launch_krylov_scale(B, phi, op->V[0], K, 5, s);
+  launch_krylov_start(B, phi, op->V[0], K, m, s);
   const bool adaptive = op->krylov_tol > 0.0;
   int built = m;
   for (int k = 0; k < m; ++k) {
     double* w = op->V[k + 1];
     g_apply(op, op->V[k], w, 1, s);
-    launch_mdot(B, op->Vdev, k, w, K, 1, s);
-    launch_orth_dot(B, op->Vdev, k, w, K, s);
-    launch_orth_update(B, op->Vdev, k, w, K, 2, s);
-    launch_krylov_scale(B, w, w, K, 1, s);
+    launch_orthogonalize(B, op->Vdev, k, w, K, s);
     if (adaptive && k + 1 < m) {
       launch_krylov_check(op->ni, K, tau_re, tau_im, k + 1, op->krylov_tol, s);
       HIPCHK(hipMemcpyAsync(op->hostpin, K.scal, (size_t)op->ni * 8 * sizeof(double), hipMemcpyDeviceToHost, s));

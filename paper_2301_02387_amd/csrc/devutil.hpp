@@ -86,6 +86,65 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// A value that every lane of the wave holds alike, as a scalar (kept in scalar
+// registers, so a kernel's uniform coefficients do not take vector registers).
+__device__ __forceinline__ double uniform(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)b >> 32));
+  return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+
+// Rotation of a double within rows of 16 lanes (DPP).
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x120 + N, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x120 + N, 0xf, 0xf, false);
+  return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+// a + b after the halves (H = 32) or the odd and even rows of 16 lanes (H = 16)
+// of the two are exchanged: lanes of the lower part then hold a's sum over both
+// parts, lanes of the upper part b's.
+template <int H>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  typedef uint32_t uvec2_t __attribute__((ext_vector_type(2)));
+  const int64_t ia = __double_as_longlong(a), ib = __double_as_longlong(b);
+  uvec2_t lo, hi;
+  if constexpr (H == 32) {
+    lo = __builtin_amdgcn_permlane32_swap((uint32_t)ia, (uint32_t)ib, false, false);
+    hi = __builtin_amdgcn_permlane32_swap((uint32_t)((uint64_t)ia >> 32), (uint32_t)((uint64_t)ib >> 32), false, false);
+  } else {
+    lo = __builtin_amdgcn_permlane16_swap((uint32_t)ia, (uint32_t)ib, false, false);
+    hi = __builtin_amdgcn_permlane16_swap((uint32_t)((uint64_t)ia >> 32), (uint32_t)((uint64_t)ib >> 32), false, false);
+  }
+  return __longlong_as_double((int64_t)(((uint64_t)hi.x << 32) | lo.x)) +
+         __longlong_as_double((int64_t)(((uint64_t)hi.y << 32) | lo.y));
+}
+// Sums over the wave of NV values at once, out[v] written by one lane (LDS).
+// Two exchange steps leave each row of 16 lanes a quarter of the values, which
+// four rotations add up: about 6 NV instructions against 36 NV for one
+// shuffle tree per value.  v is overwritten.
+template <int NV>
+__device__ __forceinline__ void wave_sum_values(double (&v)[NV], double* out) {
+  constexpr int H1 = (NV + 1) / 2, H2 = (H1 + 1) / 2;
+#pragma unroll
+  for (int i = 0; i < H1; ++i) v[i] = swap_add<32>(v[i], i + H1 < NV ? v[i + H1] : 0.0);
+#pragma unroll
+  for (int i = 0; i < H2; ++i) v[i] = swap_add<16>(v[i], i + H2 < H1 ? v[i + H2] : 0.0);
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < H2; ++i) {
+    double t = v[i];
+    t += row_rotate<8>(t);
+    t += row_rotate<4>(t);
+    t += row_rotate<2>(t);
+    t += row_rotate<1>(t);
+    const int in = i + (g & 1) * H2, idx = in + (g >> 1) * H1;
+    if ((lane & 15) == 0 && in < H1 && idx < NV) out[idx] = t;
+  }
+}
+
 // Sum over a 256-thread block; the result is returned to every thread.
 __device__ __forceinline__ double block_sum_all(double v, double* lds4) {
   v = wave_sum(v);

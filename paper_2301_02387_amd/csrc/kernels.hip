@@ -9,6 +9,7 @@
 // blockIdx.y, batch row offsets from its DevMesh (kernels.hpp).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "devutil.hpp"
@@ -883,309 +884,377 @@ constexpr int KMAX = 25;
 
 __device__ __forceinline__ int64_t kpart_stride(int nblk, int m_max) { return (int64_t)nblk * (2 * (m_max + 1) + 1); }
 
-__global__ void __launch_bounds__(NT) k_mdot(const DevMesh* __restrict__ dm, const double2* const* __restrict__ V,
-                                             int k, const double2* __restrict__ w, int with_norm, int m_max,
+// Row of element e of a packed array of n (1..8) values per row: division by a
+// constant in each branch (n is uniform), which a multiplication replaces.
+__device__ __forceinline__ int64_t row_of(int64_t e, int n) {
+  switch (n) {
+    case 1: return e;
+    case 2: return e >> 1;
+    case 3: return (int64_t)((uint64_t)e / 3u);
+    case 4: return e >> 2;
+    case 5: return (int64_t)((uint64_t)e / 5u);
+    case 6: return (int64_t)((uint64_t)e / 6u);
+    case 7: return (int64_t)((uint64_t)e / 7u);
+    default: return e >> 3;
+  }
+}
+
+// A new basis vector takes three launches: the dots of the first Gram-Schmidt
+// pass (k_mdot), the update with the decision on a second pass (k_orth) and
+// the second update, where one is taken, with the normalisation (k_orth_scale).
+// Each launch leaves one partial sum per workgroup and value, [value][workgroup],
+// and the next one folds them: every workgroup for itself on short vectors
+// (Krylov::fold, at most 256 partials per value, so the fold reads tens of KB
+// from L2 and saves a launch), else a launch of its own with one workgroup per
+// value (k_kry_fold), since hundreds of MB would be read again on long vectors.
+// Measured against eight launches per vector (a fold, the decision, the norm
+// and the scaling apart): H2 (151,750 elements)
+// Arnoldi step 1296 -> 1156 us, H2O (13.2 M elements) 18.1 -> 14.0 ms in these
+// passes over two steps
+constexpr int KT = 512;   // threads of these passes
+constexpr int KNV = 2 * KMAX + 1;
+
+// Sum over the workgroup of one value, returned to every thread.
+__device__ __forceinline__ double kry_sum(double v, double* lds) {
+  v = wave_sum(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int w = 0; w < KT / 64; ++w) t += lds[w];
+  return t;
+}
+
+template <int KM>
+__global__ void __launch_bounds__(KT) k_mdot(const DevMesh* __restrict__ dm, const double2* const* __restrict__ V,
+                                             int k, const double2* __restrict__ w, int m_max,
                                              double* __restrict__ part) {
   INSTANCE;
-  __shared__ double lw[NT / 64][2 * KMAX + 1];
+  constexpr int NV = 2 * KM + 1;
+  __shared__ double lw[KT / 64][NV];
   const int n = d.n;
   const int64_t total = d.NE * n, o = d.oE * n;
-  double hr[KMAX], hi[KMAX], nrm = 0.0;
+  double acc[NV];   // Re, Im of the dot with each V_j, then |w|^2 last
 #pragma unroll
-  for (int j = 0; j < KMAX; ++j) { hr[j] = 0.0; hi[j] = 0.0; }
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
-    const double mi = gbl(d.m)[e / n];
-    const double2 w0 = w[o + e];
+  for (int j = 0; j < NV; ++j) acc[j] = 0.0;
+  for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < total; e += (int64_t)gridDim.x * KT) {
+    const double mi = gbl(d.m)[row_of(e, n)];
+    const double2 w0 = ldg2(w, o + e);
     const double2 we = make_double2(mi * w0.x, mi * w0.y);
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
+    for (int j = 0; j < KM; ++j) {
       if (j <= k) {
-        double2 vj = ldg2(V[j], o + e);
-        hr[j] += vj.x * we.x + vj.y * we.y;
-        hi[j] += vj.x * we.y - vj.y * we.x;
+        const double2 vj = ldg2(V[j], o + e);
+        acc[2 * j] += vj.x * we.x + vj.y * we.y;
+        acc[2 * j + 1] += vj.x * we.y - vj.y * we.x;
       }
     }
-    if (with_norm) nrm += we.x * w0.x + we.y * w0.y;
+    acc[NV - 1] += we.x * w0.x + we.y * w0.y;
   }
-  // every value reduced over its wave by shuffles, then the four waves
-  // combined after one barrier
-  const int nv = 2 * (k + 1) + 1;
-  double* pb = part + blockIdx.y * kpart_stride(gridDim.x, m_max) + (int64_t)blockIdx.x * nv;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (j <= k) {
-      const double a = wave_sum(hr[j]), b = wave_sum(hi[j]);
-      if (lane == 0) {
-        lw[wid][2 * j] = a;
-        lw[wid][2 * j + 1] = b;
-      }
-    }
-  }
-  const double c = wave_sum(nrm);
-  if (lane == 0) lw[wid][nv - 1] = c;
+  wave_sum_values(acc, lw[threadIdx.x >> 6]);
   __syncthreads();
-  if (threadIdx.x < (unsigned)nv) pb[threadIdx.x] = lw[0][threadIdx.x] + lw[1][threadIdx.x] + lw[2][threadIdx.x] + lw[3][threadIdx.x];
+  const int nv = 2 * (k + 1) + 1;
+  if (threadIdx.x < (unsigned)nv) {
+    const int v = (int)threadIdx.x < nv - 1 ? (int)threadIdx.x : NV - 1;
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < KT / 64; ++w) t += lw[w][v];
+    part[blockIdx.y * kpart_stride(gridDim.x, m_max) + (int64_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+  }
 }
 
-// Finish the dots, one workgroup per value: pass 1 sets column k of H, pass 2
-// adds (re-orthogonalisation).
-__global__ void __launch_bounds__(NT) k_mdot_finish(const double* __restrict__ part, int nblk, int k, int m_max,
-                                                    int pass, double2* __restrict__ H, double2* __restrict__ hcur,
-                                                    double* __restrict__ scal) {
+// sums[v] = sum over the workgroups b of part[v][b], v < nv, by one workgroup
+// (16 lanes per value, eight loads in flight), valid to every thread on return.
+__device__ __forceinline__ void fold_values(const double* __restrict__ part, int nblk, int nv, double* sums) {
+  const int g = threadIdx.x >> 4, l = threadIdx.x & 15;
+  const auto* pg = gbl(part);
+  for (int v = g; v < nv; v += KT / 16) {
+    double s = 0.0;
+    for (int b = l; b < nblk; b += 128) {
+      double t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int bb = b + 16 * u;
+        const double x = pg[(int64_t)v * nblk + (bb < nblk ? bb : b)];
+        t[u] = bb < nblk ? x : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += t[u];
+    }
+    s += row_rotate<8>(s);
+    s += row_rotate<4>(s);
+    s += row_rotate<2>(s);
+    s += row_rotate<1>(s);
+    if (l == 0) sums[v] = s;
+  }
+  __syncthreads();
+}
+
+// The same as a launch: sums[i][v] of instance i, one workgroup per value.
+// second: the sums of the second pass, which only instances that take one need.
+__global__ void __launch_bounds__(NT) k_kry_fold(const double* __restrict__ part, int nblk, int m_max,
+                                                 double* __restrict__ sums, const double* __restrict__ scal,
+                                                 int second) {
   __shared__ double lds4[4];
   const int i = blockIdx.y, v = blockIdx.x;
-  part += i * kpart_stride(nblk, m_max);
-  H += (int64_t)i * (m_max + 1) * m_max;
-  hcur += (int64_t)i * (m_max + 1);
-  scal += 8 * i;
-  const int nv = 2 * (k + 1) + 1;
-  if (pass == 2 && scal[6] != 0.0) return;  // one Gram-Schmidt pass was enough (k_orth_decide)
-  const double s = sum_partials(part, nblk, nv, v, lds4);
-  if (threadIdx.x != 0) return;
-  if (v == nv - 1) {
-    if (pass == 1) scal[2] = s;
-    return;
-  }
-  const int j = v >> 1;
-  double* hc = (double*)&hcur[j];
-  hc[v & 1] = s;
-  double* hp = (double*)&H[j + (int64_t)(m_max + 1) * k];
-  if (pass == 1) hp[v & 1] = s;
-  else hp[v & 1] += s;
+  if (second && scal[8 * i + 6] != 0.0) return;
+  const double s = sum_partials(part + i * kpart_stride(nblk, m_max) + (int64_t)v * nblk, nblk, 1, 0, lds4);
+  if (threadIdx.x == 0) sums[(int64_t)i * (2 * (m_max + 1) + 1) + v] = s;
 }
 
-void launch_mdot(const Batch& b, double* const* V, int k, const double* w, Krylov& K, int pass, hipStream_t s) {
-  hipLaunchKernelGGL(k_mdot, dim3(K.nblk, b.ni), dim3(NT), 0, s, b.dm, (const double2* const*)V, k,
-                     (const double2*)w, pass == 1 ? 1 : 0, K.m_max, K.part);
-  hipLaunchKernelGGL(k_mdot_finish, dim3(2 * (k + 1) + 1, b.ni), dim3(NT), 0, s, K.part, K.nblk, k, K.m_max, pass,
-                     (double2*)K.H, (double2*)K.hcur, K.scal);
-}
-
-// Whether the first classical Gram-Schmidt pass suffices (the criterion of
-// Daniel, Gragg, Kaufman and Stewart 1976, on the norm kept by the pass):
-// with the basis orthonormal, |w - V h|^2 = |w|^2 - sum |h_j|^2 after the
-// first pass.  One pass leaves the new vector orthogonal to the basis to about
-// the dots' rounding error times |w| / |w - V h| (measured on random bases of
-// 200,000 rows: 6e-16 at a kept fraction of 0.7, 5e-15 at 0.1), so while the
-// pass keeps at least a tenth of |w| (1/100 of |w|^2) the second pass is
-// skipped (scal[6] = 1): the fused update then forms the norm, and the second
-// update and dot finish return at once.
-__global__ void k_orth_decide(const double2* __restrict__ hcur, double* __restrict__ scal, int k, int m_max) {
-  if (threadIdx.x != 0) return;
-  const int i = blockIdx.x;
-  hcur += (int64_t)i * (m_max + 1);
-  scal += 8 * i;
-  double hs = 0.0;
-  for (int j = 0; j <= k; ++j) hs += hcur[j].x * hcur[j].x + hcur[j].y * hcur[j].y;
-  const double w2 = scal[2];
-  scal[6] = (w2 > 0.0 && w2 - hs >= 0.01 * w2) ? 1.0 : 0.0;
-}
-
-__global__ void __launch_bounds__(NT) k_orth_update(const DevMesh* __restrict__ dm,
-                                                    const double2* const* __restrict__ V, int k,
-                                                    double2* __restrict__ w, const double2* __restrict__ hcur,
-                                                    int with_norm, int m_max, double* __restrict__ part,
-                                                    const double* __restrict__ scal) {
-  INSTANCE;
-  if (with_norm && scal[8 * blockIdx.y + 6] != 0.0) return;  // the first pass was enough
-  __shared__ double lds[8];
-  const int n = d.n;
-  const int64_t total = d.NE * n, o = d.oE * n;
-  hcur += (int64_t)blockIdx.y * (m_max + 1);
-  double2 h[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) h[j] = (j <= k) ? hcur[j] : make_double2(0.0, 0.0);
-  double nrm = 0.0;
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
-    double2 we = w[o + e];
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j)
-      if (j <= k) we = csub(we, cmul(h[j], ldg2(V[j], o + e)));
-    w[o + e] = we;
-    if (with_norm) nrm += gbl(d.m)[e / n] * (we.x * we.x + we.y * we.y);
-  }
-  if (with_norm) {
-    double c = block_sum(nrm, lds);
-    if (threadIdx.x == 0) part[blockIdx.y * kpart_stride(gridDim.x, m_max) + blockIdx.x] = c;
-  }
-}
-
-// The first update of CGS2 fused with the second pass's dot products:
-// w -= sum_j V_j hcur_j, then the partials of V_j^H M w (layout of k_mdot,
-// norm slot 0).  KM >= k + 1 sizes the register arrays.
+// First Gram-Schmidt update w -= sum_j V_j h_j from the dots of k_mdot, then
+// the partials of |w|^2 and, where a second pass is taken, of V^H M w.
+// Whether the first pass suffices is the criterion of Daniel, Gragg, Kaufman
+// and Stewart 1976 on the norm the pass keeps: with the basis orthonormal,
+// |w - V h|^2 = |w|^2 - sum |h_j|^2.  One pass leaves the new vector
+// orthogonal to the basis to about the dots' rounding error times
+// |w| / |w - V h| (measured on random bases of 200,000 rows: 6e-16 at a kept
+// fraction of 0.7, 5e-15 at 0.1), so while the pass keeps at least a tenth of
+// |w| (1/100 of |w|^2) the second pass is skipped (scal[6] = 1).
+// KM >= k + 1 sizes the register arrays.
 template <int KM>
-__global__ void __launch_bounds__(NT) k_orth_dot(const DevMesh* __restrict__ dm, const double2* const* __restrict__ V,
-                                                 int k, double2* __restrict__ w, const double2* __restrict__ hcur,
-                                                 int m_max, double* __restrict__ part, const double* __restrict__ scal) {
+__global__ void __launch_bounds__(KT) k_orth(const DevMesh* __restrict__ dm, const double2* const* __restrict__ V,
+                                             int k, double2* __restrict__ w, int m_max, int fold,
+                                             const double* __restrict__ part1, const double* __restrict__ sums1,
+                                             double* __restrict__ part2, double2* __restrict__ H,
+                                             double* __restrict__ scal) {
   INSTANCE;
-  __shared__ double lw[NT / 64][2 * KM + 1];
-  const int n = d.n;
+  constexpr int NV = 2 * KM + 1;
+  __shared__ double lw[KT / 64][NV];
+  __shared__ double hs[KNV];
+  const int n = d.n, inst = blockIdx.y;
   const int64_t total = d.NE * n, o = d.oE * n;
-  hcur += (int64_t)blockIdx.y * (m_max + 1);
-  if (scal[8 * blockIdx.y + 6] != 0.0) {
-    // single pass: w -= sum_j V_j hcur_j and the partials of |w|_M^2 (layout of
-    // the norm after the second update)
-    double2 h[KM];
+  const int nv = 2 * (k + 1) + 1;
+  part2 += inst * kpart_stride(gridDim.x, m_max);
+  if (fold) {
+    fold_values(part1 + inst * kpart_stride(gridDim.x, m_max), gridDim.x, nv, hs);
+  } else {
+    if (threadIdx.x < (unsigned)nv) hs[threadIdx.x] = sums1[(int64_t)inst * (2 * (m_max + 1) + 1) + threadIdx.x];
+    __syncthreads();
+  }
+  double2 h[KM];
+  double hsq = 0.0;
 #pragma unroll
-    for (int j = 0; j < KM; ++j) h[j] = (j <= k) ? hcur[j] : make_double2(0.0, 0.0);
+  for (int j = 0; j < KM; ++j) {
+    h[j] = make_double2(0.0, 0.0);
+    if (j <= k) h[j] = make_double2(uniform(hs[2 * j]), uniform(hs[2 * j + 1]));
+    hsq += h[j].x * h[j].x + h[j].y * h[j].y;
+  }
+  const double w2 = uniform(hs[nv - 1]);
+  const bool single = w2 > 0.0 && w2 - hsq >= 0.01 * w2;
+  if (blockIdx.x == 0 && threadIdx.x < (unsigned)nv) {
+    double* Hk = (double*)(H + (int64_t)inst * (m_max + 1) * m_max + (int64_t)(m_max + 1) * k);
+    if (threadIdx.x < (unsigned)(nv - 1)) {
+      Hk[threadIdx.x] = hs[threadIdx.x];
+    } else {
+      scal[8 * inst + 2] = w2;
+      scal[8 * inst + 6] = single ? 1.0 : 0.0;
+    }
+  }
+  if (single) {
     double nrm = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
-      double2 we = w[o + e];
+    for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < total; e += (int64_t)gridDim.x * KT) {
+      double2 we = ldg2(w, o + e);
 #pragma unroll
       for (int j = 0; j < KM; ++j)
         if (j <= k) we = csub(we, cmul(h[j], ldg2(V[j], o + e)));
       w[o + e] = we;
-      nrm += gbl(d.m)[e / n] * (we.x * we.x + we.y * we.y);
+      nrm += gbl(d.m)[row_of(e, n)] * (we.x * we.x + we.y * we.y);
     }
-    const double c = block_sum(nrm, &lw[0][0]);
-    if (threadIdx.x == 0) part[blockIdx.y * kpart_stride(gridDim.x, m_max) + blockIdx.x] = c;
+    const double c = kry_sum(nrm, &lw[0][0]);
+    if (threadIdx.x == 0) part2[(int64_t)(nv - 1) * gridDim.x + blockIdx.x] = c;
+    return;
+  }
+  double acc[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) acc[j] = 0.0;
+  for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < total; e += (int64_t)gridDim.x * KT) {
+    double2 we = ldg2(w, o + e);
+#pragma unroll
+    for (int j = 0; j < KM; ++j)
+      if (j <= k) we = csub(we, cmul(h[j], ldg2(V[j], o + e)));
+    w[o + e] = we;
+    const double mi = gbl(d.m)[row_of(e, n)];
+    const double2 wm = make_double2(mi * we.x, mi * we.y);
+    // the basis values are read again (from cache): kept, their registers would
+    // halve the waves of the usual branch above
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < KM; ++j)
+      if (j <= k) {
+        const double2 vj = ldg2(V[j], o + e);
+        acc[2 * j] += vj.x * wm.x + vj.y * wm.y;
+        acc[2 * j + 1] += vj.x * wm.y - vj.y * wm.x;
+      }
+    acc[NV - 1] += wm.x * we.x + wm.y * we.y;
+  }
+  wave_sum_values(acc, lw[threadIdx.x >> 6]);
+  __syncthreads();
+  if (threadIdx.x < (unsigned)nv) {
+    const int v = (int)threadIdx.x < nv - 1 ? (int)threadIdx.x : NV - 1;
+    double t = 0.0;
+#pragma unroll
+    for (int w8 = 0; w8 < KT / 64; ++w8) t += lw[w8][v];
+    part2[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// The new basis vector: the second update where one is taken, scaled by
+// 1 / h_{k+1,k}, h_{k+1,k} = |w|; happy breakdown when h <= 1e-14 |G v_k| (then
+// scale 0).  After a second pass |w|^2 is the first pass's norm less the
+// squares of the second dots, which are rounding-sized against it (the two
+// are comparable only where w itself is rounding noise, the breakdown).
+// nblk: partials per value of k_orth.
+template <int KM>
+__global__ void __launch_bounds__(KT) k_orth_scale(const DevMesh* __restrict__ dm,
+                                                   const double2* const* __restrict__ V, int k,
+                                                   double2* __restrict__ w, int m_max, int fold, int nblk,
+                                                   const double* __restrict__ part2,
+                                                   const double* __restrict__ sums2, double2* __restrict__ H,
+                                                   double* __restrict__ scal) {
+  INSTANCE;
+  __shared__ double lds[KT / 64];
+  __shared__ double hs[KNV];
+  const int n = d.n, inst = blockIdx.y;
+  const int64_t total = d.NE * n, o = d.oE * n;
+  const int nv = 2 * (k + 1) + 1;
+  part2 += inst * kpart_stride(nblk, m_max);
+  H += (int64_t)inst * (m_max + 1) * m_max + (int64_t)(m_max + 1) * k;
+  scal += 8 * inst;
+  const bool single = scal[6] != 0.0;
+  double nrm2 = 0.0;
+  if (single) {
+    for (int b = threadIdx.x; b < nblk; b += KT) nrm2 += part2[(int64_t)(nv - 1) * nblk + b];
+    nrm2 = kry_sum(nrm2, lds);
+  } else {
+    if (fold) {
+      fold_values(part2, nblk, nv, hs);
+    } else {
+      if (threadIdx.x < (unsigned)nv) hs[threadIdx.x] = sums2[(int64_t)inst * (2 * (m_max + 1) + 1) + threadIdx.x];
+      __syncthreads();
+    }
+    nrm2 = hs[nv - 1];
+    for (int v = 0; v < nv - 1; ++v) nrm2 -= hs[v] * hs[v];
+  }
+  const double hn = nrm2 > 0.0 ? sqrt(nrm2) : (nrm2 == nrm2 ? 0.0 : nrm2);   // NaN stays NaN
+  const bool brk = hn <= 1e-14 * sqrt(scal[2]) || !(hn > 0.0);
+  const double sc = brk ? 0.0 : 1.0 / hn;
+  if (blockIdx.x == 0) {
+    if (!single && threadIdx.x < (unsigned)(nv - 1)) ((double*)H)[threadIdx.x] += hs[threadIdx.x];
+    if (threadIdx.x == 0) {
+      H[k + 1] = make_double2(hn, 0.0);
+      scal[1] = sc;
+      if (brk && scal[4] > k + 1) scal[4] = k + 1;
+    }
+  }
+  if (single) {
+    for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < total; e += (int64_t)gridDim.x * KT)
+      w[o + e] = cscale(sc, ldg2(w, o + e));
     return;
   }
   double2 h[KM];
-  double hr[KM], hi[KM];
 #pragma unroll
   for (int j = 0; j < KM; ++j) {
-    h[j] = (j <= k) ? hcur[j] : make_double2(0.0, 0.0);
-    hr[j] = 0.0;
-    hi[j] = 0.0;
+    h[j] = make_double2(0.0, 0.0);
+    if (j <= k) h[j] = make_double2(uniform(hs[2 * j]), uniform(hs[2 * j + 1]));
   }
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
-    double2 we = w[o + e];
-    double2 vj[KM];
+  for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < total; e += (int64_t)gridDim.x * KT) {
+    double2 we = ldg2(w, o + e);
 #pragma unroll
     for (int j = 0; j < KM; ++j)
-      if (j <= k) {
-        vj[j] = ldg2(V[j], o + e);
-        we = csub(we, cmul(h[j], vj[j]));
-      }
-    w[o + e] = we;
-    const double mi = gbl(d.m)[e / n];
-    const double2 wm = make_double2(mi * we.x, mi * we.y);
-#pragma unroll
-    for (int j = 0; j < KM; ++j)
-      if (j <= k) {
-        hr[j] += vj[j].x * wm.x + vj[j].y * wm.y;
-        hi[j] += vj[j].x * wm.y - vj[j].y * wm.x;
-      }
-  }
-  const int nv = 2 * (k + 1) + 1;
-  double* pb = part + blockIdx.y * kpart_stride(gridDim.x, m_max) + (int64_t)blockIdx.x * nv;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-  for (int j = 0; j < KM; ++j)
-    if (j <= k) {
-      const double a = wave_sum(hr[j]), b = wave_sum(hi[j]);
-      if (lane == 0) {
-        lw[wid][2 * j] = a;
-        lw[wid][2 * j + 1] = b;
-      }
-    }
-  if (lane == 0) lw[wid][nv - 1] = 0.0;
-  __syncthreads();
-  if (threadIdx.x < (unsigned)nv)
-    pb[threadIdx.x] = lw[0][threadIdx.x] + lw[1][threadIdx.x] + lw[2][threadIdx.x] + lw[3][threadIdx.x];
-}
-
-// h_{k+1,k} = |w|; happy breakdown when h <= 1e-14 |G v_k| (then scale 0).
-__global__ void k_norm_finish(const double* __restrict__ part, int nblk, int k, int m_max, double2* __restrict__ H,
-                              double* __restrict__ scal) {
-  __shared__ double lds4[4];
-  const int i = blockIdx.y;
-  part += i * kpart_stride(nblk, m_max);
-  H += (int64_t)i * (m_max + 1) * m_max;
-  scal += 8 * i;
-  const double s = sum_partials(part, nblk, 1, 0, lds4);
-  if (threadIdx.x != 0) return;
-  double h = sqrt(s);
-  double wn = sqrt(scal[2]);
-  H[(k + 1) + (int64_t)(m_max + 1) * k] = make_double2(h, 0.0);
-  if (h <= 1e-14 * wn || !(h > 0.0)) {
-    scal[1] = 0.0;
-    if (scal[4] > k + 1) scal[4] = k + 1;
-  } else {
-    scal[1] = 1.0 / h;
+      if (j <= k) we = csub(we, cmul(h[j], ldg2(V[j], o + e)));
+    w[o + e] = cscale(sc, we);
   }
 }
 
-void launch_orth_update(const Batch& b, double* const* V, int k, double* w, Krylov& K, int pass, hipStream_t s) {
-  hipLaunchKernelGGL(k_orth_update, dim3(K.nblk, b.ni), dim3(NT), 0, s, b.dm, (const double2* const*)V, k,
-                     (double2*)w, (const double2*)K.hcur, pass == 2 ? 1 : 0, K.m_max, K.part, (const double*)K.scal);
-  if (pass == 2)
-    hipLaunchKernelGGL(k_norm_finish, dim3(1, b.ni), dim3(NT), 0, s, K.part, K.nblk, k, K.m_max, (double2*)K.H,
-                       K.scal);
-}
-
-void launch_orth_dot(const Batch& b, double* const* V, int k, double* w, Krylov& K, hipStream_t s) {
+template <int KM>
+static void orthogonalize(const Batch& b, double* const* V, int k, double* w, Krylov& K, hipStream_t s) {
   const dim3 g(K.nblk, b.ni);
   const auto* Vc = (const double2* const*)V;
-  const double* sc = K.scal;
-  hipLaunchKernelGGL(k_orth_decide, dim3(b.ni), dim3(64), 0, s, (const double2*)K.hcur, K.scal, k, K.m_max);
-  if (k + 1 <= 4)
-    hipLaunchKernelGGL(k_orth_dot<4>, g, dim3(NT), 0, s, b.dm, Vc, k, (double2*)w, (const double2*)K.hcur, K.m_max,
-                       K.part, sc);
-  else if (k + 1 <= 8)
-    hipLaunchKernelGGL(k_orth_dot<8>, g, dim3(NT), 0, s, b.dm, Vc, k, (double2*)w, (const double2*)K.hcur, K.m_max,
-                       K.part, sc);
-  else if (k + 1 <= 13)
-    hipLaunchKernelGGL(k_orth_dot<13>, g, dim3(NT), 0, s, b.dm, Vc, k, (double2*)w, (const double2*)K.hcur, K.m_max,
-                       K.part, sc);
-  else
-    hipLaunchKernelGGL(k_orth_dot<KMAX>, g, dim3(NT), 0, s, b.dm, Vc, k, (double2*)w, (const double2*)K.hcur,
-                       K.m_max, K.part, sc);
-  hipLaunchKernelGGL(k_mdot_finish, dim3(2 * (k + 1) + 1, b.ni), dim3(NT), 0, s, K.part, K.nblk, k, K.m_max, 2,
-                     (double2*)K.H, (double2*)K.hcur, K.scal);
+  const int nv = 2 * (k + 1) + 1, fold = K.fold ? 1 : 0;
+  hipLaunchKernelGGL(k_mdot<KM>, g, dim3(KT), 0, s, b.dm, Vc, k, (const double2*)w, K.m_max, K.part);
+  if (!fold)
+    hipLaunchKernelGGL(k_kry_fold, dim3(nv, b.ni), dim3(NT), 0, s, K.part, K.nblk, K.m_max, K.sums,
+                       (const double*)K.scal, 0);
+  hipLaunchKernelGGL(k_orth<KM>, g, dim3(KT), 0, s, b.dm, Vc, k, (double2*)w, K.m_max, fold, (const double*)K.part,
+                     (const double*)K.sums, K.part2, (double2*)K.H, K.scal);
+  if (!fold)
+    hipLaunchKernelGGL(k_kry_fold, dim3(nv, b.ni), dim3(NT), 0, s, K.part2, K.nblk, K.m_max, K.sums,
+                       (const double*)K.scal, 1);
+  hipLaunchKernelGGL(k_orth_scale<KM>, dim3(nblocks(b.mx.NE * b.mx.n, KT, 2048), b.ni), dim3(KT), 0, s, b.dm, Vc, k,
+                     (double2*)w, K.m_max, fold, K.nblk, (const double*)K.part2, (const double*)K.sums,
+                     (double2*)K.H, K.scal);
 }
 
-__global__ void k_scale_by(const DevMesh* __restrict__ dm, const double2* __restrict__ src,
-                           double2* __restrict__ dst, const double* __restrict__ scal, int which) {
-  INSTANCE;
-  const int64_t total = d.NE * d.n, o = d.oE * d.n;
-  const double f = scal[8 * blockIdx.y + which];
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT)
-    dst[o + e] = cscale(f, src[o + e]);
+void launch_orthogonalize(const Batch& b, double* const* V, int k, double* w, Krylov& K, hipStream_t s) {
+  if (k + 1 <= 4) orthogonalize<4>(b, V, k, w, K, s);
+  else if (k + 1 <= 8) orthogonalize<8>(b, V, k, w, K, s);
+  else if (k + 1 <= 13) orthogonalize<13>(b, V, k, w, K, s);
+  else orthogonalize<KMAX>(b, V, k, w, K, s);
 }
 
-void launch_krylov_scale(const Batch& b, const double* src, double* dst, Krylov& K, int which, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_by, dim3(nblocks(b.mx.NE * b.mx.n, NT, 8192), b.ni), dim3(NT), 0, s, b.dm,
-                     (const double2*)src, (double2*)dst, K.scal, which);
+// Workgroups of the passes over a Krylov vector of `total` elements, and
+// whether their partial sums are folded by the launch that needs them: one
+// short vector (up to four elements per thread of 256 workgroups).  Long
+// vectors: enough workgroups to keep the memory system busy, about 4096 over a
+// batch.
+void krylov_grid(int64_t total, int ni, int* nblk, int* fold) {
+  *fold = ni == 1 && total <= (int64_t)4 * 256 * KT;
+  int64_t nb = std::min<int64_t>(*fold ? 256 : 2048, std::max<int64_t>(1, (total + KT - 1) / KT));
+  if (ni > 1) nb = std::min<int64_t>(nb, std::max<int64_t>(8, 4096 / ni));
+  *nblk = (int)nb;
 }
 
-__global__ void __launch_bounds__(NT) k_norm_part(const DevMesh* __restrict__ dm, const double2* __restrict__ x,
+__global__ void __launch_bounds__(KT) k_norm_part(const DevMesh* __restrict__ dm, const double2* __restrict__ x,
                                                   int m_max, double* __restrict__ part) {
   INSTANCE;
-  __shared__ double lds[8];
+  __shared__ double lds[KT / 64];
   const int n = d.n;
   const int64_t total = d.NE * n, o = d.oE * n;
   double s = 0.0;
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
-    const double2 v = x[o + e];
-    s += gbl(d.m)[e / n] * (v.x * v.x + v.y * v.y);
+  for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < total; e += (int64_t)gridDim.x * KT) {
+    const double2 v = ldg2(x, o + e);
+    s += gbl(d.m)[row_of(e, n)] * (v.x * v.x + v.y * v.y);
   }
-  double c = block_sum(s, lds);
+  const double c = kry_sum(s, lds);
   if (threadIdx.x == 0) part[blockIdx.y * kpart_stride(gridDim.x, m_max) + blockIdx.x] = c;
 }
 
-__global__ void k_beta_finish(const double* __restrict__ part, int nblk, int m, double* __restrict__ scal,
-                              double2* __restrict__ H, int m_max) {
+// V_0 = phi / |phi| from the norm's partials (folded by every workgroup);
+// workgroup 0 clears H and files the scalars.
+__global__ void __launch_bounds__(KT) k_krylov_start(const DevMesh* __restrict__ dm, const double2* __restrict__ phi,
+                                                     double2* __restrict__ v0, const double* __restrict__ part,
+                                                     int nblk, int m, double* __restrict__ scal,
+                                                     double2* __restrict__ H, int m_max) {
+  INSTANCE;
+  __shared__ double lds[KT / 64];
   const int i = blockIdx.y;
+  const int64_t total = d.NE * d.n, o = d.oE * d.n;
   part += i * kpart_stride(nblk, m_max);
-  H += (int64_t)i * (m_max + 1) * m_max;
-  scal += 8 * i;
-  for (int t = threadIdx.x; t < (m_max + 1) * m_max; t += blockDim.x) H[t] = make_double2(0.0, 0.0);
-  __shared__ double lds4[4];
-  const double s = sum_partials(part, nblk, 1, 0, lds4);
-  if (threadIdx.x != 0) return;
-  double beta = sqrt(s);
-  scal[0] = beta;
-  scal[5] = beta > 0.0 ? 1.0 / beta : 0.0;
-  scal[4] = m;
-  scal[3] = 0.0;
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += KT) s += part[b];
+  const double beta = sqrt(kry_sum(s, lds));
+  const double ib = beta > 0.0 ? 1.0 / beta : 0.0;
+  if (blockIdx.x == 0) {
+    H += (int64_t)i * (m_max + 1) * m_max;
+    for (int t = threadIdx.x; t < (m_max + 1) * m_max; t += KT) H[t] = make_double2(0.0, 0.0);
+    if (threadIdx.x == 0) {
+      scal += 8 * i;
+      scal[0] = beta;
+      scal[5] = ib;
+      scal[4] = m;
+      scal[3] = 0.0;
+    }
+  }
+  for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < total; e += (int64_t)gridDim.x * KT)
+    v0[o + e] = cscale(ib, ldg2(phi, o + e));
 }
 
-void launch_norm_init(const Batch& b, const double* phi, Krylov& K, int m, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm_part, dim3(K.nblk, b.ni), dim3(NT), 0, s, b.dm, (const double2*)phi, K.m_max, K.part);
-  hipLaunchKernelGGL(k_beta_finish, dim3(1, b.ni), dim3(NT), 0, s, K.part, K.nblk, m, K.scal, (double2*)K.H,
+void launch_krylov_start(const Batch& b, const double* phi, double* v0, Krylov& K, int m, hipStream_t s) {
+  hipLaunchKernelGGL(k_norm_part, dim3(K.nblk, b.ni), dim3(KT), 0, s, b.dm, (const double2*)phi, K.m_max, K.part);
+  hipLaunchKernelGGL(k_krylov_start, dim3(nblocks(b.mx.NE * b.mx.n, KT, 2048), b.ni), dim3(KT), 0, s, b.dm,
+                     (const double2*)phi, (double2*)v0, (const double*)K.part, K.nblk, m, K.scal, (double2*)K.H,
                      K.m_max);
 }
 

@@ -182,19 +182,19 @@ void launch_build_U_full(const Batch& b, const double* W, const double* Gamma, c
 struct Krylov {
   int m_max = 0;
   double* H = nullptr;       // device c128 [ni][(m_max+1) x m_max], H[i + (m_max+1) j]
-  double* hcur = nullptr;    // device c128 [ni][m_max+1]
-  double* scal = nullptr;    // [ni][8]: [0]=beta [1]=next scale [2]=|w|^2 [3]=err [4]=m_eff [5]=1/beta
+  double* scal = nullptr;    // [ni][8]: [0]=beta [1]=last scale [2]=|w|^2 [3]=err [4]=m_eff [5]=1/beta [6]=one pass was enough
   double* y = nullptr;       // device c128 [ni][m_max]
-  double* part = nullptr;    // partial sums [ni][nblk][...]
+  double* part = nullptr;    // partial sums of the first and second pass [ni][value][nblk]
+  double* part2 = nullptr;
+  double* sums = nullptr;    // [ni][2 (m_max+1) + 1] folded values (fold = 0)
   int nblk = 0;
+  int fold = 0;              // the partials are folded by the launch that needs them
 };
-void launch_norm_init(const Batch& b, const double* phi, Krylov& K, int m, hipStream_t s);
-void launch_mdot(const Batch& b, double* const* V, int k, const double* w, Krylov& K, int pass, hipStream_t s);
-void launch_orth_update(const Batch& b, double* const* V, int k, double* w, Krylov& K, int pass, hipStream_t s);
-// The first CGS2 update fused with the second pass's dots (w -= V hcur, then
-// V^H M w finished into H and hcur as the second pass of launch_mdot).
-void launch_orth_dot(const Batch& b, double* const* V, int k, double* w, Krylov& K, hipStream_t s);
-void launch_krylov_scale(const Batch& b, const double* src, double* dst, Krylov& K, int which, hipStream_t s);
+void krylov_grid(int64_t total, int ni, int* nblk, int* fold);
+// V_0 = phi / |phi|_M, H cleared, dimension m
+void launch_krylov_start(const Batch& b, const double* phi, double* v0, Krylov& K, int m, hipStream_t s);
+// w orthogonalised against V_0 .. V_k (CGS2) and normalised in place; column k of H
+void launch_orthogonalize(const Batch& b, double* const* V, int k, double* w, Krylov& K, hipStream_t s);
 void launch_expm(int ni, Krylov& K, double tau_re, double tau_im, hipStream_t s);
 // Adaptive dimension: where the error estimate of dimension m_try meets tol,
 // the instance's dimension (scal[4]) becomes m_try.

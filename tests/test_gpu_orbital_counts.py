@@ -56,3 +56,69 @@ def test_multigrid_column_tiles(name, n):
         scale = np.sqrt(np.sum(m * np.abs(ref[k]) ** 2))
         assert np.sqrt(np.sum(m * np.abs(got[k] - ref[k]) ** 2)) <= 1e-10 * scale
         assert np.abs(got[k] - ref[k]).max() <= 1e-10 * np.abs(ref[k]).max()
+
+
+def frozen(P, op, n, seed, E=0.013, copies=1):
+    """Oracle frozen operator and the library (a handle of `copies` equal instances) frozen on the same inputs."""
+    from oracle.ci import CISpace
+    from oracle.mctdhf import Frozen
+    from synth import random_ci
+    c = orbitals(P, n, seed)
+    cs = CISpace(n, (n + 1) // 2, n // 2)
+    gam, Gam = cs.rdms(random_ci(cs.dim, seed + 1))
+    W = poisson_solver(P.ops).pair_potentials(c)
+    rep = lambda a: dev(np.concatenate([a] * copies))  # noqa: E731
+    op.freeze(rep(P.to_lib_orb(c)), rep(gam), rep(Gam), E, rep(P.W_to_lib(W, n)))
+    return c, Frozen(P.ops, c, gam, Gam, E, W)
+
+
+def check_arnoldi(P, op, c, fr, tau, m, copies=1):
+    import torch
+    from oracle.mctdhf import arnoldi_step
+    from tests.lib_cases import rel_err_cols, max_rel_cols
+    x = dev(np.concatenate([P.to_lib_orb(c)] * copies))
+    err, m_used = op.arnoldi_step(x, tau, m)
+    torch.cuda.synchronize()
+    ref, err_ref, m_ref, H = arnoldi_step(P.ops, fr.G, c, tau, m)
+    assert m_used == m_ref
+    for part in np.split(x.cpu().numpy(), copies):
+        got = P.from_lib_dof(part)
+        assert rel_err_cols(got, ref) < 1e-10
+        assert max_rel_cols(got, ref) < 1e-10
+    assert abs(err - err_ref) <= 1e-6 * err_ref + 1e-14
+    return H
+
+
+@pytest.mark.parametrize("copies", [1, 2])
+@pytest.mark.parametrize("n,m", [(1, 4), (2, 5), (3, 8), (4, 9), (5, 13), (6, 12), (7, 14), (8, 12)])
+def test_arnoldi_vectors(n, m, copies):
+    """Krylov vectors of every orbital count and the register tiles' edges (4,
+    8, 13 basis vectors), with the partial sums folded by the next launch (one
+    instance) and by a launch of their own (a batch)."""
+    import paper_2301_02387_amd as mh
+    P = pair("tiny_q1")
+    if copies == 1:
+        op = operator(P, n)
+    else:
+        op = mh.Operator.batch([P.mesh] * copies, [P.w["nuclei"]] * copies, n, (n + 1) // 2, n // 2)
+    c, fr = frozen(P, op, n, 60 + n, copies=copies)
+    check_arnoldi(P, op, c, fr, 0.02, m, copies)
+
+
+@pytest.mark.parametrize("copies", [1, 2])
+def test_arnoldi_second_pass(copies):
+    """A start vector near an eigenvector of G: the first Gram-Schmidt pass
+    keeps less than a tenth of G v_0, so the second one runs."""
+    import paper_2301_02387_amd as mh
+    P = pair("beta_one")
+    nuc = P.w["nuclei"]
+    op = mh.Operator(P.mesh, nuc, 1, 1, 0) if copies == 1 else mh.Operator.batch([P.mesh] * 2, [nuc] * 2, 1, 1, 0)
+    _, fr = frozen(P, op, 1, 80, copies=copies)
+    N = P.N
+    G = np.stack([fr.G(e[:, None])[:, 0] for e in np.eye(N, dtype=complex)], axis=1)
+    lam, X = np.linalg.eig(G)
+    x = X[:, np.argsort(-np.abs(lam))[3]]
+    rng = np.random.default_rng(5)
+    x = x + 1e-3 * np.linalg.norm(x) / np.sqrt(N) * (rng.standard_normal(N) + 1j * rng.standard_normal(N))
+    H = check_arnoldi(P, op, x[:, None], fr, 0.02, 6, copies)
+    assert np.abs(H[1, 0]) < 0.1 * np.linalg.norm(H[:2, 0])
