@@ -71,20 +71,16 @@ def stored_matrix_bytes(N, nnz, n_inst):
     return 12 * nnz + 4 * (N + n_inst)
 
 
-def poisson_algorithmic_bytes(info, op, fused=False):
+def poisson_algorithmic_bytes(info, op, float_operand=False):
     """Matrix-free bytes of one Poisson operator application on the pair
     columns (the Laplacian applied cell by cell from the 1D Gauss-Lobatto
     tables): operand rows read and result rows written once (8 B per column
-    each), the cell->node maps (int32), the hanging-node constraint rows (int32
-    index + weight) and h per cell.  With the CG direction formed in the same
-    pass (schedule bit 3) also r and the previous direction read, the new
-    direction written and the diagonal read."""
+    each; 4 B for the operand where the finest multigrid level keeps floats,
+    schedule bits 4 and 6), the cell->node maps (int32), the hanging-node
+    constraint rows (int32 index + weight) and h per cell."""
     P3 = (info["p"] + 1) ** 3
     N, ncol, nC = op.n_dof, op.n_pair_cols, info["n_cells"]
-    b = 16 * ncol * N + 4 * P3 * nC + 12 * info["hang_nnz"] + 8 * nC
-    if fused:
-        b += 16 * ncol * N + 8 * N
-    return b
+    return (12 if float_operand else 16) * ncol * N + 4 * P3 * nC + 12 * info["hang_nnz"] + 8 * nC
 
 
 def rhs_algorithmic_bytes(info, op, ecs=False):
@@ -316,9 +312,8 @@ def run_single(name, args, torch, with_adjoint, with_cpu):
     kern = {"stencil_orb": {"avg_ms": k_orb[0], "count": k_orb[1]},
             "poisson_spmv": {"avg_ms": k_poi[0], "count": k_poi[1]}}
     dom = max(kern, key=lambda k: kern[k]["avg_ms"] * kern[k]["count"])
-    fused = bool(sched["poisson"][0] & 8)
     if dom == "poisson_spmv":
-        byts = poisson_algorithmic_bytes(info, op, fused)
+        byts = poisson_algorithmic_bytes(info, op, (sched["poisson"][0] & 80) == 80)
         over = stored_matrix_bytes(op.n_dof, op.n_poisson_nnz, op.n_inst)
     else:
         byts, over = orbital_pass_bytes(info, op, bool(ecs)), 0
@@ -692,7 +687,7 @@ def run_batch(args):
     # matrix-free bytes summed over the instances (one aggregate mesh record)
     agg = {"p": w0["p"], "n_cells": n_cells, "hang_nnz": sum(mm.info["hang_nnz"] for mm in meshes),
            "n_full": sum(mm.info["n_full"] for mm in meshes)}
-    spmv_b = poisson_algorithmic_bytes(agg, op, bool(sched["poisson"][0] & 8))
+    spmv_b = poisson_algorithmic_bytes(agg, op, (sched["poisson"][0] & 80) == 80)
     spmv_over = stored_matrix_bytes(op.n_dof, op.n_poisson_nnz, op.n_inst)
     P3 = (w0["p"] + 1) ** 3
     NE, N, n = op.n_ext, op.n_dof, op.n_orb

@@ -421,9 +421,8 @@ int mh_kernel_timing(mh_op* op, int32_t which, int32_t enable, double* avg_ms, i
  * the column count is a multiple of 16 and at least 32; bit 2: rows of the
  * assembled operator with more than 48
  * entries (hanging-node masters) taken by whole waves in reserved workgroups
- * of the same launch; bit 3: the CG direction formed inside the operator
- * pass (two launches per CG iteration instead of three; fewer launches, more
- * loads per entry); bit 4: CG preconditioned by the geometric multigrid
+ * of the same launch; bit 3: accepted and without effect (every CG iteration
+ * is an operator pass and one pass over the vectors); bit 4: CG preconditioned by the geometric multigrid
  * V-cycle instead of the diagonal (a hierarchy per instance, built on first
  * use; the V-cycles of a batch run level by level in shared launches); bit 5:
  * the rows of at most 48 entries read from a sliced-ELL copy of the operator

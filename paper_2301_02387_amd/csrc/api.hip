@@ -647,8 +647,7 @@ static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_de
   launch_zero(P.acc, tE * ncol, s);
   P.p = op->alloc<double>(tE * ncol);
   launch_zero(P.p, tE * ncol, s);
-  P.p2 = op->alloc<double>(tE * ncol);
-  launch_zero(P.p2, tE * ncol, s);
+  P.w = op->alloc<double>(tE * ncol);
   P.r = op->alloc<double>(tE * ncol);
   P.q = op->alloc<double>(tE * ncol);
   P.sc = op->alloc<double>((size_t)ni * 8 * ncol);
@@ -657,7 +656,7 @@ static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_de
   launch_zero(P.red, (size_t)ni * RED_SLOTS * ncol, s);
   if (ni == 1) {  // the largest operator-pass grid (65,536 sweeping and up to 2,056 long-row workgroups)
     B.spart_cap = (int64_t)(65536 + 4096) * std::max(ncol, 2 * n);
-    B.spart = op->alloc<double>((size_t)B.spart_cap);
+    B.spart = op->alloc<double>((size_t)(B.spart_cap + SPART_RZ));
   }
   P.part_stride = (int64_t)8192 * 2 * ncol;
   P.part = op->alloc<double>((size_t)ni * P.part_stride);
@@ -1013,8 +1012,8 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
 
 // CG preconditioned by one multigrid V-cycle per instance and iteration,
 // after launch_cg_start (r_0 in P.r, accumulators initialised): z = B r,
-// rz = r.z, p = z + beta p, then the same operator and update passes as the
-// Jacobi CG (alpha = r.z / p.q), with every instance's own scalars.  With a
+// then the same operator and vector passes as the Jacobi CG, with every
+// instance's own scalars.  With a
 // smoothed finest level, r.z is accumulated by the cycle's last smoothing
 // pass; else it takes passes of its own.
 // Converged (1), not (0) or non-finite (-1).  The check (a host round trip)
@@ -1030,7 +1029,6 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
   PoissonWs& P = op->P;
   const MgDev& mg = *op->mg;
   const int ncol = op->ncol, ni = op->ni;
-  const int64_t N = B.mx.N;
   // Poisson schedule bits 8-9: Chebyshev smoothing degree 2 + their value
   op->mg->nu = 2 + ((B.mx.sched_poi >> 8) & 3);
   const int nu = mg.nu;
@@ -1040,7 +1038,7 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
   // only; the CG vectors, its operator pass and every sum stay double)
   const bool f32 = fused && (B.mx.sched_poi & 64);
   op->mg->lv[0] = f32 ? mg.lv0_float : mg.lv0_double;
-  int rz_slot = RED_RZ;
+  int rz_slot = RED_RZ, rz_rows = 0;   // slot of r.z; partial sums of it still to be folded
   // the level-0 correction alternates between two buffers (a smoothing step
   // reads one and writes the other): zc = 1 while it is in the second.  The
   // pre-smoothing starts in the buffer that makes it end in the first, where
@@ -1058,7 +1056,7 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
       float* zi = zc ? mg.z0bf : mg.z0f;
       float* zo = zc ? mg.z0f : mg.z0bf;
       zc ^= 1;
-      launch_mg_cheb_step_f(B, zi, mg.rf, zo, mg.d0f, P.red, ncol, k, rz ? rz_slot : -1, st);
+      rz_rows = launch_mg_cheb_step_f(B, zi, mg.rf, zo, mg.d0f, P.red, ncol, k, rz ? rz_slot : -1, st);
     };
   } else {
     ops.resid = [&](hipStream_t st) { launch_mg_resid(B, mg.z0, P.r, mg.t0, ncol, op->mg_red, st); };
@@ -1070,7 +1068,7 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
       double* zi = zc ? mg.z0b : mg.z0;
       double* zo = zc ? mg.z0 : mg.z0b;
       zc ^= 1;
-      launch_mg_cheb_step(B, zi, P.r, zo, mg.d0, P.red, ncol, k, rz ? rz_slot : -1, st);
+      rz_rows = launch_mg_cheb_step(B, zi, P.r, zo, mg.d0, P.red, ncol, k, rz ? rz_slot : -1, st);
     };
   }
   // the preconditioned residual after a fused cycle (single level: the dense solve's z0)
@@ -1091,24 +1089,9 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
     if (f32) launch_to_float(P.r, mg.rf, (int64_t)B.tE * ncol, s);  // later residuals by the update pass
     precondition(0);
   }
-  // one instance: each iteration's x += alpha p is deferred to the next
-  // direction pass, which reads p anyway (and to cg_xfinal after the last);
-  // a batch keeps it in the update pass (its instances stop at different
-  // iterations)
-  const bool defer = ni == 1;
-  double* xd = defer ? W : nullptr;
   while (conv == 0 && k < kmax) {
-    double* pcur = (k % 2) ? P.p2 : P.p;
-    double* pold = (k % 2) ? P.p : P.p2;
-    const int pq_prev = RED_PQ + (k + 1) % 2;   // the p.q slot of iteration k - 1
-    if (f32)
-      mg_dir(B.dm, ni, N, ncol, zf, pold, pcur, P.red, RED_RZ + k % 3, k > 0 ? RED_RZ + (k - 1) % 3 : -1,
-             RED_RR + k % 2, xd, pq_prev, s);
-    else
-      mg_dir(B.dm, ni, N, ncol, z, pold, pcur, P.red, RED_RZ + k % 3, k > 0 ? RED_RZ + (k - 1) % 3 : -1,
-             RED_RR + k % 2, xd, pq_prev, s);
-    launch_cg_apply_plain(B, P, pcur, k, s);
-    launch_cg_update(B, W, P, pcur, k, s, f32 ? mg.rf : nullptr, defer ? 0 : 1);
+    if (f32) launch_cg_iteration(B, W, P, zf, mg.rf, rz_rows, k, s);
+    else launch_cg_iteration(B, W, P, z, nullptr, rz_rows, k, s);
     if (op->cg_done) launch_cg_done(B, P, k, op->rtol, s);  // converged instances skip the rest
     ++k;
     P.it = k;
@@ -1120,8 +1103,7 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
     if (conv != 0) break;
     precondition(k);
   }
-  if (defer && k > 0)   // the last iteration's x += alpha p
-    cg_xfinal(B.dm, ni, N, ncol, W, ((k - 1) % 2) ? P.p2 : P.p, P.red, RED_RZ + (k - 1) % 3, RED_PQ + (k - 1) % 2, s);
+  launch_cg_finish(B, W, P, k, s);
   if (op->cg_done) launch_zero_int(op->cg_done, ni, s);  // no flag outside the CG
   if (iters) *iters = k;
   if (fixed == 0) op->cg_hint = k;
@@ -1148,6 +1130,7 @@ static int cg_iterate(mh_op* op, double* W, int* iters, hipStream_t s) {
     conv = poisson_converged(op, s);
     if (conv != 0) break;
   }
+  launch_cg_finish(B, W, P, it, s);
   if (iters) *iters = it;
   return conv;
 }

@@ -24,8 +24,10 @@ __device__ __forceinline__ __attribute__((address_space(1))) T* gblw(T* p) {
 }
 
 // 16-byte global load of element i of a double2 array (double2 is a class
-// type that does not copy from another address space; the native vector type does).
-typedef double dvec2_t __attribute__((ext_vector_type(2)));
+// type that does not copy from another address space; the native vector type
+// does).  Aligned to 8 bytes only: a caller's array may start at any double,
+// and global 16-byte loads need no more on this target.
+typedef double dvec2_t __attribute__((ext_vector_type(2), aligned(8)));
 __device__ __forceinline__ double2 ldg2(const double2* p, int64_t i) {
   const dvec2_t v = ((const __attribute__((address_space(1))) dvec2_t*)p)[i];
   return make_double2(v.x, v.y);

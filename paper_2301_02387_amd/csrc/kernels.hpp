@@ -84,8 +84,8 @@ struct DevMesh {
   // launch schedules (set by mh_tune): bit 0 = XCD-contiguous sweep; orbital bit 1 = interface
   // solve by Chebyshev even where a dense inverse is held, bit 2 = stiffness part by the
   // assembled operator; Poisson bit 1 =
-  // column blocks of 16, bit 2 = long rows by whole waves, bit 3 = CG direction formed
-  // inside the operator pass, bit 4 = geometric multigrid preconditioner (a
+  // column blocks of 16, bit 2 = long rows by whole waves, bit 3 = without
+  // effect, bit 4 = geometric multigrid preconditioner (a
   // hierarchy per instance), bit 5 = short rows from the sliced-ELL copy (long
   // rows by waves); grid caps (per instance)
   int sched_orb = 1, sched_poi = 13, grid_orb = 65536, grid_poi = 8192;
@@ -114,6 +114,8 @@ constexpr int KT_LONG = 48;
 constexpr int SELL_H = 64;
 constexpr int SELL_WINDOW = 4096;
 
+constexpr int64_t SPART_RZ = 8192;
+
 // A batch as seen by the launchers: the device array of instances, and a host
 // record with the shared parameters and the largest per-instance sizes (grid
 // shapes are taken from these; workgroups beyond an instance's size idle).
@@ -124,8 +126,10 @@ struct Batch {
   int64_t tE = 0, tF = 0, tMa = 0;  // batch totals of extended, full and master rows
   int cheb_iters = 0;           // Chebyshev iterations (the largest instance count)
   // one instance: the Poisson operator passes leave their per-workgroup p.q
-  // (r.z) sums here, [workgroup][column], folded by a second small launch
-  // instead of every workgroup adding into the same accumulators
+  // (r.z) sums here, [workgroup][column], folded by the launch that needs them
+  // or by a small one of its own instead of every workgroup adding into the
+  // same accumulators; SPART_RZ more doubles after the first spart_cap hold
+  // the r.z sums folded by the CG's vector pass
   double* spart = nullptr;
   int64_t spart_cap = 0;        // doubles
 };
@@ -207,12 +211,12 @@ void launch_combine(const Batch& b, double* const* V, int m, double* phi, Krylov
 struct PoissonWs {
   int ncol = 0, nharm = 0, lmax = 0;
   double* acc = nullptr;   // [tE][ncol]
-  double* p = nullptr;     // [tE][ncol] search direction (two buffers, alternating by iteration)
-  double* p2 = nullptr;
+  double* p = nullptr;     // [tE][ncol] search direction
+  double* w = nullptr;     // [tE][ncol] K z
   double* r = nullptr;     // [tE][ncol]
   double* q = nullptr;     // [tE][ncol]
   double* sc = nullptr;    // [ni][8][ncol] scalars
-  double* red = nullptr;   // [ni][RED_SLOTS][ncol] atomic accumulators (rz x3, pq x2, rr x2; see stencil.hip)
+  double* red = nullptr;   // [ni][RED_SLOTS][ncol] atomic accumulators (RED_*; see stencil.hip)
   int it = 0;              // CG iteration within the running solve
   double* part = nullptr;  // partials [ni][grid][2 ncol]
   int64_t part_stride = 0;
@@ -225,9 +229,9 @@ struct PoissonWs {
   int ev_cap = 0, ev_used = 0;
 };
 enum { SC_RZ = 0, SC_PQ = 1, SC_ALPHA = 2, SC_BETA = 3, SC_RR = 4, SC_BB = 5, SC_RZN = 6 };
-// accumulator slots: r.D^-1 r of iteration k in RED_RZ + k % 3, p.q in RED_PQ + k % 2,
-// r.r after iteration k in RED_RR + k % 2
-enum { RED_RZ = 0, RED_PQ = 3, RED_RR = 5, RED_SLOTS = 8 };
+// accumulator slots: r.z of iteration k in RED_RZ + k % 3, z.w in RED_PQ + k % 2,
+// r.r after iteration k in RED_RR + k % 2, p.q in RED_ETA + k % 2
+enum { RED_RZ = 0, RED_PQ = 3, RED_RR = 5, RED_ETA = 7, RED_SLOTS = 9 };
 // slot of r.r after the last iteration of a solve that took `it` iterations (it >= 1)
 inline int red_rr_slot(int it) { return RED_RR + (it - 1) % 2; }
 void launch_poisson_pipeline_moments(const Batch& b, const double* phi, const int* colinfo, PoissonWs& P,
@@ -237,19 +241,21 @@ void launch_poisson_rhs_full(const Batch& b, const double* phi, double* W, const
                              PoissonWs& P, hipStream_t s);
 void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int warm, hipStream_t s);
 void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s);
-// Pieces of a CG iteration with another preconditioner: q = K p with p.q into
-// slot RED_PQ + k % 2, and the update pass (alpha_k = red[RED_RZ + k % 3] / p.q).
-void launch_cg_apply_plain(const Batch& b, PoissonWs& P, const double* p, int k, hipStream_t s);
+// One iteration with another preconditioner: the operator pass on the
+// preconditioned residual z and the vector pass.  rz_rows: partial sums of r.z
+// left by launch_mg_cheb_step (0: r.z is in slot RED_RZ + k % 3).
+void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const double* z, float* rf, int rz_rows, int k,
+                         hipStream_t s);
+void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const float* z, float* rf, int rz_rows, int k,
+                         hipStream_t s);
+// After the last of `it` iterations: the solution update that is still open.
+void launch_cg_finish(const Batch& b, double* W, PoissonWs& P, int it, hipStream_t s);
 // rf (may be null): a float copy of the updated residual (Poisson schedule bit 6)
 // Batch CG convergence flags (DevMesh::cg_done, device int [ni]): set an
 // instance's flag once every column's r.r after iteration k is at most
 // rtol^2 times its largest column's b.b; clear all flags.
 void launch_cg_done(const Batch& b, const PoissonWs& P, int k, double rtol, hipStream_t s);
 void launch_zero_int(int* x, int n, hipStream_t s);
-// upd_x = 0: the x += alpha p of this iteration is left to the next direction
-// pass (mg_dir with x) or to cg_xfinal after the last iteration.
-void launch_cg_update(const Batch& b, double* W, PoissonWs& P, const double* p, int k, hipStream_t s,
-                      float* rf = nullptr, int upd_x = 1);
 void launch_to_float(const double* x, float* y, int64_t nd, hipStream_t s);
 // Multigrid-preconditioned CG on the finest level, in operator passes (the
 // Chebyshev coefficients are each instance's DevMesh::mgc; red: the CG
@@ -259,10 +265,11 @@ void launch_to_float(const double* x, float* y, int64_t nd, hipStream_t s);
 //    no third step reads it);
 //  - smoothing step k (0 .. degree - 1) from zin into zout (d updated in
 //    place); with rz_slot >= 0 (the last step after the coarse correction)
-//    it also accumulates r.zout into that slot and leaves d alone.
+//    it also accumulates r.zout into that slot and leaves d alone; returns the
+//    partial sums of r.zout left for launch_cg_iteration to fold (0: in the slot).
 void launch_mg_cheb0(const Batch& b, const double* r, double* z, double* d, double* red, int rz_slot, int ncol,
                      hipStream_t s);
-void launch_mg_cheb_step(const Batch& b, const double* zin, const double* r, double* zout, double* d, double* red,
+int launch_mg_cheb_step(const Batch& b, const double* zin, const double* r, double* zout, double* d, double* red,
                          int ncol, int k, int rz_slot, hipStream_t s);
 //  - the residual t = r - K z that the restriction to the next level reads
 //    (red_scratch: accumulators the pass may touch, not the CG's).
@@ -271,7 +278,7 @@ void launch_mg_resid(const Batch& b, const double* z, const double* r, double* t
 // Poisson schedule bit 6: the finest multigrid level's passes on float arrays
 void launch_mg_cheb0_f(const Batch& b, const float* r, float* z, float* d, double* red, int rz_slot, int ncol,
                        hipStream_t s);
-void launch_mg_cheb_step_f(const Batch& b, const float* zin, const float* r, float* zout, float* d, double* red,
+int launch_mg_cheb_step_f(const Batch& b, const float* zin, const float* r, float* zout, float* d, double* red,
                            int ncol, int k, int rz_slot, hipStream_t s);
 void launch_mg_resid_f(const Batch& b, const float* z, const float* r, float* t, int ncol, double* red_scratch,
                        hipStream_t s);

@@ -27,6 +27,7 @@
 
 #include "devutil.hpp"
 #include "kernels.hpp"
+#include "mg.hpp"
 
 namespace mh {
 
@@ -318,8 +319,7 @@ __global__ void __launch_bounds__(NT) k_mass_direct(const DevMesh* __restrict__ 
   }
 }
 
-static void launch_spmv_poisson(const Batch& b, const double* x, const double* pprev, double* pout, int ncol,
-                                double* q, const PoissonWs& P, int k, hipStream_t s);
+static void launch_spmv_plain(const Batch& b, const double* x, int ncol, double* q, double* red, hipStream_t s);
 
 template <int P, int L>
 static void launch_stencil_orb_t(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
@@ -374,13 +374,11 @@ void launch_stencil_orb(const Batch& b, const double* u, const double* Ef, int d
   const bool vel = diag_mode == 4 || (b.mx.gauge == 1 && (diag_mode == 1 || diag_mode == 2));
   const bool asm_k = (b.mx.sched_orb & 4) && kq && kred && !vel && !(b.mx.ecs && diag_mode <= 2);
   if (asm_k && diag_mode != 3) {
-    PoissonWs Pk;
-    Pk.red = kred;
     // at 2n <= 16 columns the stiffness pass runs best on at most 8192
     // workgroups, whatever cap the Poisson schedule of the pair columns takes
     Batch bk = b;
     bk.mx.grid_poi = std::min(b.mx.grid_poi, 8192);
-    launch_spmv_poisson(bk, u, u, kq, 2 * b.mx.n, kq, Pk, -1, s);
+    launch_spmv_plain(bk, u, 2 * b.mx.n, kq, kred, s);
   }
   const double* q = asm_k ? kq : nullptr;
   switch (b.mx.P) {
@@ -418,24 +416,30 @@ void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma
 // NT / L lane groups splitting the entries and an LDS reduction; the other
 // workgroups sweep the remaining rows.
 // --------------------------------------------------------------------------
-// Operator pass modes: plain q = K x (SP_PLAIN); the CG direction formed on
-// the fly (SP_CG); and the two Chebyshev smoothing passes of the multigrid
+// Operator pass modes: plain q = K x (SP_PLAIN); the CG's operator pass on the
+// preconditioned residual (SP_CG: z given, SP_CGJ: z = D^-1 r formed on the
+// fly); and the two Chebyshev smoothing passes of the multigrid
 // cycle on the finest level, which replace q by the smoother's update:
 // SP_CHEB0 runs the first two steps from z = 0 (its operand s0 D^-1 r is
 // formed on the fly), SP_CHEB runs one step on a given z into another array.
 // SP_CHEB_RZ is the second SP_CHEB step with r.z accumulated for the
 // multigrid-preconditioned CG.  SP_RES writes the residual r - K z that the
 // restriction to the next multigrid level reads.
-enum { SP_PLAIN = 0, SP_CG = 1, SP_CHEB0 = 2, SP_CHEB = 3, SP_CHEB_RZ = 4, SP_RES = 5 };
+enum { SP_PLAIN = 0, SP_CG = 1, SP_CHEB0 = 2, SP_CHEB = 3, SP_CHEB_RZ = 4, SP_RES = 5, SP_CGJ = 6 };
 
-// Value of the operand at row j, columns c0 .. c0+V: x itself; (SP_CG) the CG
-// direction p_j = D^-1_j r_j + beta p_prev,j formed on the fly (x = r then);
-// (SP_CHEB0) beta D^-1_j x_j (x = r, beta = s0).
+// Arrays of a pass beside its operand: w = K z of the CG's pass, double
+// whatever z is; full: the operand of SP_PLAIN or SP_RES is over full rows.
+struct PassExtra {
+  double* w;
+  int full;
+};
+
+// Value of the operand at row j, columns c0 .. c0+V: x itself; (SP_CGJ) D^-1_j
+// x_j; (SP_CHEB0) beta D^-1_j x_j (x = r, beta = s0).
 // T: storage type of the operand arrays (double; float for the finest-level
 // multigrid arrays of Poisson schedule bit 6).  Arithmetic is in double.
 template <int V, int MODE, class T>
 __device__ __forceinline__ void operand_row(const __attribute__((address_space(1))) T* xg,
-                                            const __attribute__((address_space(1))) T* pg,
                                             const __attribute__((address_space(1))) double* dinv, const double* beta,
                                             int64_t j, int ld, int c0, double* out) {
   load_vals<V>(xg + j * ld + c0, out);  // 16-byte loads (ncol and c0 multiples of V)
@@ -444,12 +448,10 @@ __device__ __forceinline__ void operand_row(const __attribute__((address_space(1
 #pragma unroll
     for (int v = 0; v < V; ++v) out[v] = beta[v] * dj * out[v];
   }
-  if constexpr (MODE == SP_CG) {
+  if constexpr (MODE == SP_CGJ) {
     const double dj = dinv[j];
-    double pv[V];
-    load_vals<V>(pg + j * ld + c0, pv);
 #pragma unroll
-    for (int v = 0; v < V; ++v) out[v] = dj * out[v] + (beta[v] != 0.0 ? beta[v] * pv[v] : 0.0);
+    for (int v = 0; v < V; ++v) out[v] = dj * out[v];
   }
 }
 
@@ -458,14 +460,12 @@ __device__ __forceinline__ void operand_row(const __attribute__((address_space(1
 // the index is clamped to the row's last entry (every row holds its diagonal)
 // and the coefficient zeroed, so the loads need no branch.
 template <int V, int MODE, class T>
-__device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restrict__ x,
-                                              const T* __restrict__ pprev, const double* beta, int ld, int c0,
-                                              int beg, int end, int stride, double* y) {
+__device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restrict__ x, const double* beta, int ld,
+                                              int c0, int beg, int end, int stride, double* y) {
   const auto* kcol = gbl(d.kt_col);
   const auto* kval = gbl(d.kt_val);
-  const auto* kvalf = gbl(d.kt_valf);   // the float passes read the float copy
+  const auto* kvalf = gbl(d.kt_valf);   // the preconditioner's float passes read the float copy, the CG's own pass the doubles
   const auto* xg = gbl(x);
-  const auto* pg = gbl(pprev);
   const auto* dinv = gbl(d.kdiag_inv);
   for (int t = beg; t < end; t += 4 * stride) {
     double av[4];
@@ -476,10 +476,10 @@ __device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restr
       const int tc = tt < end ? tt : end - 1;
       const int64_t j = kcol[tc];
       double a;
-      if constexpr (std::is_same<T, float>::value) a = kvalf[tc];
+      if constexpr (std::is_same<T, float>::value && MODE != SP_CG) a = kvalf[tc];
       else a = kval[tc];
       av[u] = tt < end ? a : 0.0;
-      operand_row<V, MODE, T>(xg, pg, dinv, beta, j, ld, c0, xv[u]);
+      operand_row<V, MODE, T>(xg, dinv, beta, j, ld, c0, xv[u]);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -488,8 +488,8 @@ __device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restr
   }
 }
 
-// Row i done, y = (K operand)_i.  SP_PLAIN / SP_CG: q_i = y, (SP_CG) p_i =
-// the operand of row i, and the p.q partial.
+// Row i done, y = (K operand)_i.  SP_PLAIN: q_i = y.  SP_CG, SP_CGJ: w_i = y
+// and the z.w partial.
 // Chebyshev passes (x: the operand's source, pprev = r, pout = z out, q = d,
 // cf = the instance's coefficients s0, c1, c2; step k of SP_CHEB, step 1 for
 // SP_CHEB_RZ):
@@ -505,21 +505,26 @@ template <int V, int MODE, class T>
 __device__ __forceinline__ void spmv_store(const DevMesh& d, T* __restrict__ q, T* __restrict__ pout,
                                            const T* __restrict__ x, const T* __restrict__ pprev,
                                            const double* beta, int64_t i, int ld, int c0, const double* y,
-                                           double* pq, const double* cf, int k) {
-  if constexpr (MODE == SP_RES) {
+                                           double* pq, const double* cf, int k, const PassExtra& ex) {
+  const auto* dinv = gbl(d.kdiag_inv);
+  if constexpr (MODE == SP_PLAIN) {
+    T* qo = q + i * ld + c0;
+#pragma unroll
+    for (int v = 0; v < V; ++v) qo[v] = (T)y[v];
+  } else if constexpr (MODE == SP_RES) {
     double rv[V];
-    operand_row<V, SP_PLAIN, T>(gbl(pprev), gbl(pprev), gbl(d.kdiag_inv), beta, i, ld, c0, rv);
+    operand_row<V, SP_PLAIN, T>(gbl(pprev), dinv, beta, i, ld, c0, rv);
     T* qo = q + i * ld + c0;
 #pragma unroll
     for (int v = 0; v < V; ++v) qo[v] = (T)(rv[v] - y[v]);
   } else if constexpr (MODE == SP_CHEB0 || MODE == SP_CHEB || MODE == SP_CHEB_RZ) {
     const int step = MODE == SP_CHEB_RZ ? k >> 4 : k;
-    const double di = gbl(d.kdiag_inv)[i];
+    const double di = dinv[i];
     double rv[V], xv[V], dv[V];
-    operand_row<V, SP_PLAIN, T>(gbl(pprev), gbl(pprev), gbl(d.kdiag_inv), beta, i, ld, c0, rv);
+    operand_row<V, SP_PLAIN, T>(gbl(pprev), dinv, beta, i, ld, c0, rv);
     if constexpr (MODE != SP_CHEB0) {
-      operand_row<V, SP_PLAIN, T>(gbl(x), gbl(x), gbl(d.kdiag_inv), beta, i, ld, c0, xv);
-      if (step > 0) operand_row<V, SP_PLAIN, T>(gbl((const T*)q), gbl(x), gbl(d.kdiag_inv), beta, i, ld, c0, dv);
+      operand_row<V, SP_PLAIN, T>(gbl(x), dinv, beta, i, ld, c0, xv);
+      if (step > 0) operand_row<V, SP_PLAIN, T>(gbl((const T*)q), dinv, beta, i, ld, c0, dv);
     }
     T* qo = q + i * ld + c0;
     T* po = pout + i * ld + c0;
@@ -540,33 +545,69 @@ __device__ __forceinline__ void spmv_store(const DevMesh& d, T* __restrict__ q, 
       }
     }
   } else {
-    double pi[V];
-    operand_row<V, MODE, T>(gbl(x), gbl(pprev), gbl(d.kdiag_inv), beta, i, ld, c0, pi);
-    T* qo = q + i * ld + c0;
-    T* po = pout + i * ld + c0;
+    double zi[V];
+    operand_row<V, MODE, T>(gbl(x), dinv, beta, i, ld, c0, zi);
+    auto* wo = gblw(ex.w) + i * ld + c0;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      qo[v] = (T)y[v];
-      if constexpr (MODE == SP_CG) po[v] = (T)pi[v];
-      pq[v] += y[v] * pi[v];
+      wo[v] = y[v];
+      pq[v] += zi[v] * y[v];
     }
   }
 }
+
+// The sums over g < groups of lds[g ncol + c] into lds[c], c < ncol (a tree;
+// every thread of the workgroup calls it, threadIdx.x = g ncol + c).
+__device__ __forceinline__ void col_tree(double* lds, int groups, int ncol) {
+  int h = 1;
+  while (2 * h < groups) h *= 2;
+  const int g = (int)threadIdx.x / ncol;
+  for (; h > 0; h >>= 1) {
+    __syncthreads();
+    if (g < h && g + h < groups) lds[threadIdx.x] += lds[threadIdx.x + h * ncol];
+  }
+  __syncthreads();
+}
+
+// lds[c] = sum over the rows w of part[w][c], c < nc, by one workgroup.
+__device__ __forceinline__ void fold_cols(const double* __restrict__ part, int rows, int nc, double* lds) {
+  const int per = NT / nc, g = (int)threadIdx.x / nc, c = (int)threadIdx.x - g * nc;
+  const auto* pg = gbl(part);
+  double s = 0.0;
+  if (g < per)
+    for (int w = g; w < rows; w += 8 * per) {
+      double t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int ww = w + u * per;
+        const double v = pg[(ww < rows ? ww : w) * nc + c];
+        t[u] = ww < rows ? v : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += t[u];
+    }
+  lds[threadIdx.x] = s;
+  col_tree(lds, per, nc);
+}
+// Largest number of partial sums that the launch that needs them folds itself:
+// each of its workgroups reads them (64 KB from L2), which costs less than a
+// launch; more are folded by k_fold_parts.
+constexpr int64_t FOLD_MAX = 8192;
 
 // Columns [col0, col0 + nc) of arrays with ld columns per row, col0 = blockIdx.z * nc
 // (nc = ld without column blocking).  SELL: the short rows come from the
 // sliced-ELL copy, a wave taking 64 / L slots of one slice (one width for all
 // its rows), so each round of entries is read as consecutive words.
 // MODE: SP_*; red: the CG accumulators ([ni][RED_SLOTS][ld]); k: the CG
-// iteration (SP_CG; see launch_spmv_poisson for SP_PLAIN), the
-// smoothing step (SP_CHEB) or the r.z slot (SP_CHEB0 clears it, SP_CHEB_RZ
+// iteration (SP_CG, SP_CGJ), the smoothing step (SP_CHEB) or the r.z slot (SP_CHEB0 clears it, SP_CHEB_RZ
 // accumulates into slot k & 15 at step k >> 4).
 template <int L, int V, int MODE, bool SELL, class T>
 __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__ dm, const T* __restrict__ x,
                                                      const T* __restrict__ pprev, T* __restrict__ pout,
                                                      int ld, int nc, T* __restrict__ q, int nlb,
-                                                     double* __restrict__ red, int k, double* __restrict__ part) {
-  constexpr bool FUSE = MODE == SP_CG;
+                                                     double* __restrict__ red, int k, double* __restrict__ part,
+                                                     PassExtra ex) {
+  constexpr bool CG = MODE == SP_CG || MODE == SP_CGJ;
   INSTANCE;
   if (d.cg_done && *d.cg_done) return;  // converged instance of a batch CG (batches take no partials)
   __shared__ double lds[NT * V];
@@ -578,10 +619,11 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
   // one workgroup per column block clears the slots below (workgroup 0 of the
   // block's z slice; with bit 7 workgroups 0 .. nb_col - 1, one per block)
   const bool first_wg = aff ? (int)blockIdx.x < nb_col : blockIdx.x == 0;
-  x += d.oE * ld + col0;
+  x += ((MODE == SP_PLAIN || MODE == SP_RES) && ex.full ? d.oF : d.oE) * ld + col0;
   q += d.oE * ld + col0;
   pprev += d.oE * ld + col0;
   pout += d.oE * ld + col0;
+  if (CG) ex.w += d.oE * ld + col0;
   double cf[2 * MG_MAX_DEG - 1];
 #pragma unroll
   for (int j = 0; j < 2 * MG_MAX_DEG - 1; ++j) cf[j] = d.mgc[j];
@@ -589,16 +631,9 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
   const int lane = (int)(threadIdx.x & (L - 1));
   const int c0 = lane * V;
   const bool col_ok = c0 < nc;
-  // beta_k = rz_k / rz_{k-1} per column (0 at the first iteration); s0 for SP_CHEB0
-  double beta[V];
+  double beta[V];   // s0 for SP_CHEB0
 #pragma unroll
-  for (int v = 0; v < V; ++v) {
-    beta[v] = MODE == SP_CHEB0 ? cf[0] : 0.0;
-    if (FUSE && k > 0 && c0 + v < nc) {
-      const double rzk = red[(RED_RZ + k % 3) * ld + c0 + v], rzp = red[(RED_RZ + (k + 2) % 3) * ld + c0 + v];
-      beta[v] = rzp != 0.0 ? rzk / rzp : 0.0;
-    }
-  }
+  for (int v = 0; v < V; ++v) beta[v] = MODE == SP_CHEB0 ? cf[0] : 0.0;
   double pq[V];
 #pragma unroll
   for (int v = 0; v < V; ++v) pq[v] = 0.0;
@@ -621,12 +656,12 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
       double y[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) y[v] = 0.0;
-      if (col_ok) spmv_row_part<V, MODE, T>(d, x, pprev, beta, ld, c0, beg + seg, end, SEG, y);
+      if (col_ok) spmv_row_part<V, MODE, T>(d, x, beta, ld, c0, beg + seg, end, SEG, y);
 #pragma unroll
       for (int off = L; off < 64; off <<= 1)
 #pragma unroll
         for (int v = 0; v < V; ++v) y[v] += __shfl_xor(y[v], off, 64);
-      if (seg == 0 && col_ok) spmv_store<V, MODE, T>(d, q, pout, x, pprev, beta, i, ld, c0, y, pq, cf, k);
+      if (seg == 0 && col_ok) spmv_store<V, MODE, T>(d, q, pout, x, pprev, beta, i, ld, c0, y, pq, cf, k, ex);
     }
   } else if constexpr (SELL) {
     constexpr int R = 64 / L;  // slots per wave
@@ -638,9 +673,8 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
     const auto* srow = gbl(d.sell_row);
     const auto* scol = gbl(d.sell_col);
     const auto* sval = gbl(d.sell_val);
-    const auto* svalf = gbl(d.sell_valf);   // the float passes read the float copy
+    const auto* svalf = gbl(d.sell_valf);   // as in spmv_row_part
     const auto* xg = gbl(x);
-    const auto* pg = gbl(pprev);
     const auto* dinv = gbl(d.kdiag_inv);
     for (int64_t u = sw.start + wave; u < sw.end; u += sw.step) {
       const int64_t sl = u / L;
@@ -657,16 +691,16 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
           const int e = base + (t + h) * SELL_H + slot;
-          if constexpr (std::is_same<T, float>::value) av[h] = svalf[e];
+          if constexpr (std::is_same<T, float>::value && MODE != SP_CG) av[h] = svalf[e];
           else av[h] = sval[e];
-          operand_row<V, MODE, T>(xg, pg, dinv, beta, (int64_t)scol[e], ld, c0, xv[h]);
+          operand_row<V, MODE, T>(xg, dinv, beta, (int64_t)scol[e], ld, c0, xv[h]);
         }
 #pragma unroll
         for (int h = 0; h < 4; ++h)
 #pragma unroll
           for (int v = 0; v < V; ++v) y[v] += av[h] * xv[h][v];
       }
-      spmv_store<V, MODE, T>(d, q, pout, x, pprev, beta, i, ld, c0, y, pq, cf, k);
+      spmv_store<V, MODE, T>(d, q, pout, x, pprev, beta, i, ld, c0, y, pq, cf, k, ex);
     }
   } else {
     const XcdSweep sw = aff ? xcd_sweep_cols(d.N, NT / L, nb_col, (int)blockIdx.x - nlb, (int)gridDim.x - nlb)
@@ -678,15 +712,15 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
       double y[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) y[v] = 0.0;
-      spmv_row_part<V, MODE, T>(d, x, pprev, beta, ld, c0, beg, end, 1, y);
-      spmv_store<V, MODE, T>(d, q, pout, x, pprev, beta, i, ld, c0, y, pq, cf, k);
+      spmv_row_part<V, MODE, T>(d, x, beta, ld, c0, beg, end, 1, y);
+      spmv_store<V, MODE, T>(d, q, pout, x, pprev, beta, i, ld, c0, y, pq, cf, k, ex);
     }
   }
-  if constexpr (MODE == SP_CHEB0 || MODE == SP_CHEB || MODE == SP_RES) {
+  if constexpr (MODE == SP_PLAIN || MODE == SP_CHEB0 || MODE == SP_CHEB || MODE == SP_RES) {
     if (MODE == SP_CHEB0 && first_wg && threadIdx.x < (unsigned)nc) red[(k & 255) * ld + threadIdx.x] = 0.0;
     return;
   }
-  // p.q (r.z for SP_CHEB_RZ) of the workgroup: shuffles over the rows of each wave, then 4 waves
+  // z.w (r.z for SP_CHEB_RZ) of the workgroup: shuffles over the rows of each wave, then 4 waves
 #pragma unroll
   for (int off = L; off < 64; off <<= 1)
 #pragma unroll
@@ -700,39 +734,33 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
 #pragma unroll
     for (int w = 0; w < NT / 64; ++w) sum += lds[w * (L * V) + threadIdx.x];
     if (part) {
-      part[(int64_t)blockIdx.x * nc + threadIdx.x] = sum;  // folded by k_fold_parts
-    } else if constexpr (MODE == SP_CHEB_RZ) {
-      atomicAdd(red + (k & 15) * ld + threadIdx.x, sum);  // r.z of this instance and column
+      part[(int64_t)blockIdx.x * nc + threadIdx.x] = sum;  // folded by the next launch or by k_fold_parts
     } else {
-      // iteration of this pass: k (fused), -2 - k (plain pass of a CG iteration), 0 (k = -1: start)
-      const int kk = k >= 0 ? k : (k <= -2 ? -2 - k : 0);
-      atomicAdd(red + (RED_PQ + kk % 2) * ld + threadIdx.x, sum);  // p.q of this instance and column
+      // r.z or z.w of this instance and column
+      atomicAdd(red + (MODE == SP_CHEB_RZ ? (k & 15) : RED_PQ + k % 2) * ld + threadIdx.x, sum);
     }
-    if (FUSE && first_wg) {  // clear what the update pass of this iteration accumulates into
+    if (CG && first_wg) {  // clear what the update pass of this iteration accumulates into
       red[(RED_RZ + (k + 1) % 3) * ld + threadIdx.x] = 0.0;
       red[(RED_RR + k % 2) * ld + threadIdx.x] = 0.0;
     }
   }
 }
 
-// dst[c] += sum over the rows workgroups w of part[w][c] (one instance; nc
-// divides NT): the per-workgroup sums of an operator pass, added with a few
-// hundred atomics where the pass itself would issue one per workgroup and
-// column, all on the same nc addresses.
+// dst[c] += sum over the rows workgroups w of part[w][c] (one instance): the
+// per-workgroup sums of an operator pass, added with a few hundred atomics
+// where the pass itself would issue one per workgroup and column, all on the
+// same nc addresses.
 __global__ void __launch_bounds__(NT) k_fold_parts(const double* __restrict__ part, int rows, int nc,
                                                    double* __restrict__ dst) {
   __shared__ double lds[NT];
   const int per = NT / nc;
-  const int c = (int)threadIdx.x % nc, g = (int)threadIdx.x / nc;
+  const int g = (int)threadIdx.x / nc, c = (int)threadIdx.x - g * nc;
   double s = 0.0;
-  for (int64_t w = (int64_t)blockIdx.x * per + g; w < rows; w += (int64_t)gridDim.x * per) s += part[w * nc + c];
+  if (g < per)
+    for (int64_t w = (int64_t)blockIdx.x * per + g; w < rows; w += (int64_t)gridDim.x * per) s += part[w * nc + c];
   lds[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < (unsigned)nc) {
-    double t = 0.0;
-    for (int j = 0; j < per; ++j) t += lds[j * nc + threadIdx.x];
-    atomicAdd(dst + threadIdx.x, t);
-  }
+  col_tree(lds, per, nc);
+  if (threadIdx.x < (unsigned)nc) atomicAdd(dst + threadIdx.x, lds[threadIdx.x]);
 }
 
 // Workgroups reserved for the long rows when schedule bit 2 or 5 is set:
@@ -748,194 +776,220 @@ static int long_row_blocks(const Batch& b) {
 // kernel and before its fold, so the event pair spans that kernel alone.
 static thread_local hipEvent_t t_pass_end = nullptr;
 
+// Returns the number of partial sums per column left for the next launch to
+// fold (0: the sums are in red).
 template <int L, int V, int MODE, class T>
-static void launch_spmv_m(const Batch& b, const T* x, const T* pprev, T* pout, int ld, int nc, T* q, double* red,
-                          int k, hipStream_t s) {
+static int launch_spmv_m(const Batch& b, const T* x, const T* pprev, T* pout, int ld, int nc, T* q, double* red,
+                         int k, const PassExtra& ex, hipStream_t s) {
   // schedule bit 7 with column blocks: the blocks ride along x, bound to XCDs
   // (the kernel takes the column block from the XCD), each block the whole sweep
   const int nbc = ld / nc;
-  if ((b.mx.sched_poi & 128) && nbc > 1 && N_XCD % nbc == 0) {
-    const int nlb = long_row_blocks(b) * nbc;
-    const int sweep = (b.mx.sched_poi & 32) ? xcd_grid(b.mx.n_slices * L, NT / 64, b.mx.grid_poi)
-                                            : xcd_grid(b.mx.N, NT / L, b.mx.grid_poi);
-    const dim3 g(nlb + sweep * nbc, b.ni, 1);
-    if (b.mx.sched_poi & 32)
+  const bool sell = b.mx.sched_poi & 32;
+  auto go = [&](const dim3& g, int nlb, double* part) {
+    if (sell)
       hipLaunchKernelGGL((k_spmv_poisson<L, V, MODE, true, T>), g, dim3(NT), 0, s, b.dm, x, pprev, pout, ld, nc, q,
-                         nlb, red, k, (double*)nullptr);
+                         nlb, red, k, part, ex);
     else
       hipLaunchKernelGGL((k_spmv_poisson<L, V, MODE, false, T>), g, dim3(NT), 0, s, b.dm, x, pprev, pout, ld, nc, q,
-                         nlb, red, k, (double*)nullptr);
+                         nlb, red, k, part, ex);
     if (t_pass_end) (void)hipEventRecord(t_pass_end, s);
-    return;
+  };
+  const int sweep = sell ? xcd_grid(b.mx.n_slices * L, NT / 64, b.mx.grid_poi) : xcd_grid(b.mx.N, NT / L, b.mx.grid_poi);
+  if ((b.mx.sched_poi & 128) && nbc > 1 && N_XCD % nbc == 0) {
+    const int nlb = long_row_blocks(b) * nbc;
+    go(dim3(nlb + sweep * nbc, b.ni, 1), nlb, nullptr);
+    return 0;
   }
   const int nlb = long_row_blocks(b);
-  const bool sell = b.mx.sched_poi & 32;
-  const int gx = nlb + (sell ? xcd_grid(b.mx.n_slices * L, NT / 64, b.mx.grid_poi) : xcd_grid(b.mx.N, NT / L, b.mx.grid_poi));
-  // one instance: per-workgroup sums to the partial buffer, then one fold
+  const int gx = nlb + sweep;
+  // one instance: per-workgroup sums to a partial buffer, folded by the launch
+  // that needs them or, where they are many, by one of their own
   double* part = nullptr;
-  if constexpr (MODE == SP_PLAIN || MODE == SP_CG || MODE == SP_CHEB_RZ)
-    if (b.spart && b.ni == 1 && nc == ld && NT % nc == 0 && (int64_t)gx * nc <= b.spart_cap) part = b.spart;
-  const dim3 g(gx, b.ni, ld / nc);
-  if (sell)
-    hipLaunchKernelGGL((k_spmv_poisson<L, V, MODE, true, T>), g, dim3(NT), 0, s, b.dm, x, pprev, pout, ld, nc, q,
-                       nlb, red, k, part);
-  else
-    hipLaunchKernelGGL((k_spmv_poisson<L, V, MODE, false, T>), g, dim3(NT), 0, s, b.dm, x, pprev, pout, ld, nc, q,
-                       nlb, red, k, part);
-  if (t_pass_end) (void)hipEventRecord(t_pass_end, s);
+  bool later = false;
+  if constexpr (MODE == SP_CG || MODE == SP_CGJ || MODE == SP_CHEB_RZ)
+    if (b.spart && b.ni == 1 && nc == ld && (int64_t)gx * nc <= b.spart_cap) {
+      later = (int64_t)gx * nc <= FOLD_MAX;
+      part = later && MODE == SP_CHEB_RZ ? b.spart + b.spart_cap : b.spart;   // both are folded by the update pass
+    }
+  go(dim3(gx, b.ni, nbc), nlb, part);
+  if (later) return gx;
   if (part) {
-    const int kk = k >= 0 ? k : (k <= -2 ? -2 - k : 0);
-    const int slot = MODE == SP_CHEB_RZ ? (k & 15) : RED_PQ + kk % 2;
+    const int slot = MODE == SP_CHEB_RZ ? (k & 15) : RED_PQ + k % 2;
     const int fb = (int)std::max<int64_t>(1, std::min<int64_t>(256, (int64_t)gx / (NT / nc * 16)));
     hipLaunchKernelGGL(k_fold_parts, dim3(fb), dim3(NT), 0, s, part, gx, nc, red + (int64_t)slot * ld);
   }
+  return 0;
 }
 template <int L, int V, class T>
-static void launch_spmv_t(const Batch& b, const T* x, const T* pprev, T* pout, int ld, int nc, T* q, double* red,
-                          int mode, int k, hipStream_t s) {
+static int launch_spmv_t(const Batch& b, const T* x, const T* pprev, T* pout, int ld, int nc, T* q, double* red,
+                         int mode, int k, const PassExtra& ex, hipStream_t s) {
   switch (mode) {
-    case SP_PLAIN: return launch_spmv_m<L, V, SP_PLAIN, T>(b, x, pprev, pout, ld, nc, q, red, k, s);
-    case SP_CG:  // the CG direction: double arrays only
-      if constexpr (sizeof(T) == sizeof(double)) return launch_spmv_m<L, V, SP_CG, T>(b, x, pprev, pout, ld, nc, q, red, k, s);
-      return;
-    case SP_CHEB0: return launch_spmv_m<L, V, SP_CHEB0, T>(b, x, pprev, pout, ld, nc, q, red, k, s);
-    case SP_CHEB: return launch_spmv_m<L, V, SP_CHEB, T>(b, x, pprev, pout, ld, nc, q, red, k, s);
-    case SP_RES: return launch_spmv_m<L, V, SP_RES, T>(b, x, pprev, pout, ld, nc, q, red, k, s);
-    default: return launch_spmv_m<L, V, SP_CHEB_RZ, T>(b, x, pprev, pout, ld, nc, q, red, k, s);
+    case SP_PLAIN:
+      if constexpr (sizeof(T) == sizeof(double)) return launch_spmv_m<L, V, SP_PLAIN, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
+      return 0;
+    case SP_CGJ:  // the residual itself: double only
+      if constexpr (sizeof(T) == sizeof(double)) return launch_spmv_m<L, V, SP_CGJ, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
+      return 0;
+    case SP_CG: return launch_spmv_m<L, V, SP_CG, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
+    case SP_CHEB0: return launch_spmv_m<L, V, SP_CHEB0, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
+    case SP_CHEB: return launch_spmv_m<L, V, SP_CHEB, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
+    case SP_RES: return launch_spmv_m<L, V, SP_RES, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
+    default: return launch_spmv_m<L, V, SP_CHEB_RZ, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
   }
 }
 
-// q = K x (k < 0: k = -1 at the CG start, -2 - j for the plain pass of iteration j),
-// or for CG iteration k >= 0: p_k = D^-1 r + beta_k p_{k-1} formed on the fly from
-// x = r and pprev, written to pout, and q = K p_k.
+// One operator pass in the given mode over all columns.
 // Schedule bit 1 (column blocking): with 32 or more columns in multiples of 16,
 // grid.z runs over blocks of 16 columns, so a row slice is 128 B and the band of
 // neighbour rows a sweep touches stays in L2 (the matrix is read once per block).
 template <class T>
-static void launch_spmv_mode(const Batch& b, const T* x, const T* pprev, T* pout, int ncol, T* q, double* red,
-                             int mode, int k, hipStream_t s);
-static void launch_spmv_poisson(const Batch& b, const double* x, const double* pprev, double* pout, int ncol,
-                                double* q, const PoissonWs& P, int k, hipStream_t s) {
-  launch_spmv_mode(b, x, pprev, pout, ncol, q, P.red, k >= 0 ? SP_CG : SP_PLAIN, k, s);
-}
-template <class T>
-static void launch_spmv_mode(const Batch& b, const T* x, const T* pprev, T* pout, int ncol, T* q, double* red,
-                             int mode, int k, hipStream_t s) {
+static int launch_spmv_mode(const Batch& b, const T* x, const T* pprev, T* pout, int ncol, T* q, double* red,
+                            int mode, int k, hipStream_t s, const PassExtra& ex) {
   if ((b.mx.sched_poi & 2) && ncol >= 32 && ncol % 16 == 0)
-    return launch_spmv_t<4, 4, T>(b, x, pprev, pout, ncol, 16, q, red, mode, k, s);
+    return launch_spmv_t<4, 4, T>(b, x, pprev, pout, ncol, 16, q, red, mode, k, ex, s);
   if (ncol % 4 == 0 && ncol > 4) {  // 4 columns per lane (two 16-byte loads; one for float)
-    if (ncol <= 16) return launch_spmv_t<4, 4, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-    if (ncol <= 32) return launch_spmv_t<8, 4, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-    return launch_spmv_t<16, 4, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
+    if (ncol <= 16) return launch_spmv_t<4, 4, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+    if (ncol <= 32) return launch_spmv_t<8, 4, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+    return launch_spmv_t<16, 4, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
   }
   if (ncol % 2 == 0) {  // column pairs
-    if (ncol <= 4) return launch_spmv_t<2, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-    if (ncol <= 8) return launch_spmv_t<4, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-    if (ncol <= 16) return launch_spmv_t<8, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-    if (ncol <= 32) return launch_spmv_t<16, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-    return launch_spmv_t<32, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
+    if (ncol <= 4) return launch_spmv_t<2, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+    if (ncol <= 8) return launch_spmv_t<4, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+    if (ncol <= 16) return launch_spmv_t<8, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+    if (ncol <= 32) return launch_spmv_t<16, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+    return launch_spmv_t<32, 2, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
   }
-  if (ncol <= 1) return launch_spmv_t<1, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-  if (ncol <= 2) return launch_spmv_t<2, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-  if (ncol <= 4) return launch_spmv_t<4, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-  if (ncol <= 8) return launch_spmv_t<8, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-  if (ncol <= 16) return launch_spmv_t<16, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-  if (ncol <= 32) return launch_spmv_t<32, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
-  return launch_spmv_t<64, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, s);
+  if (ncol <= 1) return launch_spmv_t<1, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+  if (ncol <= 2) return launch_spmv_t<2, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+  if (ncol <= 4) return launch_spmv_t<4, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+  if (ncol <= 8) return launch_spmv_t<8, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+  if (ncol <= 16) return launch_spmv_t<16, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+  if (ncol <= 32) return launch_spmv_t<32, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+  return launch_spmv_t<64, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
+}
+static PassExtra no_extra(int full = 0) { return PassExtra{nullptr, full}; }
+static void launch_spmv_plain(const Batch& b, const double* x, int ncol, double* q, double* red, hipStream_t s) {
+  launch_spmv_mode(b, x, x, q, ncol, q, red, SP_PLAIN, -1, s, no_extra());
 }
 
 // --------------------------------------------------------------------------
 // Jacobi-preconditioned CG, all columns of all instances at once with their
 // own alpha and beta.  Scalars sc[i][slot][c] (SC_* in kernels.hpp).
 // --------------------------------------------------------------------------
-// One CG iteration is two launches.  The operator pass forms the direction
-// p_k = D^-1 r_k + beta_k p_{k-1} on the fly for every row it reads (beta_k =
-// rz_k / rz_{k-1} from the accumulators), writes p_k to the other direction
-// buffer, and accumulates p.q with FP64 atomics per instance and column.  The
-// update pass takes alpha_k = rz_k / p.q, updates x and r, and accumulates
-// rz_{k+1} and r.r.  The accumulators rotate (rz over three slots, p.q and
-// r.r over two), and each pass clears only slots that no workgroup of the
-// same launch reads, so no launch overwrites a value its own workgroups use.
+// One CG iteration is two launches beside its preconditioner: the operator
+// pass, w = K z with z.w, and the vector pass,
+//   beta = r.z / (r.z)_old, eta = z.w - beta^2 eta_old, alpha = r.z / eta,
+//   p = z + beta p, q = w + beta q, x += alpha p, r -= alpha q, r.r
+// (Chronopoulos and Gear 1989): q is K p by its recurrence and eta is p.q, as
+// the directions are K-orthogonal, so the operator pass takes z and needs no
+// scalar of the iteration.  It gathers z (float rows where the multigrid
+// level keeps floats) instead of p, in whatever row order it runs, while
+// every vector is swept once, in order.  eta is taken from z.w alone (a restart,
+// beta = 0) where the subtraction leaves less than a thousandth of z.w, so a
+// column at its rounding floor cannot take a step of arbitrary length.
+// x takes two iterations' terms at once, every second iteration (one instance;
+// the instances of a batch stop at different iterations).
+// Against a direction pass, an operator pass on p and an update pass with
+// their sums folded by launches of their own: H2O (1.5 M rows x 64 columns,
+// float z) 2.52 -> 2.30 ms per iteration, 16 H2 (1.16 M x 4) 284 -> 217 us, Q1 water
+// (0.2 M x 64) 255 -> 212 us, H2 (66,635 x 4) 39 -> 27 us.  With the vector
+// updates in the operator pass itself H2O takes 2.22 ms, but 16 H2 382 us: with
+// few columns the rows of a wave, sorted by length, lie apart.
+// The accumulators rotate (rz over three slots, z.w, eta and r.r over two), and
+// each pass clears only slots that no workgroup of the same launch reads, so
+// no launch overwrites a value its own workgroups use.
 
-// x += alpha p; r -= alpha q; accumulate (r.D^-1 r, r.r).  x over full rows.
-__global__ void __launch_bounds__(NT) k_cg_update2(const DevMesh* __restrict__ dm, double* __restrict__ x,
-                                                   double* __restrict__ r, const double* __restrict__ p,
-                                                   const double* __restrict__ q, int ncol, double* __restrict__ red,
-                                                   int k, float* __restrict__ rf, int upd_x) {
+// The vector pass.  JAC: z = D^-1 r, and r.D^-1 r of the new r is accumulated
+// for the next iteration.  xmode 0: x left for the next pass; 1: x += alpha p;
+// 2: also the previous iteration's term.  zw_rows, rz_rows > 0: z.w and r.z are
+// folded here from the partial sums of the passes that formed them.
+// A thread takes one column and U rows at a time, all their loads in flight
+// before the first store.
+template <class Z, bool JAC, int U>
+__global__ void __launch_bounds__(NT) k_cg_vectors(const DevMesh* __restrict__ dm, double* __restrict__ x,
+                                                   double* __restrict__ r, const Z* __restrict__ z,
+                                                   double* __restrict__ p, const double* __restrict__ w,
+                                                   double* __restrict__ q, int ncol, double* __restrict__ red, int k,
+                                                   float* __restrict__ rf, int xmode,
+                                                   const double* __restrict__ zw_part, int zw_rows,
+                                                   const double* __restrict__ rz_part, int rz_rows) {
   INSTANCE;
   if (d.cg_done && *d.cg_done) return;
   __shared__ double lds[2 * NT];
   x += d.oF * ncol;
   if (rf) rf += d.oE * ncol;
   r += d.oE * ncol;
+  if (!JAC) z += d.oE * ncol;
   p += d.oE * ncol;
+  w += d.oE * ncol;
   q += d.oE * ncol;
   red += (int64_t)blockIdx.y * RED_SLOTS * ncol;
   const int groups = NT / ncol;
   const int g = threadIdx.x / ncol, c = threadIdx.x - g * ncol;
   const bool act = g < groups;
   const auto* dinv = gbl(d.kdiag_inv);
+  if (zw_rows > 0) fold_cols(zw_part, zw_rows, ncol, lds);
+  if (rz_rows > 0) fold_cols(rz_part, rz_rows, ncol, lds + NT);
   double rz = 0.0, rr = 0.0;
   if (act) {
-    const double pq = red[(RED_PQ + k % 2) * ncol + c], rz0 = red[(RED_RZ + k % 3) * ncol + c];
-    const double al = (pq != 0.0 && rz0 != 0.0) ? rz0 / pq : 0.0;
-    for (int64_t kk = (int64_t)blockIdx.x * groups + g; kk < d.N; kk += (int64_t)gridDim.x * groups) {
-      const int64_t e = kk * ncol + c;
-      if (upd_x) x[e] += al * p[e];   // else deferred to the next direction pass
-      const double rn = r[e] - al * q[e];
-      r[e] = rn;
-      if (rf) rf[e] = (float)rn;  // the finest multigrid level's float copy (Poisson schedule bit 6)
-      rz += rn * rn * dinv[kk];
-      rr += rn * rn;
-    }
-  }
-  lds[threadIdx.x] = act ? rz : 0.0;
-  lds[NT + threadIdx.x] = act ? rr : 0.0;
-  __syncthreads();
-  if (threadIdx.x < (unsigned)ncol) {
-    double t = 0.0, u = 0.0;
-    for (int gg = 0; gg < groups; ++gg) {
-      t += lds[gg * ncol + threadIdx.x];
-      u += lds[NT + gg * ncol + threadIdx.x];
-    }
-    atomicAdd(red + (RED_RZ + (k + 1) % 3) * ncol + threadIdx.x, t);
-    atomicAdd(red + (RED_RR + k % 2) * ncol + threadIdx.x, u);
-    if (blockIdx.x == 0) red[(RED_PQ + (k + 1) % 2) * ncol + threadIdx.x] = 0.0;  // for the next operator pass
-  }
-}
-
-// Direction pass for schedules without bit 3: p_k = D^-1 r_k + beta_k p_{k-1}
-// into pcur; workgroup 0 clears the slots the update pass of iteration k
-// accumulates into (the operator pass does this when it forms p_k itself).
-__global__ void __launch_bounds__(NT) k_cg_dir(const DevMesh* __restrict__ dm, const double* __restrict__ r,
-                                               const double* __restrict__ pprev, double* __restrict__ pcur, int ncol,
-                                               double* __restrict__ red, int k) {
-  INSTANCE;
-  __shared__ double beta[64];
-  const int64_t total = d.N * ncol;
-  r += d.oE * ncol;
-  pprev += d.oE * ncol;
-  pcur += d.oE * ncol;
-  red += (int64_t)blockIdx.y * RED_SLOTS * ncol;
-  if (threadIdx.x < (unsigned)ncol) {
-    double bt = 0.0;
+    const double ga = rz_rows > 0 ? lds[NT + c] : red[(RED_RZ + k % 3) * ncol + c];
+    const double zw = zw_rows > 0 ? lds[c] : red[(RED_PQ + k % 2) * ncol + c];
+    double be = 0.0, eta = zw, alp = 0.0;
     if (k > 0) {
-      const double rzk = red[(RED_RZ + k % 3) * ncol + threadIdx.x], rzp = red[(RED_RZ + (k + 2) % 3) * ncol + threadIdx.x];
-      bt = rzp != 0.0 ? rzk / rzp : 0.0;
+      const double gp = red[(RED_RZ + (k + 2) % 3) * ncol + c], ep = red[(RED_ETA + (k + 1) % 2) * ncol + c];
+      be = gp != 0.0 ? ga / gp : 0.0;
+      alp = (ep != 0.0 && gp != 0.0) ? gp / ep : 0.0;
+      eta = zw - be * be * ep;
+      if (!(eta > 1e-3 * zw)) {
+        be = 0.0;
+        eta = zw;
+      }
     }
-    beta[threadIdx.x] = bt;
+    const double al = (eta != 0.0 && ga != 0.0) ? ga / eta : 0.0;
+    if (blockIdx.x == 0 && g == 0) {
+      if (rz_rows > 0) red[(RED_RZ + k % 3) * ncol + c] = ga;
+      red[(RED_ETA + k % 2) * ncol + c] = eta;
+      red[(RED_PQ + (k + 1) % 2) * ncol + c] = 0.0;  // for the next operator pass
+    }
+    const int64_t step = (int64_t)gridDim.x * groups;
+    for (int64_t kk = (int64_t)blockIdx.x * groups + g; kk < d.N; kk += U * step) {
+      double ro[U], wi[U], zi[U], po[U], qo[U], xo[U], di[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t row = kk + u * step < d.N ? kk + u * step : kk;   // past the end: the first row again, not stored
+        const int64_t e = row * ncol + c;
+        ro[u] = r[e];
+        wi[u] = w[e];
+        di[u] = JAC ? dinv[row] : 0.0;
+        zi[u] = JAC ? di[u] * ro[u] : (double)z[e];
+        po[u] = k > 0 ? p[e] : 0.0;
+        qo[u] = k > 0 ? q[e] : 0.0;
+        xo[u] = xmode ? x[e] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (u > 0 && kk + u * step >= d.N) break;
+        const int64_t e = (kk + u * step) * ncol + c;
+        const double pn = zi[u] + be * po[u], qn = wi[u] + be * qo[u];
+        p[e] = pn;
+        q[e] = qn;
+        if (xmode) x[e] = xo[u] + (xmode == 2 ? alp * po[u] + al * pn : al * pn);
+        const double rn = ro[u] - al * qn;
+        r[e] = rn;
+        if (rf) rf[e] = (float)rn;  // the finest multigrid level's float copy (Poisson schedule bit 6)
+        if (JAC) rz += rn * rn * di[u];
+        rr += rn * rn;
+      }
+    }
   }
   __syncthreads();
-  const auto* dinv = gbl(d.kdiag_inv);
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
-    const int64_t kk = e / ncol;
-    const int c = (int)(e - kk * ncol);
-    const double bt = beta[c];
-    pcur[e] = dinv[kk] * r[e] + (bt != 0.0 ? bt * pprev[e] : 0.0);
-  }
-  if (blockIdx.x == 0 && threadIdx.x < (unsigned)ncol) {
-    red[(RED_RZ + (k + 1) % 3) * ncol + threadIdx.x] = 0.0;
-    red[(RED_RR + k % 2) * ncol + threadIdx.x] = 0.0;
+  lds[threadIdx.x] = act ? rr : 0.0;
+  if (JAC) lds[NT + threadIdx.x] = act ? rz : 0.0;
+  col_tree(lds, groups, ncol);
+  if (JAC) col_tree(lds + NT, groups, ncol);
+  if (threadIdx.x < (unsigned)ncol) {
+    atomicAdd(red + (RED_RR + k % 2) * ncol + threadIdx.x, lds[threadIdx.x]);
+    if (JAC) atomicAdd(red + (RED_RZ + (k + 1) % 3) * ncol + threadIdx.x, lds[NT + threadIdx.x]);
   }
 }
 
@@ -958,15 +1012,14 @@ __global__ void __launch_bounds__(NT) k_rz_start(const double* __restrict__ part
   }
 }
 
-// start: r = rhs - q (warm) or rhs (cold, x = 0); partial rz, rr.  x over full rows.
+// start: partial rz, rr of the first residual r (cold: x = 0).  x over full rows.
 __global__ void __launch_bounds__(NT) k_cg_start2(const DevMesh* __restrict__ dm, double* __restrict__ x,
-                                                  double* __restrict__ r, const double* __restrict__ q, int ncol,
-                                                  int warm, int64_t part_stride, double* __restrict__ part) {
+                                                  const double* __restrict__ r, int ncol, int warm,
+                                                  int64_t part_stride, double* __restrict__ part) {
   INSTANCE;
   __shared__ double lds[2 * NT];
   x += d.oF * ncol;
   r += d.oE * ncol;
-  q += d.oE * ncol;
   const int groups = NT / ncol;
   const int g = threadIdx.x / ncol, c = threadIdx.x - g * ncol;
   const bool act = g < groups;
@@ -974,36 +1027,21 @@ __global__ void __launch_bounds__(NT) k_cg_start2(const DevMesh* __restrict__ dm
   if (act)
     for (int64_t k = (int64_t)blockIdx.x * groups + g; k < d.N; k += (int64_t)gridDim.x * groups) {
       const int64_t e = k * ncol + c;
-      const double rn = warm ? r[e] - q[e] : r[e];
+      const double rn = r[e];
       if (!warm) x[e] = 0.0;
-      r[e] = rn;
       const double di = gbl(d.kdiag_inv)[k];
       rz += rn * rn * di;
       rr += rn * rn;
     }
   lds[threadIdx.x] = act ? rz : 0.0;
   lds[NT + threadIdx.x] = act ? rr : 0.0;
-  __syncthreads();
+  col_tree(lds, groups, ncol);
+  col_tree(lds + NT, groups, ncol);
   if (threadIdx.x < (unsigned)ncol) {
-    double t = 0.0, u = 0.0;
-    for (int gg = 0; gg < groups; ++gg) {
-      t += lds[gg * ncol + threadIdx.x];
-      u += lds[NT + gg * ncol + threadIdx.x];
-    }
     double* pb = part + blockIdx.y * part_stride + (int64_t)blockIdx.x * 2 * ncol;
-    pb[threadIdx.x] = t;
-    pb[ncol + threadIdx.x] = u;
+    pb[threadIdx.x] = lds[threadIdx.x];
+    pb[ncol + threadIdx.x] = lds[NT + threadIdx.x];
   }
-}
-
-// DoF rows of x (full rows) into y (extended rows)
-__global__ void __launch_bounds__(NT) k_copy_dofs(const DevMesh* __restrict__ dm, const double* __restrict__ x,
-                                                  double* __restrict__ y, int ncol) {
-  INSTANCE;
-  const int64_t total = d.N * ncol;
-  x += d.oF * ncol;
-  y += d.oE * ncol;
-  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) y[e] = x[e];
 }
 
 // Workgroups of the CG start and update passes: about 32 elements per thread,
@@ -1014,49 +1052,71 @@ static int cg_blocks(const Batch& b, int ncol) {
   return nblocks(b.mx.N, NT / ncol, (int)want);
 }
 
-// the operator pass with optional event timing on the launch stream
-static void cg_apply2(const Batch& b, PoissonWs& P, const double* x, const double* pprev, double* pout, double* q,
-                      int k, hipStream_t s) {
+// The CG's operator pass with optional event timing on the launch stream.
+template <class T>
+static int cg_pass(const Batch& b, PoissonWs& P, const T* z, int mode, int k, hipStream_t s) {
   const bool rec = P.ev && P.ev_used + 2 <= P.ev_cap;
   if (rec) {
     (void)hipEventRecord(P.ev[P.ev_used], s);
     t_pass_end = P.ev[P.ev_used + 1];
   }
-  launch_spmv_poisson(b, x, pprev, pout, P.ncol, q, P, k, s);
+  const int rows = launch_spmv_mode<T>(b, z, z, nullptr, P.ncol, nullptr, P.red, mode, k, s, PassExtra{P.w, 0});
   if (rec) {
     t_pass_end = nullptr;
     P.ev_used += 2;
   }
+  return rows;
+}
+// How the solution update of iteration k is taken (k_cg_vectors).
+static int cg_xmode(const Batch& b, int k) { return b.ni > 1 ? 1 : (k % 2 ? 2 : 0); }
+
+constexpr int CG_ROWS = 2;
+template <class Z, bool JAC>
+static void cg_vectors(const Batch& b, double* W, PoissonWs& P, const Z* z, float* rf, int zw_rows, int rz_rows, int k,
+                       hipStream_t s) {
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(cg_blocks(b, P.ncol), b.ni), dim3(NT), 0, s, b.dm, W, P.r, z, P.p,
+                       (const double*)P.w, P.q, P.ncol, P.red, k, rf, cg_xmode(b, k), (const double*)b.spart, zw_rows,
+                       (const double*)(b.spart ? b.spart + b.spart_cap : nullptr), rz_rows);
+  };
+  go(k_cg_vectors<Z, JAC, CG_ROWS>);
+}
+template <class Z>
+static void cg_iteration(const Batch& b, double* W, PoissonWs& P, const Z* z, float* rf, int rz_rows, int k,
+                         hipStream_t s) {
+  const int rows = cg_pass<Z>(b, P, z, SP_CG, k, s);
+  cg_vectors<Z, false>(b, W, P, z, rf, rows, rz_rows, k, s);
+}
+void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const double* z, float* rf, int rz_rows, int k,
+                         hipStream_t s) {
+  cg_iteration(b, W, P, z, rf, rz_rows, k, s);
+}
+void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const float* z, float* rf, int rz_rows, int k,
+                         hipStream_t s) {
+  cg_iteration(b, W, P, z, rf, rz_rows, k, s);
+}
+// One Jacobi-preconditioned iteration.
+void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s) {
+  const int k = P.it;
+  const int rows = cg_pass<double>(b, P, P.r, SP_CGJ, k, s);
+  cg_vectors<double, true>(b, W, P, nullptr, nullptr, rows, 0, k, s);
+  P.it = k + 1;
+}
+// The solution update still open after `it` iterations: x += alpha p of the
+// last one where it left its term to a next pass.
+void launch_cg_finish(const Batch& b, double* W, PoissonWs& P, int it, hipStream_t s) {
+  if (it > 0 && cg_xmode(b, it - 1) == 0)
+    cg_xfinal(b.dm, b.ni, b.mx.N, P.ncol, W, P.p, P.red, RED_RZ + (it - 1) % 3, RED_ETA + (it - 1) % 2, s);
 }
 
 void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int warm, hipStream_t s) {
   const int ncol = P.ncol;
-  if (warm) {  // q = K x0, x0 = the DoF rows of W (staged in the first direction buffer)
-    hipLaunchKernelGGL(k_copy_dofs, dim3(nblocks(b.mx.N * ncol, NT, 8192), b.ni), dim3(NT), 0, s, b.dm, W, P.p, ncol);
-    cg_apply2(b, P, P.p, P.p2, P.p2, P.q, -1, s);
-  }
+  // warm: r = rhs - K x0, x0 = the DoF rows of W (full rows)
+  if (warm) launch_spmv_mode<double>(b, W, rhs_r, rhs_r, ncol, rhs_r, P.red, SP_RES, -1, s, no_extra(1));
   const int nb = cg_blocks(b, ncol);
-  hipLaunchKernelGGL(k_cg_start2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, rhs_r, P.q, ncol, warm, P.part_stride,
-                     P.part);
+  hipLaunchKernelGGL(k_cg_start2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, rhs_r, ncol, warm, P.part_stride, P.part);
   hipLaunchKernelGGL(k_rz_start, dim3(ncol, b.ni), dim3(NT), 0, s, P.part, P.part_stride, nb, ncol, P.sc, P.red);
   P.it = 0;
-}
-
-void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s) {
-  const int ncol = P.ncol, k = P.it;
-  double* pcur = (k % 2) ? P.p2 : P.p;
-  double* pprev = (k % 2) ? P.p : P.p2;
-  if (b.mx.sched_poi & 8) {
-    cg_apply2(b, P, P.r, pprev, pcur, P.q, k, s);  // direction formed inside the operator pass
-  } else {
-    hipLaunchKernelGGL(k_cg_dir, dim3(nblocks(b.mx.N * ncol, NT, 8192), b.ni), dim3(NT), 0, s, b.dm, P.r, pprev, pcur,
-                       ncol, P.red, k);
-    cg_apply2(b, P, pcur, pprev, pcur, P.q, -2 - k, s);  // plain operator pass of iteration k
-  }
-  const int nb = cg_blocks(b, ncol);
-  hipLaunchKernelGGL(k_cg_update2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, P.r, pcur, P.q, ncol, P.red, k,
-                     (float*)nullptr, 1);
-  P.it = k + 1;
 }
 
 // Chebyshev smoothing on the finest multigrid level fused into the operator
@@ -1065,20 +1125,21 @@ void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s) {
 // t = r - K z on the finest level (the residual the restriction reads)
 void launch_mg_resid(const Batch& b, const double* z, const double* r, double* t, int ncol, double* red_scratch,
                      hipStream_t s) {
-  launch_spmv_mode(b, z, r, t, ncol, t, red_scratch, SP_RES, -1, s);
+  launch_spmv_mode(b, z, r, t, ncol, t, red_scratch, SP_RES, -1, s, no_extra());
 }
 void launch_mg_resid_f(const Batch& b, const float* z, const float* r, float* t, int ncol, double* red_scratch,
                        hipStream_t s) {
-  launch_spmv_mode<float>(b, z, r, t, ncol, t, red_scratch, SP_RES, -1, s);
+  launch_spmv_mode<float>(b, z, r, t, ncol, t, red_scratch, SP_RES, -1, s, no_extra());
 }
 void launch_mg_cheb0(const Batch& b, const double* r, double* z, double* d, double* red, int rz_slot, int ncol,
                      hipStream_t s) {
-  launch_spmv_mode(b, r, r, z, ncol, d, red, SP_CHEB0, rz_slot, s);
+  launch_spmv_mode(b, r, r, z, ncol, d, red, SP_CHEB0, rz_slot, s, no_extra());
 }
-void launch_mg_cheb_step(const Batch& b, const double* zin, const double* r, double* zout, double* d, double* red,
+int launch_mg_cheb_step(const Batch& b, const double* zin, const double* r, double* zout, double* d, double* red,
                          int ncol, int k, int rz_slot, hipStream_t s) {
-  if (rz_slot >= 0) launch_spmv_mode(b, zin, r, zout, ncol, d, red, SP_CHEB_RZ, rz_slot | (k << 4), s);
-  else launch_spmv_mode(b, zin, r, zout, ncol, d, red, SP_CHEB, k, s);
+  if (rz_slot >= 0)
+    return launch_spmv_mode(b, zin, r, zout, ncol, d, red, SP_CHEB_RZ, rz_slot | (k << 4), s, no_extra());
+  return launch_spmv_mode(b, zin, r, zout, ncol, d, red, SP_CHEB, k, s, no_extra());
 }
 
 // The same finest-level passes on float storage (Poisson schedule bit 6):
@@ -1087,19 +1148,15 @@ void launch_mg_cheb_step(const Batch& b, const double* zin, const double* r, dou
 // double passes of the CG itself).
 void launch_mg_cheb0_f(const Batch& b, const float* r, float* z, float* d, double* red, int rz_slot, int ncol,
                        hipStream_t s) {
-  launch_spmv_mode<float>(b, r, r, z, ncol, d, red, SP_CHEB0, rz_slot, s);
+  launch_spmv_mode<float>(b, r, r, z, ncol, d, red, SP_CHEB0, rz_slot, s, no_extra());
 }
-void launch_mg_cheb_step_f(const Batch& b, const float* zin, const float* r, float* zout, float* d, double* red,
+int launch_mg_cheb_step_f(const Batch& b, const float* zin, const float* r, float* zout, float* d, double* red,
                            int ncol, int k, int rz_slot, hipStream_t s) {
-  if (rz_slot >= 0) launch_spmv_mode<float>(b, zin, r, zout, ncol, d, red, SP_CHEB_RZ, rz_slot | (k << 4), s);
-  else launch_spmv_mode<float>(b, zin, r, zout, ncol, d, red, SP_CHEB, k, s);
+  if (rz_slot >= 0)
+    return launch_spmv_mode<float>(b, zin, r, zout, ncol, d, red, SP_CHEB_RZ, rz_slot | (k << 4), s, no_extra());
+  return launch_spmv_mode<float>(b, zin, r, zout, ncol, d, red, SP_CHEB, k, s, no_extra());
 }
 
-// The plain operator pass of CG iteration k on the direction p (q = K p, p.q
-// accumulated for the update pass), and the update pass itself.
-void launch_cg_apply_plain(const Batch& b, PoissonWs& P, const double* p, int k, hipStream_t s) {
-  cg_apply2(b, P, p, p, const_cast<double*>(p), P.q, -2 - k, s);
-}
 // Convergence flags of a batch's multigrid CG (the host test of the same
 // solve, on the device): after the update pass of iteration k an instance is
 // done once every column's r.r is at most rtol^2 times its largest column's
@@ -1131,12 +1188,6 @@ __global__ void k_zero_int(int* __restrict__ x, int n) {
 }
 void launch_zero_int(int* x, int n, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(k_zero_int, dim3(nblocks(n)), dim3(NT), 0, s, x, n);
-}
-
-void launch_cg_update(const Batch& b, double* W, PoissonWs& P, const double* p, int k, hipStream_t s, float* rf,
-                      int upd_x) {
-  const int nb = cg_blocks(b, P.ncol);
-  hipLaunchKernelGGL(k_cg_update2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, P.r, p, P.q, P.ncol, P.red, k, rf, upd_x);
 }
 
 __global__ void __launch_bounds__(NT) k_to_float(const double* __restrict__ x, float* __restrict__ y, int64_t nd) {
