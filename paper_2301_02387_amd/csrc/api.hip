@@ -675,11 +675,10 @@ static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_de
   c.dim = c.NA * c.NB;
   c.exa = op->upload(excitation_table(n, sa), s);
   c.exb = op->upload(excitation_table(n, sb), s);
-  c.D = op->alloc<double>((size_t)ni * 2 * c.dim * ncol);
   c.T = op->alloc<double>((size_t)ni * 2 * c.dim * ncol);
   c.hp = op->alloc<double>((size_t)ni * 2 * ncol);
   c.w = op->alloc<double>((size_t)ni * 2 * c.dim);
-  c.part = op->alloc<double>((size_t)ni * gram_blocks(c.dim) * 2 * 4096 + 64);
+  c.part = op->alloc<double>((size_t)ni * ci_part_doubles(c.dim));
   int mci = std::min(12, c.dim);
   for (int j = 0; j <= mci; ++j) op->Qh.push_back(op->alloc<double>((size_t)ni * 2 * c.dim));
   op->Qdev = op->alloc<double*>(op->Qh.size());
@@ -1293,7 +1292,7 @@ extern "C" int mh_poisson_pairs(mh_op* op, const double* phi, double* W, int32_t
 extern "C" int mh_ci_rdms(mh_op* op, const double* Ci, double* gamma, double* Gamma, void* stream) {
   if (!op || !Ci || !gamma || !Gamma) return fail(MH_INVALID_ARG, "null argument");
   return guarded([&]() -> int {
-    launch_ci_rdm_full(op->ni, op->ci, Ci, gamma, Gamma, op->Gtmp, S(stream));
+    launch_ci_rdm_full(op->ni, op->ci, Ci, gamma, Gamma, S(stream));
     HIPCHK(hipGetLastError());
     return MH_OK;
   });
@@ -1396,7 +1395,7 @@ static void whole_step(mh_op* op, double* phi, double* Ci, double* W, int K, dou
                        int imaginary, hipStream_t s) {
   const Batch& B = op->B;
   const int64_t wlen = (int64_t)B.tF * op->ncol;
-  launch_ci_rdm_full(op->ni, op->ci, Ci, op->gam, op->Gam, op->Gtmp, s);
+  launch_ci_rdm_full(op->ni, op->ci, Ci, op->gam, op->Gam, s);
   launch_extrapolate2(W, op->Wprev, op->Wprev2, wlen, s);
   poisson_begin(op, phi, W, 1, s);
   mg_pcg(op, W, nullptr, s, K);
@@ -1525,7 +1524,7 @@ extern "C" int mh_propagate(mh_op* op, double* phi, double* Ci, double* W, const
         if (rr != MH_OK) return rr;
         continue;
       }
-      launch_ci_rdm_full(ni, op->ci, Ci, op->gam, op->Gam, op->Gtmp, s);
+      launch_ci_rdm_full(ni, op->ci, Ci, op->gam, op->Gam, s);
       int it = 0;
       // CG start: the previous solution; at the third step of the call the
       // linear extrapolation 2 W_{n-1} - W_{n-2}, from the fourth the quadratic
@@ -1776,7 +1775,6 @@ extern "C" int mh_propagate_adjoint(mh_op* op, const double* phi0, const double*
     double* th = mem.get((size_t)2 * nn), *tg2 = mem.get((size_t)2 * nn * nn);
     double* Gz = mem.get((size_t)2 * nn), *Sm = mem.get((size_t)2 * nn);
     double* kap = mem.get(clen), *ca = mem.get(clen), *cb = mem.get(clen), *sig = mem.get(clen);
-    double* DA = mem.get((size_t)2 * dim * nn), *DB = mem.get((size_t)2 * dim * nn);
     double* ebar = mem.get((size_t)n_steps + 1);
     launch_zero(ebar, n_steps + 1, s);
     launch_zero(Zb, wlen, s);
@@ -1787,7 +1785,7 @@ extern "C" int mh_propagate_adjoint(mh_op* op, const double* phi0, const double*
 
     // one forward step of mh_propagate (real time), W warm-started from its contents
     auto fwd_step = [&](double* c, double* Cv, double* W, int k) -> int {
-      launch_ci_rdm_full(1, op->ci, Cv, op->gam, op->Gam, op->Gtmp, s);
+      launch_ci_rdm_full(1, op->ci, Cv, op->gam, op->Gam, s);
       int it = 0;
       const int rc = poisson_solve(op, c, W, 1, &it, s);
       if (rc < 0) return rc;
@@ -1819,7 +1817,7 @@ extern "C" int mh_propagate_adjoint(mh_op* op, const double* phi0, const double*
       if (rc < 0) return rc;
     }
     // terminal adjoint state from d_N
-    launch_ci_rdm_full(1, op->ci, curC, op->gam, op->Gam, op->Gtmp, s);
+    launch_ci_rdm_full(1, op->ci, curC, op->gam, op->Gam, s);
     launch_gram(B, cur, cur, WT_DIPOLE, ROWS_EXT, op->gpart, gram_blocks(B.mx.NE), op->zmat, s);
     launch_zero(sm, 2 * ADJ_NBLK * nn, s);
     launch_zero(KGam, 2 * nn * nn, s);
@@ -1843,7 +1841,7 @@ extern "C" int mh_propagate_adjoint(mh_op* op, const double* phi0, const double*
       for (int k = s0; k < s1; ++k) {
         const int j = k - s0;
         launch_copy(j == 0 ? W_work : segW[j - 1], segW[j], wlen, s);
-        launch_ci_rdm_full(1, op->ci, segC[j], op->gam, op->Gam, op->Gtmp, s);
+        launch_ci_rdm_full(1, op->ci, segC[j], op->gam, op->Gam, s);
         int it = 0;
         const int rc = poisson_solve(op, seg[j], segW[j], 1, &it, s);
         if (rc < 0) return rc;
@@ -1864,7 +1862,7 @@ extern "C" int mh_propagate_adjoint(mh_op* op, const double* phi0, const double*
         launch_zero(Kg, 2 * nn * nn, s);
         launch_zero(Q, 2 * B.tE * nn, s);
         // frozen data, integrals and observables of step k
-        launch_ci_rdm_full(1, op->ci, Cv, op->gam, op->Gam, op->Gtmp, s);
+        launch_ci_rdm_full(1, op->ci, Cv, op->gam, op->Gam, s);
         launch_set(op->Ebuf, E_steps[k], s);
         freeze_body(op, c, op->gam, op->Gam, W, s);
         load_vector(op, c, op->Ebuf, 1, op->F, s);
@@ -1895,7 +1893,7 @@ extern "C" int mh_propagate_adjoint(mh_op* op, const double* phi0, const double*
                             0, s);
           launch_copy(Cv, cb, clen, s);
           launch_ci_lanczos(1, op->ci, op->Qdev, op->Qh.data(), mci, op->gint, cb, op->KC, gx[j] * dt, 0.0, 0, s);
-          launch_ci_trdm(1, op->ci, ca, cb, DA, DB, tgam, tGam, op->Gtmp, s);
+          launch_ci_trdm(1, op->ci, ca, cb, tgam, tGam, s);
           launch_caxpy(nn, 0.0, wi, tgam, KH, s);
           launch_caxpy((int64_t)nn * nn, 0.0, 0.5 * wi, tGam, Kg, s);
         }

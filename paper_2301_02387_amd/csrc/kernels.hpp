@@ -173,9 +173,6 @@ int gram_blocks(int64_t rows);
 // (A, B batch orbital arrays [tE][n]); G instance stride n*n.
 void launch_gram(const Batch& b, const double* A, const double* B, int wsel, int rows, double* part, int nblk,
                  double* G, hipStream_t s);
-// Same on flat per-instance arrays of `rows` rows: X [ni][rows][na], Y [ni][rows][nb].
-void launch_xgram_flat(int ni, const double* X, int na, const double* Y, int nb, int64_t rows, double* part,
-                       int nblk, double* out, hipStream_t s);
 int gint_blocks(const Batch& b);
 void launch_gint_full(const Batch& b, const double* phi, const double* W, const int* colmap, double* part, int nblk,
                       double* Gtmp, double* g, hipStream_t s);
@@ -297,19 +294,19 @@ struct CIDev {
   int n = 0, NA = 0, NB = 0, dim = 0;
   const int32_t* exa = nullptr;  // [NA][n*n]: I | (sign<0)<<30 with E_pq|I> = sign|J>, or -1
   const int32_t* exb = nullptr;  // [NB][n*n]
-  double* D = nullptr;           // [ni][dim][n*n] c128
   double* T = nullptr;           // [ni][dim][n*n] c128
   double* hp = nullptr;          // h' [ni][n*n] c128
   double* part = nullptr;
   double* w = nullptr;           // [ni][dim] c128
 };
-void launch_ci_rdm_full(int ni, const CIDev& c, const double* C, double* gamma, double* Gamma, double* Gtmp,
-                        hipStream_t s);
+size_t ci_part_doubles(int dim);   // doubles of CIDev::part per instance
+void launch_ci_rdm_full(int ni, const CIDev& c, const double* C, double* gamma, double* Gamma, hipStream_t s);
 void launch_ci_hprime(int ni, const CIDev& c, const double* h, const double* g, hipStream_t s);
 void launch_ci_lanczos(int ni, const CIDev& c, double* const* Qdev, double* const* Qhost, int m, const double* g,
                        double* Cvec, Krylov& K, double tau_re, double tau_im, int normalize, hipStream_t s);
-void launch_ci_trdm(int ni, const CIDev& c, const double* A, const double* Bv, double* DA, double* DB,
-                    double* gamma, double* Gamma, double* Gtmp, hipStream_t s);
+// Transition RDMs <A|E_pq|B> and <A|E_pq E_rs|B> - delta_qr <A|E_ps|B>
+void launch_ci_trdm(int ni, const CIDev& c, const double* A, const double* Bv, double* gamma, double* Gamma,
+                    hipStream_t s);
 void launch_ci_apply(int ni, const CIDev& c, const double* h, const double* g, const double* C, double* sigma,
                      hipStream_t s);
 

@@ -122,3 +122,56 @@ def test_arnoldi_second_pass(copies):
     x = x + 1e-3 * np.linalg.norm(x) / np.sqrt(N) * (rng.standard_normal(N) + 1j * rng.standard_normal(N))
     H = check_arnoldi(P, op, x[:, None], fr, 0.02, 6, copies)
     assert np.abs(H[1, 0]) < 0.1 * np.linalg.norm(H[:2, 0])
+
+
+@pytest.mark.parametrize("n,na,nb", [(1, 1, 0), (2, 1, 1), (2, 2, 1), (3, 2, 1), (4, 3, 2), (5, 2, 3), (5, 3, 2), (6, 3, 2),
+                                     (7, 4, 3), (8, 5, 5)])
+@pytest.mark.parametrize("copies", [1, 2])
+def test_rdms_tiles(n, na, nb, copies):
+    """RDMs at every pair-tile count, in one workgroup (at most 64
+    determinants) and with partial sums, ragged last chunks among them; sums of
+    at most 3,136 products of amplitudes of a unit vector: 1e-13."""
+    import torch
+    import paper_2301_02387_amd as mh
+    from oracle.ci import CISpace
+    from synth import random_ci
+    P = pair("uniform_q1_odd")
+    op = mh.Operator.batch([P.mesh] * copies, [P.w["nuclei"]] * copies, n, na, nb)
+    cs = CISpace(n, na, nb)
+    C = np.stack([random_ci(cs.dim, 90 + i) for i in range(copies)])
+    gam = torch.zeros((copies, n, n), dtype=torch.complex128, device="cuda")
+    Gam = torch.zeros((copies, n, n, n, n), dtype=torch.complex128, device="cuda")
+    op.ci_rdms(dev(C), gam, Gam)
+    torch.cuda.synchronize()
+    for i in range(copies):
+        g_ref, G_ref = cs.rdms(C[i])
+        assert np.abs(gam[i].cpu().numpy() - g_ref).max() <= 1e-13
+        assert np.abs(Gam[i].cpu().numpy() - G_ref).max() <= 1e-13
+
+
+@pytest.mark.parametrize("n,na,nb", [(2, 1, 1), (3, 2, 1), (4, 2, 2), (4, 3, 3), (5, 2, 2), (6, 2, 1)])
+def test_ci_step_sizes(n, na, nb):
+    """Two coupled steps with the CI exponential in one workgroup (up to 64
+    determinants and 1,024 amplitudes: 4, 9, 36, 16 determinants) and by the
+    launches beyond (100 and 90 determinants, the 12-vector space)."""
+    import torch
+    import paper_2301_02387_amd as mh
+    from oracle.ci import CISpace
+    from oracle.mctdhf import Propagator
+    from synth import random_ci
+    from tests.lib_cases import rel_err_cols
+    P = pair("tiny_q1")
+    op = mh.Operator(P.mesh, P.w["nuclei"], n, na, nb, poisson_rtol=1e-13, poisson_maxit=20000)
+    op.tune(1, 53, 8192)
+    cs = CISpace(n, na, nb)
+    c, C = orbitals(P, n, 70 + n), random_ci(cs.dim, 71)
+    pr = Propagator(P.ops, cs, poisson_solver(P.ops))
+    cr, Cr = c, C
+    for E in (0.01, 0.03):
+        cr, Cr, _ = pr.step(cr, Cr, E, 0.02, 10)
+    x, Cd = dev(P.to_lib_orb(c)), dev(C)
+    W = torch.zeros((P.NF, n * n), dtype=torch.float64, device="cuda")
+    op.propagate(x, Cd, W, [0.01, 0.03, 0.0], 0.02, m=10, final=False)
+    torch.cuda.synchronize()
+    assert np.linalg.norm(Cd.cpu().numpy().ravel() - Cr) <= 1e-8
+    assert rel_err_cols(P.from_lib_dof(x.cpu().numpy()), cr) <= 1e-8
