@@ -944,6 +944,7 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
   upload_instances(op, s);
   std::vector<std::vector<MgLevelDev>> rec(nlev, std::vector<MgLevelDev>(ni));
   std::vector<MgLevelDev> co(ni);
+  std::vector<std::vector<double>> keep_vd;
   for (int i = 0; i < ni; ++i) {
     const DevMesh& dh = op->dh[i];
     const int nl = (int)H[i].lv.size();
@@ -971,9 +972,17 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
         L.a_col = op->upload(h.k_col, s);
         L.a_val = op->upload(h.k_val, s);
         L.dinv = op->upload(h.dinv, s);
+        std::vector<double> vd(h.k_val.size());
+        for (size_t t = 0; t < vd.size(); ++t) vd[t] = h.k_val[t] * h.dinv[h.k_col[t]];
+        keep_vd.push_back(std::move(vd));   // host copy alive until the final synchronisation
+        L.a_vd = op->upload(keep_vd.back(), s);
         const size_t len = (size_t)std::max<int64_t>(1, h.N) * ncol;
+        L.Nh = h.h_ptr.empty() ? 0 : (int64_t)h.h_ptr.size() - 1;
+        L.h_ptr = op->upload(h.h_ptr, s);
+        L.h_col = op->upload(h.h_col, s);
+        L.h_w = op->upload(h.h_w, s);
         L.r = op->alloc<double>(len);
-        L.z = op->alloc<double>(len);
+        L.z = op->alloc<double>(len + (size_t)L.Nh * ncol);
         L.d = op->alloc<double>(len);
         L.t = op->alloc<double>(len);
       }
@@ -986,6 +995,11 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
         L.r_ptr = op->upload(h.r_ptr, s);
         L.r_col = op->upload(h.r_col, s);
         L.r_val = op->upload(h.r_val, s);
+        if (h.cell_pf) {
+          L.nC = (int64_t)(h.cell_f.size() / ((size_t)h.cell_pf * h.cell_pf * h.cell_pf));
+          L.cell_f = op->upload(h.cell_f, s);
+          L.cell_c = op->upload(h.cell_c, s);
+        }
       } else {
         double* ci = op->upload(H[i].coarse_dense, s);
         launch_dense_inverse(ci, h.N, s);  // Gauss-Jordan (the operator is SPD)
@@ -997,6 +1011,28 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
     }
   }
   mg->nlev = nlev;
+  // cell by cell where every instance that has the level transfers so, with the same degrees
+  for (int l = 0; l + 1 < nlev; ++l) {
+    bool all = true;
+    for (int i = 0; i < ni; ++i) {
+      if (l + 1 >= (int)H[i].lv.size()) continue;
+      const MgLevel& h = H[i].lv[l];
+      if (!mg->cell_pf[l]) {
+        mg->cell_pf[l] = h.cell_pf;
+        mg->cell_pc[l] = h.cell_pc;
+      }
+      all = all && h.cell_pf && h.cell_pf == mg->cell_pf[l] && h.cell_pc == mg->cell_pc[l];
+      mg->max_cells[l] = std::max(mg->max_cells[l], rec[l][i].nC);
+      mg->max_hang[l + 1] = std::max(mg->max_hang[l + 1], rec[l + 1][i].Nh);
+    }
+    if (!all) mg->cell_pf[l] = mg->cell_pc[l] = 0;
+    const int pf = mg->cell_pf[l], pc = mg->cell_pc[l];
+    if (pf) {
+      const Gll f = make_gll(pf - 1), c = make_gll(pc - 1);
+      for (int a = 0; a < pf; ++a)
+        for (int b = 0; b < pc; ++b) mg->interp[l][a * pc + b] = lagrange(c.x, b, f.x[a]);
+    }
+  }
   for (int l = 0; l < nlev; ++l) mg->lv.push_back(op->upload(rec[l], s));
   mg->lv0_double = mg->lv[0];
   for (MgLevelDev& L : rec[0]) L.f32 = 1;

@@ -119,8 +119,8 @@ void build_operator(const Mesh& mesh, const std::vector<Nucleus>& nuc, const dou
 
 // Geometric multigrid hierarchy for the assembled pair Poisson operator
 // (homogeneous Dirichlet problem on the DoFs).  Level 0 is the operator's own
-// mesh; level 1 is Q1 on the same leaves; then Q1 with every ball one level
-// shallower, down to the uniform base grid; then base grids of half the cells
+// mesh; below Q3 comes Q2 on the same leaves, then Q1 on them, then Q1 with every
+// ball one level shallower, down to the uniform base grid; then base grids of half the cells
 // per edge while the interior is larger than `max_coarse`.  The spaces are
 // nested, so the prolongation is nodal interpolation of the coarse function at
 // the fine DoF nodes (coarse hanging nodes expanded through their constraints,
@@ -134,6 +134,15 @@ struct MgLevel {
   std::vector<double> p_val;
   std::vector<int32_t> r_ptr, r_col;       // restriction to level l+1 (transpose): rows = DoFs of l+1
   std::vector<double> r_val;
+  // the next level lies on the same leaves at a lower degree (prolongation cell
+  // by cell): P = cell_pf, cell_pc nodes per edge (0: not so); per cell the fine
+  // DoFs this cell writes (-1: another cell's, hanging or boundary nodes), and
+  // the coarse nodes' rows (DoFs, then hanging rows; -1: boundary)
+  int cell_pf = 0, cell_pc = 0;
+  std::vector<int32_t> cell_f, cell_c;
+  // this level's hanging rows over its DoFs
+  std::vector<int32_t> h_ptr, h_col;
+  std::vector<double> h_w;
 };
 struct MgHost {
   std::vector<MgLevel> lv;                 // lv[0] finest ... lv.back() coarsest

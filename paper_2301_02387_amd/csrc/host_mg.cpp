@@ -132,8 +132,123 @@ void take_operator(const OpHost& H, int64_t N, MgLevel& L) {
   L.dinv = H.kdiag_inv;
 }
 
+// Tables of the cell-by-cell prolongation where mesh C has F's leaves at a lower
+// degree: F's levels' cell_f, cell_c and C's hanging rows (into the level of C).
+void cell_transfer(const Mesh& F, const Mesh& C, MgLevel& lf, MgLevel& lc) {
+  std::unordered_map<uint64_t, int64_t> leaves;
+  leaves.reserve(C.n_cells * 2);
+  for (int64_t e = 0; e < C.n_cells; ++e)
+    leaves[leaf_key(C.cell_level[e], C.cell_ijk[3 * e], C.cell_ijk[3 * e + 1], C.cell_ijk[3 * e + 2])] = e;
+  const int64_t F3 = (int64_t)F.P * F.P * F.P, C3 = (int64_t)C.P * C.P * C.P, NEc = C.N + C.Nh;
+  std::vector<int32_t> cf(F.n_cells * F3, -1), cc(F.n_cells * C3, -1);
+  std::vector<char> taken(F.N, 0);
+  for (int64_t e = 0; e < F.n_cells; ++e) {
+    auto it = leaves.find(leaf_key(F.cell_level[e], F.cell_ijk[3 * e], F.cell_ijk[3 * e + 1], F.cell_ijk[3 * e + 2]));
+    if (it == leaves.end()) return;   // other leaves
+    for (int64_t t = 0; t < F3; ++t) {
+      const int32_t nd = F.cell_nodes[e * F3 + t];
+      if (nd < F.N && !taken[nd]) {
+        taken[nd] = 1;
+        cf[e * F3 + t] = nd;
+      }
+    }
+    for (int64_t t = 0; t < C3; ++t) {
+      const int32_t nd = C.cell_nodes[it->second * C3 + t];
+      if (nd < NEc) cc[e * C3 + t] = nd;
+    }
+  }
+  for (char t : taken)
+    if (!t) return;
+  lf.cell_pf = F.P;
+  lf.cell_pc = C.P;
+  lf.cell_f.swap(cf);
+  lf.cell_c.swap(cc);
+  lc.h_ptr.assign(C.Nh + 1, 0);
+  for (int64_t h = 0; h < C.Nh; ++h) {
+    for (int64_t t = C.hang_ptr[h]; t < C.hang_ptr[h + 1]; ++t)
+      if (C.hang_col[t] < C.N) {
+        lc.h_col.push_back((int32_t)C.hang_col[t]);
+        lc.h_w.push_back(C.hang_w[t]);
+      }
+    lc.h_ptr[h + 1] = (int32_t)lc.h_col.size();
+  }
+}
+
+// L <- P^T A P, A and the prolongation P from level F: row by row A P (its
+// entries in order of first appearance), then each coarse row from the fine
+// rows it gathers.  Entries at the rounding level of the product are dropped
+// (by a symmetric test, so L stays symmetric).
+void galerkin(const MgLevel& F, int64_t Nc, MgLevel& L) {
+  std::vector<int32_t> ap_ptr(F.N + 1, 0), ap_col, at(Nc, -1);
+  std::vector<double> ap_val;
+  for (int64_t i = 0; i < F.N; ++i) {
+    const int32_t beg = (int32_t)ap_col.size();
+    for (int32_t t = F.k_ptr[i]; t < F.k_ptr[i + 1]; ++t) {
+      const int32_t k = F.k_col[t];
+      for (int32_t u = F.p_ptr[k]; u < F.p_ptr[k + 1]; ++u) {
+        const int32_t c = F.p_col[u];
+        const double v = F.k_val[t] * F.p_val[u];
+        if (at[c] < beg) {
+          at[c] = (int32_t)ap_col.size();
+          ap_col.push_back(c);
+          ap_val.push_back(v);
+        } else {
+          ap_val[at[c]] += v;
+        }
+      }
+    }
+    if (ap_col.size() >= (size_t)INT32_MAX) throw std::runtime_error("multigrid: coarse operator too large");
+    ap_ptr[i + 1] = (int32_t)ap_col.size();
+  }
+  std::fill(at.begin(), at.end(), -1);
+  L.N = Nc;
+  L.k_ptr.assign(Nc + 1, 0);
+  L.k_col.clear();
+  L.k_val.clear();
+  L.dinv.assign(Nc, 0.0);
+  std::vector<double> diag(Nc, 0.0);
+  std::vector<std::vector<std::pair<int32_t, double>>> rows(Nc);
+  for (int64_t r = 0; r < Nc; ++r) {
+    auto& row = rows[r];
+    for (int32_t t = F.r_ptr[r]; t < F.r_ptr[r + 1]; ++t) {
+      const int32_t i = F.r_col[t];
+      for (int32_t u = ap_ptr[i]; u < ap_ptr[i + 1]; ++u) {
+        const int32_t c = ap_col[u];
+        const double v = F.r_val[t] * ap_val[u];
+        if (at[c] < 0) {
+          at[c] = (int32_t)row.size();
+          row.push_back({c, v});
+        } else {
+          row[at[c]].second += v;
+        }
+      }
+    }
+    for (const auto& e : row) at[e.first] = -1;
+    std::sort(row.begin(), row.end());
+    for (const auto& e : row)
+      if (e.first == r) diag[r] = e.second;
+  }
+  for (int64_t r = 0; r < Nc; ++r) {
+    for (const auto& e : rows[r])
+      if (e.second * e.second > 1e-28 * diag[r] * diag[e.first]) {
+        L.k_col.push_back(e.first);
+        L.k_val.push_back(e.second);
+      }
+    if (L.k_col.size() >= (size_t)INT32_MAX) throw std::runtime_error("multigrid: coarse operator too large");
+    L.k_ptr[r + 1] = (int32_t)L.k_col.size();
+    L.dinv[r] = 1.0 / diag[r];
+  }
+}
+
 }  // namespace
 
+// Operators of the levels: Q2 below Q3 is rediscretised (the Galerkin product
+// would carry 60 entries a row where the collocated operator carries 13), Q1
+// levels are Galerkin products P^T A P: the collocated Q1 operator, with its
+// lumped mass, is stiffer than the fine one on the modes the smoother leaves.
+// Iterations of the CG from zero to 1e-12, Q1 straight below Q3 and collocated
+// operators -> these: H2 (Q3) 20 -> 11, a Q2 mesh of 50,429 unknowns 16 -> 12, a
+// Q1 mesh of 14,205 17 -> 13.
 void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_coarse) {
   mg.lv.clear();
   std::vector<Mesh> meshes;
@@ -141,18 +256,19 @@ void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_co
   MgLevel L0;
   take_operator(fop, fine.N, L0);
   mg.lv.push_back(std::move(L0));
-  // coarser meshes: Q1 on the same leaves, then shallower balls (a Kelly mesh:
-  // its leaves capped one level shallower at a time, so every level nests in
-  // the one above), then coarser base grids
+  // coarser meshes: Q2 on the same leaves (below Q3), Q1 on them, then shallower
+  // balls (a Kelly mesh: its leaves capped one level shallower at a time, so every
+  // level nests in the one above), then coarser base grids
   struct Plan {
-    int nc;
+    int nc, p;
     std::vector<Ball> balls;
     int cap;  // level cap of a Kelly mesh, -1 otherwise
   };
   std::vector<Plan> plan;
   const bool kelly = !fine.kelly.nuclei.empty();
+  if (fine.p == 3) plan.push_back({fine.nc, 2, fine.balls, kelly ? fine.Lmax : -1});
   if (kelly) {
-    for (int cap = fine.Lmax; cap >= 0; --cap) plan.push_back({fine.nc, {}, cap});
+    for (int cap = fine.Lmax; cap >= 0; --cap) plan.push_back({fine.nc, 1, {}, cap});
   } else {
     int maxlev = 0;
     for (const Ball& b : fine.balls) maxlev = std::max(maxlev, b.levels);
@@ -162,20 +278,20 @@ void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_co
         b.levels = std::max(0, b.levels - drop);
         if (b.levels > 0) bl.push_back(b);
       }
-      plan.push_back({fine.nc, bl, -1});
+      plan.push_back({fine.nc, 1, bl, -1});
     }
   }
   for (int nc = fine.nc; nc % 2 == 0 && (int64_t)(nc - 1) * (nc - 1) * (nc - 1) > max_coarse;) {
     nc /= 2;
-    plan.push_back({nc, {}, -1});
+    plan.push_back({nc, 1, {}, -1});
   }
   const double pol[3] = {0.0, 0.0, 1.0};
   for (size_t pi = 0; pi < plan.size(); ++pi) {
     const auto& pl = plan[pi];
     Mesh C;
     bool uns = false;
-    std::string err = pl.cap >= 0 ? build_mesh(fine.lo, fine.hi, pl.nc, 1, {}, C, uns, nullptr, pl.cap, &fine)
-                                  : build_mesh(fine.lo, fine.hi, pl.nc, 1, pl.balls, C, uns);
+    std::string err = pl.cap >= 0 ? build_mesh(fine.lo, fine.hi, pl.nc, pl.p, {}, C, uns, nullptr, pl.cap, &fine)
+                                  : build_mesh(fine.lo, fine.hi, pl.nc, pl.p, pl.balls, C, uns);
     if (!err.empty()) throw std::runtime_error("multigrid coarse mesh: " + err);
     const Mesh& F = meshes.back();
     if (F.p == 1 && C.n_cells == F.n_cells && C.nc == F.nc) continue;  // same mesh as the level above
@@ -183,11 +299,16 @@ void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_co
     // coarsening much; skip it (the meshes are nested, so the next one still is)
     if (pi + 1 < plan.size() && (double)C.N > 0.6 * (double)mg.lv.back().N) continue;
     if (C.N == 0) break;
-    OpHost HC;
-    build_operator(C, {}, pol, 0, HC);
     prolongation(F, C, mg.lv.back());
     MgLevel LC;
-    take_operator(HC, C.N, LC);
+    if (pl.p == 1) {
+      galerkin(mg.lv.back(), C.N, LC);
+    } else {
+      OpHost HC;
+      build_operator(C, {}, pol, 0, HC);
+      take_operator(HC, C.N, LC);
+    }
+    if (F.n_cells == C.n_cells && F.nc == C.nc && F.p == C.p + 1) cell_transfer(F, C, mg.lv.back(), LC);
     mg.lv.push_back(std::move(LC));
     meshes.push_back(std::move(C));
     if (mg.lv.back().N <= max_coarse) break;  // small enough for the dense solve

@@ -8,6 +8,7 @@
 // records of levels an instance does not have are inactive.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "devutil.hpp"
@@ -111,53 +112,43 @@ __device__ __forceinline__ void row_gather_v(IP col, DP val, int beg, int end, i
   }
 }
 
-// coarse.r = R (fine.r - fine.t) for each instance whose fine record is
-// active (tres: fine.t holds the residual r - A z already, R fine.t).  A
-// restriction row gathers every fine node in the support of a coarse basis
-// function (up to 343 entries from Q3 to Q1), so one wave takes a row: groups
-// of cw lanes (a power of two >= ncol) split its entries, lane c of a group
-// holds column c, and the groups are combined by shuffles.
+// coarse.r = R fine.t (t: the residual r - A z) for each instance whose fine
+// record is active.  A restriction row gathers every fine node in the support
+// of a coarse basis function, so G lanes take a row: groups of cw lanes (a power
+// of two >= ncol) split its entries, lane c of a group holds column c, and the
+// groups are combined by shuffles; rows swept by XCD.
 __global__ void __launch_bounds__(NT) k_mg_restrict(const MgLevelDev* __restrict__ fine,
-                                                    const MgLevelDev* __restrict__ coarse, int ncol, int cw,
-                                                    int tres) {
+                                                    const MgLevelDev* __restrict__ coarse, int ncol, int cw, int G) {
   const MgLevelDev& F = fine[blockIdx.y];
   if (!F.active || (F.done && *F.done)) return;
   const MgLevelDev& C = coarse[blockIdx.y];
   const auto* ptr = gbl(F.r_ptr);
   const auto* col = gbl(F.r_col);
   const auto* val = gbl(F.r_val);
-  const auto* r = gbl((const double*)F.r);
   const auto* t = gbl((const double*)F.t);
-  const auto* rf = gbl(F.rf);
   const auto* tf = gbl((const float*)F.tf);
   const bool f32 = F.f32 != 0;
   auto* y = gblw(C.r);
-  const int lane = threadIdx.x & 63;
-  const int grp = lane / cw, c = lane - grp * cw, ngrp = 64 / cw;
-  const int64_t nrow = C.N;
-  for (int64_t w = ((int64_t)blockIdx.x * NT + threadIdx.x) >> 6; w < nrow; w += ((int64_t)gridDim.x * NT) >> 6) {
+  const int lane = threadIdx.x & (G - 1);
+  const int grp = lane / cw, c = lane - grp * cw, ngrp = G / cw;
+  const XcdSweep sw = xcd_sweep(C.N, NT / G);
+  for (int64_t w = sw.start + threadIdx.x / G; w < sw.end; w += sw.step) {
     double s = 0.0;
     if (c < ncol) {
       const int beg = ptr[w] + grp, end = ptr[w + 1];
-      if (end > beg) {
-        if (tres)
-          s = f32 ? row_gather_dot<false>(col, val, beg, end, ngrp, tf, tf, ncol, c)
-                  : row_gather_dot<false>(col, val, beg, end, ngrp, t, t, ncol, c);
-        else
-          s = f32 ? row_gather_dot<true>(col, val, beg, end, ngrp, rf, tf, ncol, c)
-                  : row_gather_dot<true>(col, val, beg, end, ngrp, r, t, ncol, c);
-      }
+      if (end > beg)
+        s = f32 ? row_gather_dot<false>(col, val, beg, end, ngrp, tf, tf, ncol, c)
+                : row_gather_dot<false>(col, val, beg, end, ngrp, t, t, ncol, c);
     }
-    for (int off = 32; off >= cw; off >>= 1) s += __shfl_xor(s, off, 64);
+    for (int off = G / 2; off >= cw; off >>= 1) s += __shfl_xor(s, off, 64);
     if (grp == 0 && c < ncol) y[w * ncol + c] = s;
   }
 }
 
 // The restriction with V columns per lane (ncol a multiple of V, cw a power
 // of two >= ncol / V lanes per group): 64 / cw groups split a row's entries,
-// each with eight entries in flight, and the coarse rows are swept by XCD.
-// TRES as tres of k_mg_restrict.
-template <int V, bool TRES>
+// each with eight entries in flight.
+template <int V>
 __global__ void __launch_bounds__(NT) k_mg_restrict_v(const MgLevelDev* __restrict__ fine,
                                                       const MgLevelDev* __restrict__ coarse, int ncol, int cw) {
   const MgLevelDev& F = fine[blockIdx.y];
@@ -166,9 +157,7 @@ __global__ void __launch_bounds__(NT) k_mg_restrict_v(const MgLevelDev* __restri
   const auto* ptr = gbl(F.r_ptr);
   const auto* col = gbl(F.r_col);
   const auto* val = gbl(F.r_val);
-  const auto* r = gbl((const double*)F.r);
   const auto* t = gbl((const double*)F.t);
-  const auto* rf = gbl(F.rf);
   const auto* tf = gbl((const float*)F.tf);
   const bool f32 = F.f32 != 0;
   auto* y = gblw(C.r);
@@ -182,13 +171,8 @@ __global__ void __launch_bounds__(NT) k_mg_restrict_v(const MgLevelDev* __restri
     for (int v = 0; v < V; ++v) s[v] = 0.0;
     const int beg = ptr[w] + grp, end = ptr[w + 1];
     if (act && end > beg) {
-      if constexpr (TRES) {
-        if (f32) row_gather_v<V, false>(col, val, beg, end, ngrp, tf, tf, ncol, c0, s);
-        else row_gather_v<V, false>(col, val, beg, end, ngrp, t, t, ncol, c0, s);
-      } else {
-        if (f32) row_gather_v<V, true>(col, val, beg, end, ngrp, rf, tf, ncol, c0, s);
-        else row_gather_v<V, true>(col, val, beg, end, ngrp, r, t, ncol, c0, s);
-      }
+      if (f32) row_gather_v<V, false>(col, val, beg, end, ngrp, tf, tf, ncol, c0, s);
+      else row_gather_v<V, false>(col, val, beg, end, ngrp, t, t, ncol, c0, s);
     }
     for (int off = 32; off >= cw; off >>= 1)
 #pragma unroll
@@ -335,94 +319,98 @@ __global__ void __launch_bounds__(64 * MC_W) k_mg_coarse(const MgLevelDev* __res
 static dim3 level_grid(int64_t n, int ncol, int ni) { return dim3(nblocks(n * ncol, NT, 16384), ni); }
 
 // Coarse-level passes with the operator product fused in, LN lanes per row
-// and V adjacent columns per lane (16-byte loads for V = 4):
-//  - MODE 0, one Chebyshev smoothing step k (the recurrence of k_mg_cheb):
-//    res = r - A zin (res = r for the first step from zero), d = c1 d +
-//    c2 D^-1 res, zout = zin + d (zout = d for the first step from zero).
-//    The smoothing has degree 2 (k = 0, 1): d is stored only by step 0 from
-//    a nonzero z; from zero, step 1 takes d from its zin, which step 0 wrote.
-//    zin and zout are the level's z and t arrays (into_t: z -> t, else
-//    t -> z), so the rows gathered from zin are never the rows written.
-//  - MODE 1, the residual t = r - A z that the restriction reads.
+// and V adjacent columns per lane (16-byte loads for V = 4).  The smoothing is
+// Chebyshev of degree 2 (zin and zout are the level's z and t arrays, so the
+// rows gathered are never the rows written):
+//  - LP_ZERO, both steps from zero: the first step's c0 D^-1 r is formed in the
+//    product (a_vd holds the values times D^-1 of their columns), r -> z;
+//  - LP_STEP0, LP_STEP1, the two steps on a given correction: z -> t with d kept,
+//    then t -> z;
+//  - LP_RES, the residual t = r - A z that the restriction reads.
+// Bound by the gathers (13 rows of 512 B per row at 64 columns, out of L2) on
+// large levels, by the index -> gather chain of the longest rows on small ones.
+// Per cycle, five passes before -> four: Q2 level of H2O (429,000 rows x 64
+// columns) 1607 -> 1428 us, of H2 (18,700 x 4) 50.5 -> 28.9 us.  Rows swept in
+// one range per XCD: 1442 us, and 54.9 us at H2 (long rows lie together).
+enum { LP_ZERO = 0, LP_STEP0 = 1, LP_STEP1 = 2, LP_RES = 3 };
 template <int MODE, int V, int LN>
-__global__ void __launch_bounds__(NT) k_mg_level_pass(const MgLevelDev* __restrict__ lv, int ncol, int k,
-                                                      int from_zero, int into_t) {
+__global__ void __launch_bounds__(NT) k_mg_level_pass(const MgLevelDev* __restrict__ lv, int ncol, int cw) {
   const MgLevelDev& L = lv[blockIdx.y];
   if (!L.active || (L.done && *L.done)) return;
   const double b = L.lmax, a = L.lmax / MG_RANGE;
   const double theta = 0.5 * (b + a), delta = 0.5 * (b - a), sigma = theta / delta;
-  double c1 = 0.0, c2 = 1.0 / theta;
-  double rho = 1.0 / sigma;
-  for (int j = 1; j <= k; ++j) {
-    const double rn = 1.0 / (2.0 * sigma - rho);
-    c1 = rn * rho;
-    c2 = 2.0 * rn / delta;
-    rho = rn;
-  }
-  const bool first = MODE == 0 && from_zero && k == 0;
+  const double c0 = 1.0 / theta, rn = 1.0 / (2.0 * sigma - 1.0 / sigma);
+  const double c1 = rn / sigma, c2 = 2.0 * rn / delta;
   const auto* ptr = gbl(L.a_ptr);
   const auto* col = gbl(L.a_col);
-  const auto* val = gbl(L.a_val);
+  const auto* val = gbl(MODE == LP_ZERO ? L.a_vd : L.a_val);
   const auto* dinv = gbl(L.dinv);
   const auto* r = gbl((const double*)L.r);
-  const auto* zin = gbl((const double*)(MODE == 1 || into_t ? L.z : L.t));
-  auto* zout = gblw(MODE == 1 || into_t ? L.t : L.z);
+  const auto* x = gbl((const double*)(MODE == LP_ZERO ? L.r : (MODE == LP_STEP1 ? L.t : L.z)));
+  auto* zout = gblw(MODE == LP_STEP0 || MODE == LP_RES ? L.t : L.z);
   auto* dd = gblw(L.d);
-  const int c0 = (int)(threadIdx.x % LN) * V;
-  const bool act = c0 < ncol;
-  for (int64_t i = ((int64_t)blockIdx.x * NT + threadIdx.x) / LN; i < L.N; i += (int64_t)gridDim.x * NT / LN) {
-    if (!act) continue;
-    double y[V];
+  // groups of cw lanes split the row's entries (V = 1; V = 4: one group)
+  const int lane = (int)(threadIdx.x % LN);
+  const int grp = V > 1 ? 0 : lane / cw, ngrp = V > 1 ? 1 : LN / cw;
+  const int col0 = (V > 1 ? lane : lane - grp * cw) * V;
+  const bool act = col0 < ncol;
+  for (int64_t i = (int64_t)blockIdx.x * (NT / LN) + threadIdx.x / LN; i < L.N; i += (int64_t)gridDim.x * (NT / LN)) {
+    double y[V], rv[V], xv[V], dv[V], di = 0.0;
 #pragma unroll
     for (int v = 0; v < V; ++v) y[v] = 0.0;
-    if (!first) {
-      const int beg = ptr[i], end = ptr[i + 1];
-      if (end > beg) row_gather_v<V, false>(col, val, beg, end, 1, zin, zin, ncol, c0, y);
+    const int64_t e = i * ncol + col0;
+    if (act) {
+      load_vals<V>(r + e, rv);
+      if constexpr (MODE == LP_STEP0 || MODE == LP_STEP1) load_vals<V>(x + e, xv);
+      if constexpr (MODE == LP_STEP1) load_vals<V>((const __attribute__((address_space(1))) double*)dd + e, dv);
+      if (MODE != LP_RES) di = dinv[i];
+      const int beg = ptr[i] + grp, end = ptr[i + 1];
+      if (end > beg) row_gather_v<V, false>(col, val, beg, end, ngrp, x, x, ncol, col0, y);
     }
-    const int64_t e = i * ncol + c0;
-    double rv[V];
-    load_vals<V>(r + e, rv);
-    if constexpr (MODE == 1) {
+    if constexpr (V == 1)
+      for (int off = LN / 2; off >= cw; off >>= 1) y[0] += __shfl_xor(y[0], off, 64);
+    if (!act || grp > 0) continue;
 #pragma unroll
-      for (int v = 0; v < V; ++v) zout[e + v] = rv[v] - y[v];
-    } else {
-      const double di = dinv[i];
-      double dv[V], zv[V];
-      if (!first) load_vals<V>(zin + e, zv);
-      if (k > 0) {
-        if (from_zero) {  // the first step's d is its zout, this step's zin
-#pragma unroll
-          for (int v = 0; v < V; ++v) dv[v] = zv[v];
-        } else {
-          load_vals<V>(dd + e, dv);
-        }
-      }
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const double dn = (k > 0 ? c1 * dv[v] : 0.0) + c2 * di * (rv[v] - y[v]);
-        if (k == 0 && !from_zero) dd[e + v] = dn;   // the only d a later step reads
-        zout[e + v] = first ? dn : zv[v] + dn;
+    for (int v = 0; v < V; ++v) {
+      if constexpr (MODE == LP_RES) {
+        zout[e + v] = rv[v] - y[v];
+      } else if constexpr (MODE == LP_ZERO) {
+        const double z0 = c0 * di * rv[v];
+        zout[e + v] = z0 + (c1 * z0 + c2 * di * (rv[v] - c0 * y[v]));
+      } else if constexpr (MODE == LP_STEP0) {
+        const double dn = c0 * di * (rv[v] - y[v]);
+        dd[e + v] = dn;
+        zout[e + v] = xv[v] + dn;
+      } else {
+        zout[e + v] = xv[v] + (c1 * dv[v] + c2 * di * (rv[v] - y[v]));
       }
     }
   }
 }
 
 template <int MODE>
-static void coarse_pass(const MgDev& mg, int l, int ni, int ncol, int k, int from_zero, int into_t, hipStream_t s) {
+static void coarse_pass(const MgDev& mg, int l, int ni, int ncol, hipStream_t s) {
+  int cw = 1;
+  while (cw < ncol) cw *= 2;
   auto go = [&](auto kern, int ln) {
-    hipLaunchKernelGGL(kern, dim3(nblocks(mg.max_n[l] * ln, NT, 16384), ni), dim3(NT), 0, s, mg.lv[l], ncol, k,
-                       from_zero, into_t);
+    hipLaunchKernelGGL(kern, dim3(nblocks(mg.max_n[l] * ln, NT, 16384), ni), dim3(NT), 0, s, mg.lv[l], ncol, cw);
   };
+  // Few columns: four lane groups share a row's entries where one lane per entry
+  // and column leaves the chip idle (2^20 lanes: four waves' worth of every SIMD's
+  // slots), since the longest rows, beside hanging nodes, then set the time.
+  // Measured, one group -> four: 18,700 rows x 4 columns 10.1 -> 7.2 us a pass,
+  // 16 x 34,000 rows x 4 columns 57 -> 72 us.
+  const bool few = mg.max_n[l] * ni * cw < (int64_t)1 << 20;
   if (ncol >= 16 && ncol % 4 == 0) {
     if (ncol > 32) go(k_mg_level_pass<MODE, 4, 16>, 16);
     else if (ncol > 16) go(k_mg_level_pass<MODE, 4, 8>, 8);
     else go(k_mg_level_pass<MODE, 4, 4>, 4);
-  } else if (ncol <= 1) go(k_mg_level_pass<MODE, 1, 1>, 1);
-  else if (ncol <= 2) go(k_mg_level_pass<MODE, 1, 2>, 2);
-  else if (ncol <= 4) go(k_mg_level_pass<MODE, 1, 4>, 4);
-  else if (ncol <= 8) go(k_mg_level_pass<MODE, 1, 8>, 8);
-  else if (ncol <= 16) go(k_mg_level_pass<MODE, 1, 16>, 16);
-  else if (ncol <= 32) go(k_mg_level_pass<MODE, 1, 32>, 32);
+  } else if (cw == 1) few ? go(k_mg_level_pass<MODE, 1, 4>, 4) : go(k_mg_level_pass<MODE, 1, 1>, 1);
+  else if (cw == 2) few ? go(k_mg_level_pass<MODE, 1, 8>, 8) : go(k_mg_level_pass<MODE, 1, 2>, 2);
+  else if (cw == 4) few ? go(k_mg_level_pass<MODE, 1, 16>, 16) : go(k_mg_level_pass<MODE, 1, 4>, 4);
+  else if (cw == 8) few ? go(k_mg_level_pass<MODE, 1, 32>, 32) : go(k_mg_level_pass<MODE, 1, 8>, 8);
+  else if (cw == 16) few ? go(k_mg_level_pass<MODE, 1, 64>, 64) : go(k_mg_level_pass<MODE, 1, 16>, 16);
+  else if (cw == 32) go(k_mg_level_pass<MODE, 1, 32>, 32);
   else go(k_mg_level_pass<MODE, 1, 64>, 64);
 }
 
@@ -436,10 +424,130 @@ static void smooth(const MgDev& mg, int l, int ni, int ncol, bool from_zero, con
     }
     return;
   }
-  // coarser levels: Chebyshev degree 2 with the products fused into the
-  // steps; the first step writes t, the second brings the correction back to z
-  coarse_pass<0>(mg, l, ni, ncol, 0, from_zero ? 1 : 0, 1, s);
-  coarse_pass<0>(mg, l, ni, ncol, 1, from_zero ? 1 : 0, 0, s);
+  if (from_zero) {
+    coarse_pass<LP_ZERO>(mg, l, ni, ncol, s);
+  } else {
+    coarse_pass<LP_STEP0>(mg, l, ni, ncol, s);
+    coarse_pass<LP_STEP1>(mg, l, ni, ncol, s);
+  }
+}
+
+// Hanging rows of a level's correction (z rows N .. N + Nh), so that the cells of
+// the finer level read every coarse node's value directly.
+__global__ void __launch_bounds__(NT) k_mg_fill(const MgLevelDev* __restrict__ lv, int ncol) {
+  const MgLevelDev& L = lv[blockIdx.y];
+  if (L.done && *L.done) return;
+  const int64_t total = L.Nh * ncol;
+  const auto* ptr = gbl(L.h_ptr);
+  const auto* z = gbl((const double*)L.z);
+  for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
+    const int64_t h = e / ncol;
+    const int c = (int)(e - h * ncol), beg = ptr[h], end = ptr[h + 1];
+    gblw(L.z)[L.N * ncol + e] = end > beg ? row_gather_dot<false>(gbl(L.h_col), gbl(L.h_w), beg, end, 1, z, z, ncol, c) : 0.0;
+  }
+}
+
+// fine.z += P coarse.z where the two levels lie on the same leaves, PF and PC
+// nodes per edge: a cell interpolates its PC^3 coarse nodes along z, y and x
+// (B[a][b]: coarse basis function b at fine node a) and adds to the fine DoFs it
+// is named for.  Row by row every fine node gathers up to PC^3 coarse rows, 12.7
+// on average from Q2 to Q3; here a cell reads PC^3 rows for its share of the fine
+// nodes (27 for 27).  Bound by the chain index -> row -> store, so a plane's rows
+// are requested together; a thread takes a column of a cell, or (SPLIT) of one of
+// its planes.  Rows -> cells, Q2 to
+// Q3 and Q1 to Q2 together: H2O (1.5 M and 429,000 fine rows x 64 columns) 1333 ->
+// 882 us (by planes 1066), 16 H2 (4 columns) 136 -> 68 us by planes (85 by cells).
+struct InterpTable {
+  double B[12];
+};
+template <int PF, int PC, bool SPLIT>
+__global__ void __launch_bounds__(NT) k_mg_prolong_cells(const MgLevelDev* __restrict__ fine,
+                                                         const MgLevelDev* __restrict__ coarse, int ncol,
+                                                         InterpTable tab) {
+  const MgLevelDev& F = fine[blockIdx.y];
+  if (!F.active || (F.done && *F.done)) return;
+  const auto* x = gbl((const double*)coarse[blockIdx.y].z);
+  const auto* cf = gbl(F.cell_f);
+  const auto* cc = gbl(F.cell_c);
+  auto* z = gblw(F.z);
+  auto* zf = gblw(F.zf);
+  const bool f32 = F.f32 != 0;
+  constexpr int PF3 = PF * PF * PF, PC3 = PC * PC * PC, NP = SPLIT ? PF : 1;
+  const int total = (int)F.nC * NP, per = NT / ncol;   // ncol consecutive threads take a cell (plane)
+  const int g = (int)threadIdx.x / ncol, c = (int)threadIdx.x - g * ncol;
+  if (g >= per) return;
+  const XcdSweep sw = xcd_sweep(total, per);
+  for (int w = (int)sw.start + g; w < (int)sw.end; w += (int)sw.step) {
+    const int64_t e = w / NP;
+    const int plane = w - (int)e * NP;
+    double u[PC3];
+#pragma unroll
+    for (int k = 0; k < PC3; ++k) {
+      const int j = cc[e * PC3 + k];
+      const double v = x[(int64_t)(j < 0 ? 0 : j) * ncol + c];
+      u[k] = j < 0 ? 0.0 : v;
+    }
+#pragma unroll
+    for (int q = 0; q < (SPLIT ? 1 : PF); ++q) {
+      const int fz = SPLIT ? plane : q;
+      int f[PF * PF];
+#pragma unroll
+      for (int k = 0; k < PF * PF; ++k) f[k] = cf[e * PF3 + fz * PF * PF + k];
+      double zo[PF * PF], wz[PC * PC];
+#pragma unroll
+      for (int k = 0; k < PF * PF; ++k) {
+        const int64_t o = (int64_t)(f[k] < 0 ? 0 : f[k]) * ncol + c;
+        zo[k] = f32 ? (double)zf[o] : z[o];
+      }
+#pragma unroll
+      for (int k = 0; k < PC * PC; ++k) {
+        double t = 0.0;
+#pragma unroll
+        for (int m = 0; m < PC; ++m) t += tab.B[fz * PC + m] * u[m * PC * PC + k];
+        wz[k] = t;
+      }
+#pragma unroll
+      for (int fy = 0; fy < PF; ++fy) {
+        double wy[PC];
+#pragma unroll
+        for (int k = 0; k < PC; ++k) {
+          double t = 0.0;
+#pragma unroll
+          for (int m = 0; m < PC; ++m) t += tab.B[fy * PC + m] * wz[m * PC + k];
+          wy[k] = t;
+        }
+#pragma unroll
+        for (int fx = 0; fx < PF; ++fx) {
+          double t = zo[fy * PF + fx];
+#pragma unroll
+          for (int m = 0; m < PC; ++m) t += tab.B[fx * PC + m] * wy[m];
+          if (f[fy * PF + fx] >= 0) {
+            const int64_t o = (int64_t)f[fy * PF + fx] * ncol + c;
+            if (f32) zf[o] = (float)t;
+            else z[o] = t;
+          }
+        }
+      }
+    }
+  }
+}
+
+static void prolong_cells(const MgDev& mg, int l, int ni, int ncol, hipStream_t s) {
+  const int pf = mg.cell_pf[l], pc = mg.cell_pc[l];
+  if (mg.max_hang[l + 1] > 0)
+    hipLaunchKernelGGL(k_mg_fill, dim3(nblocks(mg.max_hang[l + 1] * ncol, NT, 16384), ni), dim3(NT), 0, s, mg.lv[l + 1],
+                       ncol);
+  InterpTable tab{};
+  for (int a = 0; a < pf; ++a)
+    for (int b = 0; b < pc; ++b) tab.B[a * pc + b] = mg.interp[l][a * pc + b];
+  // a thread per plane where the cells alone leave the chip idle (below 2^19 lanes)
+  const bool split = mg.max_cells[l] * ncol * ni < (int64_t)1 << 19;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(mg.max_cells[l] * (split ? pf : 1), NT / ncol, 65536), ni), dim3(NT), 0, s,
+                       mg.lv[l], mg.lv[l + 1], ncol, tab);
+  };
+  if (pf == 4) split ? go(k_mg_prolong_cells<4, 3, true>) : go(k_mg_prolong_cells<4, 3, false>);
+  else split ? go(k_mg_prolong_cells<3, 2, true>) : go(k_mg_prolong_cells<3, 2, false>);
 }
 
 void mg_vcycle(const MgDev& mg, int ni, int ncol, const MgLevel0Ops& ops, hipStream_t s) {
@@ -453,20 +561,21 @@ void mg_vcycle(const MgDev& mg, int ni, int ncol, const MgLevel0Ops& ops, hipStr
     smooth(mg, l, ni, ncol, true, ops, s);
     // the residual r - A z that the restriction reads: the level-0 residual
     // pass, or the coarse level's fused pass
-    const int tres = 1;
-    if (l > 0) coarse_pass<1>(mg, l, ni, ncol, 0, 0, 1, s);
+    if (l > 0) coarse_pass<LP_RES>(mg, l, ni, ncol, s);
     else ops.resid(s);
     if (wide) {
       int cw = 1;
       while (cw * 4 < ncol) cw *= 2;
       const dim3 g(xcd_grid(mg.max_n[l + 1], NT / 64, 16384), ni);
-      if (tres) hipLaunchKernelGGL((k_mg_restrict_v<4, true>), g, dim3(NT), 0, s, mg.lv[l], mg.lv[l + 1], ncol, cw);
-      else hipLaunchKernelGGL((k_mg_restrict_v<4, false>), g, dim3(NT), 0, s, mg.lv[l], mg.lv[l + 1], ncol, cw);
+      hipLaunchKernelGGL(k_mg_restrict_v<4>, g, dim3(NT), 0, s, mg.lv[l], mg.lv[l + 1], ncol, cw);
     } else {
       int cw = 1;
       while (cw < ncol) cw *= 2;
-      hipLaunchKernelGGL(k_mg_restrict, dim3(nblocks(mg.max_n[l + 1] * 64, NT, 16384), ni), dim3(NT), 0, s,
-                         mg.lv[l], mg.lv[l + 1], ncol, cw, tres);
+      // lanes per row: four groups of them share its entries where the rows alone
+      // fill the chip (at least 16 lanes), else the whole wave
+      const int G = mg.max_n[l + 1] * ni >= 8192 ? std::min(64, std::max(16, 4 * cw)) : 64;
+      hipLaunchKernelGGL(k_mg_restrict, dim3(xcd_grid(mg.max_n[l + 1], NT / G, 16384), ni), dim3(NT), 0, s, mg.lv[l],
+                         mg.lv[l + 1], ncol, cw, G);
     }
   }
   {
@@ -478,7 +587,9 @@ void mg_vcycle(const MgDev& mg, int ni, int ncol, const MgLevel0Ops& ops, hipStr
     else go(k_mg_coarse<4>);
   }
   for (int l = nl - 2; l >= 0; --l) {
-    if (wide_p && ncol > 32)
+    if (mg.cell_pf[l])
+      prolong_cells(mg, l, ni, ncol, s);
+    else if (wide_p && ncol > 32)
       hipLaunchKernelGGL((k_mg_prolong_v<4, 16>), dim3(xcd_grid(mg.max_n[l], NT / 16, 16384), ni), dim3(NT), 0, s,
                          mg.lv[l], mg.lv[l + 1], ncol);
     else if (wide_p && ncol > 16)

@@ -23,12 +23,20 @@ struct MgLevelDev {
   int active = 0, coarse = 0;
   const int32_t* a_ptr = nullptr; const int32_t* a_col = nullptr;   // operator (CSR)
   const double* a_val = nullptr;
+  const double* a_vd = nullptr;                                    // levels from 1 on: values times 1 / diagonal of the column
   const double* dinv = nullptr;                                    // 1 / diagonal
   double lmax = 0.0;                                               // bound of the spectrum of D^-1 A
   const int32_t* p_ptr = nullptr; const int32_t* p_col = nullptr;   // prolongation from level + 1 (rows N)
   const double* p_val = nullptr;
   const int32_t* r_ptr = nullptr; const int32_t* r_col = nullptr;   // restriction to level + 1 (its rows)
   const double* r_val = nullptr;
+  // prolongation from level + 1 cell by cell (where that level lies on the same
+  // leaves, MgDev::cell_pf): the fine DoFs each cell writes, the coarse rows of
+  // its nodes; this level's hanging rows (z holds them after its N rows)
+  int64_t nC = 0, Nh = 0;
+  const int32_t* cell_f = nullptr; const int32_t* cell_c = nullptr;
+  const int32_t* h_ptr = nullptr; const int32_t* h_col = nullptr;
+  const double* h_w = nullptr;
   const double* cinv = nullptr;                                    // dense inverse (coarse levels)
   double* r = nullptr;   // right-hand side [N][ncol] (level 0: the batch residual at this instance)
   double* z = nullptr;   // correction
@@ -53,6 +61,9 @@ struct MgDev {
   MgLevelDev* coarse = nullptr;
   int64_t max_n[32] = {};   // largest N of each level over the instances (grid shapes)
   int64_t max_coarse = 0;
+  int cell_pf[32] = {}, cell_pc[32] = {};   // level l: nodes per edge of it and of level l + 1 (0: prolongation by rows)
+  int64_t max_cells[32] = {}, max_hang[32] = {};
+  double interp[32][12] = {};               // and the 1D interpolation between them, [fine node][coarse node]
   double* z0 = nullptr;
   double* z0b = nullptr;    // second level-0 correction array (the fused smoothing steps alternate)
   double* t0 = nullptr;

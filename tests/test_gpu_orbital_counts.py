@@ -35,6 +35,33 @@ def orbitals(P, n, seed):
     return orthonormalize(P.ops, random_orbitals(P.om.xyz[P.om.dof_nodes], n, seed, n_gauss=10, spread=1.5))
 
 
+@pytest.mark.parametrize("sched", [21, 85])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("name", ["tiny_q3", "tiny_q2", "uniform_q2"])
+def test_multigrid_degree_levels(name, n, sched):
+    """Hierarchies whose first levels lie on the same leaves (Q3 - Q2 - Q1, with
+    and without hanging nodes): transfers cell by cell, lane groups of the
+    coarse passes at every column count, the finest corrections in double and in
+    float.  A wrong transfer or smoothing step costs iterations, not accuracy, so
+    those are held as well: the cycle gains a digit an iteration, 13 are asked
+    for, twice as many are allowed."""
+    import torch
+    P = pair(name)
+    op = operator(P, n)
+    op.tune(1, sched, 8192)
+    c = orbitals(P, n, 60 + n)
+    W = torch.zeros((P.NF, n * n), dtype=torch.float64, device="cuda")
+    it, rc = op.poisson_pairs(dev(P.to_lib_orb(c)), W)
+    torch.cuda.synchronize()
+    assert rc == 0 and it <= 26
+    got, ref = P.W_from_lib(W.cpu().numpy(), n), poisson_solver(P.ops).pair_potentials(c)
+    m = P.ops.m
+    for k in ref:
+        scale = np.sqrt(np.sum(m * np.abs(ref[k]) ** 2))
+        assert np.sqrt(np.sum(m * np.abs(got[k] - ref[k]) ** 2)) <= 1e-10 * scale
+        assert np.abs(got[k] - ref[k]).max() <= 1e-10 * np.abs(ref[k]).max()
+
+
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("name", ["uniform_q1_odd", "tiny_q1"])
 def test_multigrid_column_tiles(name, n):
@@ -56,6 +83,27 @@ def test_multigrid_column_tiles(name, n):
         scale = np.sqrt(np.sum(m * np.abs(ref[k]) ** 2))
         assert np.sqrt(np.sum(m * np.abs(got[k] - ref[k]) ** 2)) <= 1e-10 * scale
         assert np.abs(got[k] - ref[k]).max() <= 1e-10 * np.abs(ref[k]).max()
+
+
+def test_multigrid_cells_wide():
+    """41 equal instances at 8 orbitals (535,000 cell columns): the cell-by-cell
+    prolongation with a whole cell per thread; each against the oracle."""
+    import paper_2301_02387_amd as mh
+    import torch
+    P, n, copies = pair("tiny_q3"), 8, 41
+    op = mh.Operator.batch([P.mesh] * copies, [P.w["nuclei"]] * copies, n, 4, 4, poisson_rtol=1e-13,
+                           poisson_maxit=20000)
+    op.tune(1, 21, 8192)
+    c = orbitals(P, n, 75)
+    W = torch.zeros((P.NF * copies, n * n), dtype=torch.float64, device="cuda")
+    it, rc = op.poisson_pairs(dev(np.concatenate([P.to_lib_orb(c)] * copies)), W)
+    torch.cuda.synchronize()
+    assert rc == 0 and it <= 26
+    ref = poisson_solver(P.ops).pair_potentials(c)
+    for part in np.split(W.cpu().numpy(), copies):
+        got = P.W_from_lib(part, n)
+        for k in ref:
+            assert np.abs(got[k] - ref[k]).max() <= 1e-10 * np.abs(ref[k]).max()
 
 
 def frozen(P, op, n, seed, E=0.013, copies=1):
