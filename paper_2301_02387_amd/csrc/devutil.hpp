@@ -1,5 +1,6 @@
 // Device helpers shared by the kernel translation units (wave64, 256 threads).
 #pragma once
+#include <type_traits>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -223,6 +224,72 @@ __device__ inline void solid_regular_m(double x, double y, double z, int lmax, i
     R[l * l + m] = re;
     if (m > 0) R[l * l + l + m] = im;
   }
+}
+
+// One sparse row applied to orbital rows [.][n] of x by LR lanes: NP
+// lanes (n rounded up to a power of two) hold one orbital each, so that an entry
+// gathers its row of x in one coalesced access, and LR / NP groups share
+// the row's entries, U of each in flight.  The indices of the next round are
+// requested before this round's gathers; entries past the end repeat the last
+// one with coefficient 0.  Columns from `limit` on count as zero rows.
+// Returns the (complex) sum of this lane's orbital, equal in every group.
+template <int NP, int LR, int U>
+__device__ __forceinline__ double2 orb_row(const int32_t* colp, const double* valp, int beg, int end, int limit,
+                                           const double2* x, int n) {
+  constexpr int G = LR / NP;
+  const auto* col = gbl(colp);
+  const auto* val = gbl(valp);
+  const int lane = (int)(threadIdx.x & (LR - 1)), p = lane & (NP - 1), g = lane / NP;
+  double sx = 0.0, sy = 0.0;
+  if (end > beg && p < n) {
+    int jn[U];
+    double an[U];
+#pragma unroll
+    for (int h = 0; h < U; ++h) {
+      const int t = beg + g + h * G, tc = t < end ? t : end - 1;
+      jn[h] = col[tc];
+      an[h] = t < end ? val[tc] : 0.0;
+    }
+    for (int t0 = beg; t0 < end; t0 += U * G) {
+      int j[U];
+      double a[U];
+#pragma unroll
+      for (int h = 0; h < U; ++h) {
+        a[h] = jn[h] < limit ? an[h] : 0.0;
+        j[h] = jn[h] < limit ? jn[h] : 0;
+      }
+      if (t0 + U * G < end) {
+#pragma unroll
+        for (int h = 0; h < U; ++h) {
+          const int t = t0 + U * G + g + h * G, tc = t < end ? t : end - 1;
+          jn[h] = col[tc];
+          an[h] = t < end ? val[tc] : 0.0;
+        }
+      }
+      double2 v[U];
+#pragma unroll
+      for (int h = 0; h < U; ++h) v[h] = ldg2(x, (int64_t)j[h] * n + p);
+#pragma unroll
+      for (int h = 0; h < U; ++h) {
+        sx += a[h] != 0.0 ? a[h] * v[h].x : 0.0;
+        sy += a[h] != 0.0 ? a[h] * v[h].y : 0.0;
+      }
+    }
+  }
+#pragma unroll
+  for (int off = LR / 2; off >= NP; off >>= 1) {
+    sx += __shfl_xor(sx, off, 64);
+    sy += __shfl_xor(sy, off, 64);
+  }
+  return make_double2(sx, sy);
+}
+// go(NP) with the orbital count rounded up to a power of two
+template <class F>
+static inline void orb_dispatch(int n, F&& go) {
+  if (n <= 1) go(std::integral_constant<int, 1>{});
+  else if (n <= 2) go(std::integral_constant<int, 2>{});
+  else if (n <= 4) go(std::integral_constant<int, 4>{});
+  else go(std::integral_constant<int, 8>{});
 }
 
 static inline int nblocks(int64_t work, int per = NT, int cap = 1 << 20) {

@@ -54,58 +54,46 @@ __global__ void __launch_bounds__(NT) k_cheb_init(const DevMesh* __restrict__ dm
   }
 }
 
-// One row of the interface block per group of CHEB_G lanes: the lanes split
-// the row's entries (tens per row) and combine by shuffles, all n orbitals
-// at once.
-constexpr int CHEB_G = 8;
+// One Chebyshev step on the interface block, a row per four groups of NP lanes (25
+// entries a row at Q3, 9 at Q1).  Bound by the chain row -> index -> gather: the
+// matrix and the vectors (10 and 21 MB at H2O) stay in the caches.  Eight lanes
+// a row, each gathering whole orbital rows (one 16-byte load per lane and
+// orbital, scattered) -> an orbital per lane, a launch: H2O (33,344 rows x 8
+// orbitals) 31.6 -> 17.8 us, its Q1 mesh (12,746 x 8) 10.5 -> 6.2 us, 16 H2
+// (2,382 x 2 each) 11.7 -> 11.0 us (thirty-two lanes a row: 19.0, 7.5, 14.1 us).
+template <int NP>
 __global__ void __launch_bounds__(NT) k_cheb_iter(const DevMesh* __restrict__ dm, double2* __restrict__ x,
                                                   double2* __restrict__ r, const double2* __restrict__ din,
                                                   double2* __restrict__ dout, int k) {
   INSTANCE;
+  constexpr int LR = 4 * NP;
   const int n = d.n;
   if (d.nMa == 0) return;
   const int64_t o = d.oMa * n;
   const double c1 = d.cheb[1 + 2 * k], c2 = d.cheb[2 + 2 * k];
-  const double2* dI = din + o;
-  const int g = (int)(threadIdx.x & (CHEB_G - 1));
+  const int lane = (int)(threadIdx.x & (LR - 1));
+  const auto* mp = gbl(d.ma_ptr);
   // XCD x sweeps the x-th eighth of the (band-ordered) rows, so its gathers
   // stay within that part of the vectors and hit its own L2
-  const XcdSweep sw = xcd_sweep(d.nMa, NT / CHEB_G);
-  for (int64_t i = sw.start + threadIdx.x / CHEB_G; i < sw.end; i += sw.step) {
-    double sx[8], sy[8];
-#pragma unroll
-    for (int p = 0; p < 8; ++p) { sx[p] = 0.0; sy[p] = 0.0; }
-    const auto* mp = gbl(d.ma_ptr);
-    for (int t = mp[i] + g; t < mp[i + 1]; t += CHEB_G) {
-      const double a = gbl(d.ma_val)[t];
-      const double2* row = dI + (int64_t)gbl(d.ma_col)[t] * n;
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-        if (p < n) {
-          const double2 v = row[p];
-          sx[p] += a * v.x;
-          sy[p] += a * v.y;
-        }
+  const XcdSweep sw = xcd_sweep(d.nMa, NT / LR);
+  for (int64_t i = sw.start + threadIdx.x / LR; i < sw.end; i += sw.step) {
+    const int beg = mp[i], end = mp[i + 1];
+    double2 dk = make_double2(0.0, 0.0), xi = dk, ri = dk;
+    double gi = 0.0;
+    const int64_t idx = o + i * n + lane;
+    if (lane < n) {
+      dk = ldg2(din, idx);
+      xi = ldg2((const double2*)x, idx);
+      ri = ldg2((const double2*)r, idx);
+      gi = c2 * gbl(d.ma_dinv)[i];
     }
-#pragma unroll
-    for (int off = CHEB_G / 2; off > 0; off >>= 1)
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-        if (p < n) {
-          sx[p] += __shfl_xor(sx[p], off, CHEB_G);
-          sy[p] += __shfl_xor(sy[p], off, CHEB_G);
-        }
-    const double gi = c2 * gbl(d.ma_dinv)[i];
-#pragma unroll
-    for (int p = 0; p < 8; ++p)
-      if (p < n && p % CHEB_G == g) {
-        const int64_t idx = o + i * n + p;
-        const double2 dk = din[idx];
-        x[idx] = cadd(x[idx], dk);
-        const double2 rn = csub(r[idx], make_double2(sx[p], sy[p]));
-        r[idx] = rn;
-        dout[idx] = make_double2(c1 * dk.x + gi * rn.x, c1 * dk.y + gi * rn.y);
-      }
+    const double2 q = orb_row<NP, LR, 4>(d.ma_col, d.ma_val, beg, end, INT32_MAX, din + o, n);
+    if (lane < n) {
+      const double2 rn = csub(ri, q);
+      x[idx] = cadd(xi, dk);
+      r[idx] = rn;
+      dout[idx] = make_double2(c1 * dk.x + gi * rn.x, c1 * dk.y + gi * rn.y);
+    }
   }
 }
 
@@ -250,10 +238,12 @@ void launch_ma_solve(const Batch& b, const double* ma_b, double* x, double* r, d
                      (double2*)dbuf0);
   double* din = dbuf0;
   double* dout = dbuf1;
-  const dim3 gi(xcd_grid(b.mx.nMa, NT / CHEB_G, 65536), b.ni);
   for (int k = 0; k < b.cheb_iters; ++k) {
-    hipLaunchKernelGGL(k_cheb_iter, gi, dim3(NT), 0, s, b.dm, (double2*)x, (double2*)r, (const double2*)din,
-                       (double2*)dout, k);
+    orb_dispatch(b.mx.n, [&](auto np) {
+      const dim3 gi(xcd_grid(b.mx.nMa, NT / (4 * np.value), 65536), b.ni);
+      hipLaunchKernelGGL(k_cheb_iter<np.value>, gi, dim3(NT), 0, s, b.dm, (double2*)x, (double2*)r,
+                         (const double2*)din, (double2*)dout, k);
+    });
     double* t = din;
     din = dout;
     dout = t;
@@ -263,35 +253,35 @@ void launch_ma_solve(const Batch& b, const double* ma_b, double* x, double* r, d
 }
 
 // Hanging rows: x[h] = sum_k c_hk x[k] over DoF masters (boundary values of
-// orbitals vanish); optionally zero the hanging rows of acc.
+// orbitals vanish); optionally zero the hanging rows of acc.  A row per
+// four groups of NP lanes: the masters (12.6 on average at Q3) are gathered in one round
+// instead of one after the other by a thread per orbital: H2 (9,240 rows x 2
+// orbitals) 9.8 -> 4.7 us, 16 of it 26.8 -> 13.8 us, H2O (129,640 x 8) 31.7 -> 32.4 us.
+template <int NP>
 __global__ void __launch_bounds__(NT) k_fill_orb(const DevMesh* __restrict__ dm, double2* __restrict__ x,
                                                  double2* __restrict__ acc) {
   INSTANCE;
+  constexpr int LR = 4 * NP;
   const int n = d.n;
-  const int64_t total = d.Nh * n, o = d.oE * n;
-  for (int64_t idx = (int64_t)blockIdx.x * NT + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * NT) {
-    const int64_t h = idx / n;
-    const int p = (int)(idx - h * n);
-    double2 s = make_double2(0.0, 0.0);
-    const auto* hp = gbl(d.hang_ptr);
-    for (int t = hp[h]; t < hp[h + 1]; ++t) {
-      int col = gbl(d.hang_col)[t];
-      if (col < d.N) {
-        const double w = gbl(d.hang_w)[t];
-        double2 v = x[o + (int64_t)col * n + p];
-        s.x += w * v.x;
-        s.y += w * v.y;
-      }
+  const int64_t o = d.oE * n;
+  const int lane = (int)(threadIdx.x & (LR - 1));
+  const auto* hp = gbl(d.hang_ptr);
+  const XcdSweep sw = xcd_sweep(d.Nh, NT / LR);
+  for (int64_t h = sw.start + threadIdx.x / LR; h < sw.end; h += sw.step) {
+    const double2 s = orb_row<NP, LR, 4>(d.hang_col, d.hang_w, hp[h], hp[h + 1], (int)d.N, x + o, n);
+    if (lane < n) {
+      x[o + (d.N + h) * n + lane] = s;
+      if (acc) acc[o + (d.N + h) * n + lane] = make_double2(0.0, 0.0);
     }
-    x[o + (d.N + h) * n + p] = s;
-    if (acc) acc[o + (d.N + h) * n + p] = make_double2(0.0, 0.0);
   }
 }
 
 void launch_fill_orb(const Batch& b, double* x, double* acc, hipStream_t s) {
   if (b.mx.Nh == 0) return;
-  hipLaunchKernelGGL(k_fill_orb, dim3(nblocks(b.mx.Nh * b.mx.n), b.ni), dim3(NT), 0, s, b.dm, (double2*)x,
-                     (double2*)acc);
+  orb_dispatch(b.mx.n, [&](auto np) {
+    hipLaunchKernelGGL(k_fill_orb<np.value>, dim3(xcd_grid(b.mx.Nh, NT / (4 * np.value), 65536), b.ni), dim3(NT), 0, s, b.dm,
+                       (double2*)x, (double2*)acc);
+  });
 }
 
 __global__ void k_copy(const double* __restrict__ in, double* __restrict__ out, int64_t nd) {

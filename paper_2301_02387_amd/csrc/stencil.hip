@@ -249,59 +249,31 @@ __global__ void __launch_bounds__(NT) k_stencil_orb(const DevMesh* __restrict__ 
   }
 }
 
-// Masters: load value = acc_k + sum_h c_hk acc_h (transposed constraints).
-// One master per group of GATHER_G lanes splitting its hanging rows (about
-// fifty), combined by shuffles; all n orbitals at once.
-constexpr int GATHER_G = 16;
+// Masters: load value = acc_k + sum_h c_hk acc_h (transposed constraints), a
+// master per 32 lanes (49 hanging rows on average at Q3, 180 at most; 8
+// at Q1).  Sixteen lanes gathering whole orbital rows -> an orbital per lane:
+// H2 (2,382 masters x 2 orbitals) 10.8 -> 4.8 us, 16 of it 26.6 -> 18.6 us, H2O
+// (33,344 x 8) 60.9 -> 34.1 us.
+template <int NP>
 __global__ void __launch_bounds__(NT) k_ma_gather_orb(const DevMesh* __restrict__ dm, const double2* __restrict__ acc,
                                                       int mode, double2* __restrict__ out,
                                                       double2* __restrict__ ma_b) {
   INSTANCE;
+  constexpr int LR = 32;
   const int n = d.n;
   const int64_t o = d.oE * n, om = d.oMa * n;
-  const int g = (int)(threadIdx.x & (GATHER_G - 1));
-  const int64_t groups = (int64_t)gridDim.x * (NT / GATHER_G);
-  for (int64_t i = ((int64_t)blockIdx.x * NT + threadIdx.x) / GATHER_G; i < d.nMa; i += groups) {
+  const int lane = (int)(threadIdx.x & (LR - 1));
+  const auto* ctp = gbl(d.ct_ptr);
+  const XcdSweep sw = xcd_sweep(d.nMa, NT / LR);
+  for (int64_t i = sw.start + threadIdx.x / LR; i < sw.end; i += sw.step) {
     const int64_t k = gbl(d.ma_dof)[i];
-    double fx[8], fy[8];
-#pragma unroll
-    for (int p = 0; p < 8; ++p) { fx[p] = 0.0; fy[p] = 0.0; }
-    if (g == 0) {
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-        if (p < n) {
-          const double2 a = acc[o + k * n + p];
-          fx[p] = a.x;
-          fy[p] = a.y;
-        }
+    double2 f = make_double2(0.0, 0.0);
+    if (lane < n) f = ldg2(acc, o + k * n + lane);
+    f = cadd(f, orb_row<NP, LR, NP == 8 ? 8 : 4>(d.ct_row, d.ct_w, ctp[i], ctp[i + 1], INT32_MAX, acc + o, n));
+    if (lane < n) {
+      if (mode == 0) out[o + k * n + lane] = f;
+      else ma_b[om + i * n + lane] = f;
     }
-    const auto* ctp = gbl(d.ct_ptr);
-    for (int t = ctp[i] + g; t < ctp[i + 1]; t += GATHER_G) {
-      const double w = gbl(d.ct_w)[t];
-      const double2* row = acc + o + (int64_t)gbl(d.ct_row)[t] * n;
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-        if (p < n) {
-          const double2 a = row[p];
-          fx[p] += w * a.x;
-          fy[p] += w * a.y;
-        }
-    }
-#pragma unroll
-    for (int off = GATHER_G / 2; off > 0; off >>= 1)
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-        if (p < n) {
-          fx[p] += __shfl_xor(fx[p], off, GATHER_G);
-          fy[p] += __shfl_xor(fy[p], off, GATHER_G);
-        }
-#pragma unroll
-    for (int p = 0; p < 8; ++p)
-      if (p < n && p % GATHER_G == g) {
-        const double2 f = make_double2(fx[p], fy[p]);
-        if (mode == 0) out[o + k * n + p] = f;
-        else ma_b[om + i * n + p] = f;
-      }
   }
 }
 
@@ -390,8 +362,10 @@ void launch_stencil_orb(const Batch& b, const double* u, const double* Ef, int d
 
 void launch_ma_gather_orb(const Batch& b, const double* acc, int mode, double* out, double* ma_b, hipStream_t s) {
   if (b.mx.nMa == 0) return;
-  hipLaunchKernelGGL(k_ma_gather_orb, dim3(nblocks(b.mx.nMa * GATHER_G), b.ni), dim3(NT), 0, s, b.dm,
-                     (const double2*)acc, mode, (double2*)out, (double2*)ma_b);
+  orb_dispatch(b.mx.n, [&](auto np) {
+    hipLaunchKernelGGL(k_ma_gather_orb<np.value>, dim3(xcd_grid(b.mx.nMa, NT / 32, 65536), b.ni), dim3(NT), 0, s,
+                       b.dm, (const double2*)acc, mode, (double2*)out, (double2*)ma_b);
+  });
 }
 
 void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma_b, hipStream_t s) {
