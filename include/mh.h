@@ -413,10 +413,8 @@ int mh_kernel_timing(mh_op* op, int32_t which, int32_t enable, double* avg_ms, i
  * only, sched bit 1: solve the interface block of the mass matrix by the
  * Chebyshev iteration even where the operator holds its dense inverse (a
  * single instance with at most 4096 interface unknowns holds one); bit 2:
- * the stiffness part of the orbital operator by the assembled Poisson
- * operator K~ applied to the 2n real columns of the orbitals (one sparse
- * pass with the Poisson schedule's long-row and sweep options), the node pass
- * adding only the diagonal and mean-field terms.  Poisson
+ * accepted and without effect (the operator is always applied by assembled
+ * rows).  Poisson
  * only, sched bit 1: column blocking (16 columns per block on grid.z) when
  * the column count is a multiple of 16 and at least 32; bit 2: rows of the
  * assembled operator with more than 48

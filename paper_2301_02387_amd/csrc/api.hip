@@ -110,8 +110,6 @@ struct mh_op {
   double* ginv = nullptr;   // [ni][n][n] c128
   double* lam = nullptr;    // [ni][n][n] c128
   double* F = nullptr;      // [tE][n] c128
-  double* kq = nullptr;     // [tE][n] c128: assembled stiffness times the orbitals (orbital schedule bit 2)
-  double* kred = nullptr;   // [ni][RED_SLOTS][2n] scratch accumulators of that operator pass
   double* ma_b = nullptr, *ma_x = nullptr, *ma_r = nullptr, *ma_d0 = nullptr, *ma_d1 = nullptr;  // [tMa][n]
   double* gpart = nullptr;  // reduction partials
   double* Mr = nullptr;     // [ni][n^2][n^2]
@@ -425,6 +423,42 @@ void* scratch_on(int dev) {
 }
 }  // namespace
 
+// Rows of the orbitals' one-body operator: counted, laid out and filled on the
+// device from the cells' node maps.
+static void build_orb_rows(mh_op* op, hipStream_t s) {
+  for (int i = 0; i < op->ni; ++i) {
+    DevMesh& d = op->dh[i];
+    int32_t* ptr = op->alloc<int32_t>(d.NE + 1);
+    std::vector<int32_t> h(d.NE + 1, 0);
+    if (d.NE > 0) {
+      launch_orb_row_count(op->B, i, ptr + 1, s);
+      HIPCHK(hipMemcpyAsync(h.data() + 1, ptr + 1, (size_t)d.NE * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s));
+    }
+    int64_t nnz = 0;
+    for (int64_t r = 1; r <= d.NE; ++r) {
+      nnz += h[r];
+      if (nnz > INT32_MAX) throw std::runtime_error("orbital operator: too many entries");
+      h[r] = (int32_t)nnz;
+    }
+    HIPCHK(hipMemcpyAsync(ptr, h.data(), h.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    HIPCHK(hipStreamSynchronize(s));  // h is a host temporary
+    int32_t* col = op->alloc<int32_t>(nnz);
+    double* k = op->alloc<double>(nnz);
+    double* sv = op->alloc<double>(nnz);
+    double* kc = d.ecs ? op->alloc<double>(2 * nnz) : nullptr;
+    double* sc = d.ecs ? op->alloc<double>(2 * nnz) : nullptr;
+    d.or_ptr = ptr;
+    d.or_col = col;
+    d.or_k = k;
+    d.or_s = sv;
+    d.or_kc = kc;
+    d.or_sc = sc;
+    upload_instances(op, s);
+    if (d.NE > 0) launch_orb_row_fill(op->B, i, col, k, sv, kc, sc, s);
+  }
+}
+
 static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_desc& desc, hipStream_t s) {
   const int ni = (int)spec.size();
   const int n = desc.n_orb, ncol = n * n;
@@ -594,6 +628,7 @@ static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_de
   op->dm = op->alloc<DevMesh>(ni);
   B.dm = op->dm;
   upload_instances(op.get(), s);
+  build_orb_rows(op.get(), s);
   // Poisson column layout
   std::vector<int> colinfo, colmap(n * n, -1);
   for (int r = 0; r < n; ++r)
@@ -614,8 +649,6 @@ static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_de
   op->ginv = op->alloc<double>(ni * 2 * nn);
   op->lam = op->alloc<double>(ni * 2 * nn);
   op->F = op->alloc<double>(2 * tE * n);
-  op->kq = op->alloc<double>(2 * tE * n);
-  op->kred = op->alloc<double>((size_t)ni * RED_SLOTS * 2 * n);
   const size_t nma = std::max<size_t>(1, B.tMa);
   op->ma_b = op->alloc<double>(2 * nma * n);
   op->ma_x = op->alloc<double>(2 * nma * n);
@@ -803,7 +836,7 @@ static void stencil_orb(mh_op* op, const double* u, const double* Ef, int diag_m
                         hipStream_t s) {
   const bool rec = op->timing && op->ev_used[0] + 2 <= (int)op->ev[0].size();
   if (rec) HIPCHK(hipEventRecord(op->ev[0][op->ev_used[0]], s));
-  launch_stencil_orb(op->B, u, Ef, diag_mode, op->Upk, op->ginv, mode, op->lam, out, op->acc, op->kq, op->kred, s);
+  launch_stencil_orb(op->B, u, Ef, diag_mode, op->Upk, op->ginv, mode, op->lam, out, op->acc, s);
   if (rec) {
     HIPCHK(hipEventRecord(op->ev[0][op->ev_used[0] + 1], s));
     op->ev_used[0] += 2;

@@ -53,6 +53,16 @@ struct DevMesh {
   const double* inv_mass = nullptr;     // [N] 1/m for non-masters
   const double* kdiag_inv = nullptr;    // [N]
   const int32_t* node_inc = nullptr;    // [NE][8]: cell*64 + local index of each incident cell, -1 padded
+  // one-body operator of the orbitals by rows, over the extended nodes (constraints
+  // not folded): (1/2) K and the antisymmetric derivative along the field
+  // direction; with complex scaling also both with the contour factors, times
+  // rho (re, im)
+  const int32_t* or_ptr = nullptr;      // [NE + 1]
+  const int32_t* or_col = nullptr;
+  const double* or_k = nullptr;
+  const double* or_s = nullptr;
+  const double* or_kc = nullptr;
+  const double* or_sc = nullptr;
   const int32_t* kt_ptr = nullptr;      // assembled Poisson operator on DoFs (CSR)
   const int32_t* kt_col = nullptr;
   const double* kt_val = nullptr;
@@ -82,8 +92,7 @@ struct DevMesh {
   double mgc[2 * MG_MAX_DEG - 1] = {};
   double vnn = 0.0;                     // nuclear repulsion
   // launch schedules (set by mh_tune): bit 0 = XCD-contiguous sweep; orbital bit 1 = interface
-  // solve by Chebyshev even where a dense inverse is held, bit 2 = stiffness part by the
-  // assembled operator; Poisson bit 1 =
+  // solve by Chebyshev even where a dense inverse is held, bit 2 = without effect; Poisson bit 1 =
   // column blocks of 16, bit 2 = long rows by whole waves, bit 3 = without
   // effect, bit 4 = geometric multigrid preconditioner (a
   // hierarchy per instance), bit 5 = short rows from the sliced-ELL copy (long
@@ -140,12 +149,13 @@ struct Batch {
 // 2: + mean field, 3: mz only, 4: -i S_e only (momentum along e).  mode 0:
 // load vector F; 1: M^-1 F; 2: M^-1 F - v lam.  Non-master DoFs are final in
 // out; masters and hanging nodes go to acc.  E is read from the device scalar
-// *Ef (times each instance's E0).  Orbital schedule bit 2: the stiffness part
-// by the assembled K~ (kq, kred scratch); not taken where the velocity term
-// or the momentum is applied (those run node by node).
+// *Ef (times each instance's E0).
 void launch_stencil_orb(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
-                        const double* ginv, int mode, const double* lam, double* out, double* acc, double* kq,
-                        double* kred, hipStream_t s);
+                        const double* ginv, int mode, const double* lam, double* out, double* acc, hipStream_t s);
+// rows of the one-body operator: entries per row into cnt [NE] (instance inst), then the entries
+void launch_orb_row_count(const Batch& b, int inst, int32_t* cnt, hipStream_t s);
+void launch_orb_row_fill(const Batch& b, int inst, int32_t* col, double* k, double* sv, double* kc, double* sc,
+                         hipStream_t s);
 // Masters: acc_k + sum_h c_hk acc_h -> out (mode 0) or the interface rhs ma_b.
 void launch_ma_gather_orb(const Batch& b, const double* acc, int mode, double* out, double* ma_b, hipStream_t s);
 void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma_b, hipStream_t s);

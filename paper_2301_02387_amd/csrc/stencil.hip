@@ -6,9 +6,8 @@
 // The element stiffness (h/2)(A x W x W + W x A x W + W x W x A) couples a
 // node only to the nodes on its three coordinate lines inside each cell
 // holding it (W is diagonal).  Each node therefore gathers its assembled
-// value directly: for every incident cell (at most 8) it sums the three line
-// contractions of the input, read straight from the cell's node map.  The
-// result is written once, with no scatter and no atomics.  Node-diagonal
+// value directly, from the row of coupled nodes laid out when the operator is
+// created.  The result is written once, with no scatter and no atomics.  Node-diagonal
 // terms (nuclear potential, field, mean field) are added by the same
 // thread; for DoFs that are not hanging-node masters the mass solve and
 // the projector term are applied in the same pass, so the output is final.
@@ -34,219 +33,338 @@ namespace mh {
 #define INSTANCE const DevMesh& d = dm[blockIdx.y]
 
 // --------------------------------------------------------------------------
+// Rows of the one-body operator.  Entry e = (cell t, direction, line point q)
+// of node i couples it to one node of a line through it; the row holds each
+// coupled node once, in order of first appearance (at most 8 cells x 3 lines x
+// (P - 1) + 1).  Stiffness (1/2) K; S along the field direction e: per cell
+// (h/2)^2 (Qs x W x W) along x and likewise along y and z.  Complex scaling: a
+// cell's stiffness and derivative loads along d take the contour factors
+// e^{i (s - 2 b_d) theta} and e^{i (s - b_d) theta} (s scaled directions, b_d
+// whether d is one), the node's sum rho = m / m_theta.
+// --------------------------------------------------------------------------
+template <int P>
+__device__ __forceinline__ int orb_entry_col(const DevMesh& d, int64_t i, int e) {
+  const int q = e % P, dir = (e / P) % 3, t = e / (3 * P);
+  const int code = gbl(d.node_inc)[i * 8 + t];
+  if (code < 0) return -1;
+  const int loc = code & 63, a = loc % P, b = (loc / P) % P, c = loc / (P * P);
+  const int l = dir == 0 ? (c * P + b) * P + q : dir == 1 ? (c * P + q) * P + a : (q * P + b) * P + a;
+  const int j = gbl(d.cell_nodes)[(int64_t)(code >> 6) * (P * P * P) + l];
+  return j < d.NE ? j : -1;
+}
+template <int P>
+__device__ __forceinline__ void orb_entry_add(const DevMesh& d, int64_t i, int e, double& k, double& sv, double2& kc,
+                                              double2& sc) {
+  const int q = e % P, dir = (e / P) % 3, t = e / (3 * P);
+  const int code = gbl(d.node_inc)[i * 8 + t], loc = code & 63;
+  const int64_t K = code >> 6;
+  const int x[3] = {loc % P, (loc / P) % P, loc / (P * P)};
+  const int a = x[dir], o1 = x[dir == 0 ? 1 : 0], o2 = x[dir == 2 ? 1 : 2];
+  const double h2 = gbl(d.cell_hh)[K], ww = d.w[o1] * d.w[o2];
+  const double fk = 0.5 * h2 * ww * d.A[a * P + q], fs = h2 * h2 * d.pol[dir] * ww * d.Qs[a * P + q];
+  k += fk;
+  sv += fs;
+  if (d.ecs) {
+    const int bits = gbl(d.ecs_code)[K], bd = (bits >> dir) & 1;
+    const int s = (bits & 1) + ((bits >> 1) & 1) + ((bits >> 2) & 1);
+    auto pw = [&](int z) { return make_double2(d.ecs_pw[2 * (z + 2)], d.ecs_pw[2 * (z + 2) + 1]); };
+    kc = cadd(kc, cscale(fk, pw(s - 2 * bd)));
+    sc = cadd(sc, cscale(fs, pw(s - bd)));
+  }
+}
+template <int P, bool FILL>
+__global__ void __launch_bounds__(NT) k_orb_row_build(const DevMesh* __restrict__ dm, int inst, int32_t* cnt,
+                                                      int32_t* col, double* k, double* sv, double2* kc, double2* sc) {
+  const DevMesh& d = dm[inst];
+  constexpr int E = 24 * P;
+  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < d.NE; i += (int64_t)gridDim.x * NT) {
+    int cols[E], m = 0;
+    for (int e = 0; e < E; ++e) cols[e] = orb_entry_col<P>(d, i, e);
+    const int64_t at = FILL ? gbl(d.or_ptr)[i] : 0;
+    for (int e = 0; e < E; ++e) {
+      const int j = cols[e];
+      if (j < 0) continue;
+      if (FILL) {
+        double kv = 0.0, s = 0.0;
+        double2 kz = make_double2(0.0, 0.0), sz = kz;
+        for (int f = e; f < E; ++f)
+          if (cols[f] == j) {
+            orb_entry_add<P>(d, i, f, kv, s, kz, sz);
+            cols[f] = -1;
+          }
+        col[at + m] = j;
+        k[at + m] = kv;
+        sv[at + m] = s;
+        if (d.ecs) {
+          const double2 rho = make_double2(d.ecs_rho[2 * i], d.ecs_rho[2 * i + 1]);
+          kc[at + m] = cmul(rho, kz);
+          sc[at + m] = cmul(rho, sz);
+        }
+      } else {
+        for (int f = e; f < E; ++f)
+          if (cols[f] == j) cols[f] = -1;
+      }
+      ++m;
+    }
+    if (!FILL) cnt[i] = m;
+  }
+}
+template <bool FILL>
+static void orb_row_build(const Batch& b, int inst, int32_t* cnt, int32_t* col, double* k, double* sv, double* kc,
+                          double* sc, hipStream_t s) {
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(nblocks(b.mx.NE, NT, 4096)), dim3(NT), 0, s, b.dm, inst, cnt, col, k, sv,
+                       (double2*)kc, (double2*)sc);
+  };
+  if (b.mx.P == 2) go(k_orb_row_build<2, FILL>);
+  else if (b.mx.P == 3) go(k_orb_row_build<3, FILL>);
+  else go(k_orb_row_build<4, FILL>);
+}
+void launch_orb_row_count(const Batch& b, int inst, int32_t* cnt, hipStream_t s) {
+  orb_row_build<false>(b, inst, cnt, nullptr, nullptr, nullptr, nullptr, nullptr, s);
+}
+void launch_orb_row_fill(const Batch& b, int inst, int32_t* col, double* k, double* sv, double* kc, double* sc,
+                         hipStream_t s) {
+  orb_row_build<true>(b, inst, nullptr, col, k, sv, kc, sc, s);
+}
+
+// --------------------------------------------------------------------------
 // Orbital operator.  mode 0: F = load vector; 1: M^-1 F; 2: M^-1 F - v lam.
+// diag_mode 0: one-body stiffness; 1: with the potential and the field; 2: with
+// the mean field; 3: dipole weights only; 4: momentum along the field.
 // Non-master DoFs get their final value in `out`; masters and hanging nodes
 // store the load value in `acc`.
+//
+// One pass over the rows above: L lanes (n rounded up to a power of two) hold
+// the node's orbitals, GR groups of them share its entries.  What the node adds
+// itself (diagonal weights, its n^2 mean-field values) is requested before the
+// row is gathered.  OP_K: stiffness; OP_S: the first-derivative term -i a.S u of
+// the velocity gauge (a = A(t) e, or e alone for the momentum); CX: instances
+// with complex scaling take the complex rows (their potential and field weights
+// are the continued ones, in units of the real mass; the mean-field load is
+// unchanged).
+// Bound by the gathers out of L2 (13 rows a node at Q3) and, at eight orbitals,
+// by HBM (512 B of mean-field values a node beside 128 B read and written);
+// where few nodes are, by the chain row -> index -> gather.  Before, the line
+// sums ran cell by cell (indices of every line of up to eight cells), or the
+// assembled Poisson operator on 2n real columns and a second pass over the nodes.
+// Measured, before -> rows: H2O (1.65 M nodes x 8 orbitals) 353 + 462 -> 539 us,
+// its momentum 1650 -> 359; on the Q1 mesh, velocity gauge with complex scaling
+// (234,000 x 8) 274 -> 113; 16 H2 (75,900 x 2 each) 144 + 52 -> 158; H2 14.0 +
+// 6.6 -> 12.9; 3 orbitals in the velocity gauge (Q2) 27 -> 10.4 us.
 // --------------------------------------------------------------------------
-// ASM: the stiffness part is taken from kq, the assembled K~ u on the DoF
-// rows (constraints folded in, so hanging rows carry no stiffness and the
-// masters already hold their hanging neighbours' share); the node then only
-// adds its diagonal and mean-field terms.
-// VEL: the first-derivative term -i a.S u of the velocity gauge (a = A(t) e,
-// or e alone for the momentum, diag_mode 4), S the Gauss-Lobatto Galerkin
-// derivative in its antisymmetric form: per cell (h/2)^2 (Qs x W x W) along x
-// and likewise along y and z, so its line sums share the stiffness's loads.
-// ECS: exterior complex scaling of the one-body part (diag_mode 0..2, on
-// instances that carry it): each cell's stiffness and derivative loads along
-// d take the contour factors e^{i (s - 2 b_d) theta} and e^{i (s - b_d) theta}
-// (s scaled directions, b_d whether d is one), the node's cell sum is
-// multiplied by rho = m / m_theta, and the potential and field weights are the
-// continued complex ones, so the load is in units of the real mass; the
-// mean-field load is unchanged.
-template <int P, int L, bool ASM, bool VEL, bool ECS>
-__global__ void __launch_bounds__(NT) k_stencil_orb(const DevMesh* __restrict__ dm, const double2* __restrict__ u,
-                                                    const double* __restrict__ Ef, int diag_mode,
-                                                    const double* __restrict__ Upk, const double2* __restrict__ ginv,
-                                                    int mode, const double2* __restrict__ lam,
-                                                    double2* __restrict__ out, double2* __restrict__ acc,
-                                                    const double2* __restrict__ kq) {
+template <int L, int GR, bool OP_K, bool OP_S, bool CX, bool MF>
+__global__ void __launch_bounds__(NT, OP_S && MF ? 3 : 4) k_orb_rows(const DevMesh* __restrict__ dm,
+                                                             const double2* __restrict__ u,
+                                                             const double* __restrict__ Ef, int diag_mode,
+                                                             const double* __restrict__ Upk,
+                                                             const double2* __restrict__ ginv, int mode,
+                                                             const double2* __restrict__ lam,
+                                                             double2* __restrict__ out, double2* __restrict__ acc) {
   INSTANCE;
-  constexpr int P3 = P * P * P;
-  // per wave: the packed mean-field matrices of its 64 / L nodes (at most 64 doubles each)
-  __shared__ double sU[NT / 64][512];
+  constexpr int LR = L * GR, RW = 64 / LR, U = GR > 2 ? 16 / GR : CX ? 4 : 8, NQ = (L + GR - 1) / GR, LS = L + 1;
+  // per wave: the rows' packed mean-field matrices (row stride L + 1: lanes p and
+  // rows fall on different banks), orbitals and mean-field products
+  __shared__ double sU[MF ? NT / 64 : 1][MF ? RW * L * LS : 1];
+  __shared__ double2 su[NT / 64][RW * L], sz[NT / 64][MF ? RW * L : 1];
+  __shared__ double2 sg[MF ? L * L : 1], sl[L * L];   // S^-1 transposed, lambda: row q, lane p
   const int n = d.n;
   const int64_t o = d.oE * n;
   u += o;
   out += o;
   acc += o;
-  if (ASM) kq += o;
   Upk += d.oE * n * n;
-  ginv += (int64_t)blockIdx.y * n * n;
-  if (lam) lam += (int64_t)blockIdx.y * n * n;
-  const double E = (diag_mode == 1 || diag_mode == 2) ? Ef[0] * d.E0 : 0.0;
-  // velocity term: vector potential a = A e (diag_mode 4: a = e); no stiffness for diag_mode 4
-  const double av = diag_mode == 4 ? 1.0 : E;
-  const double ax = VEL ? av * d.pol[0] : 0.0, ay = VEL ? av * d.pol[1] : 0.0, az = VEL ? av * d.pol[2] : 0.0;
-  const bool stiff = diag_mode <= 2;
-  const double Elen = d.gauge == 1 ? 0.0 : E;   // the length-gauge term only in the length gauge
-  const bool ecs_i = ECS && d.ecs && diag_mode <= 2;
-  // e^{i k theta}, k = -2..3, staged in LDS: the cells pick their factors by a per-lane index
-  __shared__ double2 spw[6];
-  if (ECS) {
-    if (threadIdx.x < 6) spw[threadIdx.x] = make_double2(d.ecs_pw[2 * threadIdx.x], d.ecs_pw[2 * threadIdx.x + 1]);
-    __syncthreads();
+  const int lane = (int)(threadIdx.x % LR), p = lane % L, grp = lane / L;
+  const int wave = (int)(threadIdx.x >> 6), slot = (int)(threadIdx.x & 63) / LR;
+  const bool act = p < n && grp == 0;
+  const int pc = min(p, n - 1);   // lanes past the last orbital repeat it and write nothing
+  for (int f = threadIdx.x; f < n * n; f += NT) {
+    const int r = f / n, c = f - r * n;
+    if (MF) sg[c * L + r] = ldg2(ginv, (int64_t)blockIdx.y * n * n + f);
+    if (mode == 2) sl[r * L + c] = ldg2(lam, (int64_t)blockIdx.y * n * n + f);
   }
-  auto pw = [&](int k) { return spw[k + 2]; };
-  const XcdSweep sw = xcd_sweep(d.NE, NT / L, d.sched_orb & 1);
-  // all L lanes of a node share i, so a node group enters and leaves together
-  for (int64_t i = sw.start + threadIdx.x / L; i < sw.end; i += sw.step) {
-    const int p = (int)(threadIdx.x & (L - 1));
-    const bool act = p < n;
-    double2 y = make_double2(0.0, 0.0), ui = make_double2(0.0, 0.0);
-    if (act) ui = u[i * n + p];
-    // the node's 8 incidence codes in two 16-byte loads (row of 32 bytes)
-    typedef int ivec4_t __attribute__((ext_vector_type(4)));
-    const auto* inc4 = reinterpret_cast<const __attribute__((address_space(1))) ivec4_t*>(gbl(d.node_inc) + i * 8);
-    ivec4_t ca = ivec4_t{-1, -1, -1, -1}, cb = ca;
-    if (!ASM) {
-      ca = inc4[0];
-      cb = inc4[1];
-    } else if (diag_mode != 3 && i < d.N && act) {
-      y = cscale(0.5, kq[i * n + p]);  // (1/2) K~ u
-    }
-    if (diag_mode == 3) ca = cb = ivec4_t{-1, -1, -1, -1};  // dipole weights only: no stiffness
-    const int codes[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
+  if (MF || mode == 2) __syncthreads();
+  const double E = (diag_mode == 1 || diag_mode == 2) ? Ef[0] * d.E0 : 0.0;
+  const double av = diag_mode == 4 ? 1.0 : E;
+  const double Elen = d.gauge == 1 ? 0.0 : E;   // the length-gauge term only in the length gauge
+  const bool cx = CX && d.ecs;
+  const bool diag = diag_mode >= 1 && diag_mode <= 3;
+  double* Up = &sU[MF ? wave : 0][MF ? slot * L * LS : 0];
+  double2* Us = &su[wave][slot * L];
+  double2* Zs = &sz[wave][MF ? slot * L : 0];
+  const auto* colp = gbl(d.or_col);
+  const auto* kp = gbl(d.or_k);
+  const auto* sp = gbl(d.or_s);
+  const XcdSweep sw = xcd_sweep(d.NE, NT / LR, d.sched_orb & 1);
+  // all LR lanes of a node share i, so a node group enters and leaves together
+  for (int i = (int)sw.start + (int)threadIdx.x / LR; i < (int)sw.end; i += (int)sw.step) {
+    const int64_t at = (int64_t)i * n + pc;
+    int beg = 0, end = 0, jn[U];
+    if (OP_K || OP_S) {
+      beg = gbl(d.or_ptr)[i] + grp;
+      end = gbl(d.or_ptr)[i + 1];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int code = codes[t];
-      if (code < 0) continue;
-      const int64_t K = code >> 6;
-      const int loc = code & 63;
-      const int a = loc % P, b = (loc / P) % P, c = loc / (P * P);
-      const auto* cn = gbl(d.cell_nodes) + K * P3;
-      double2 s0 = make_double2(0.0, 0.0), s1 = s0, s2 = s0;
-      double2 t0 = s0, t1 = s0, t2 = s0;
-#pragma unroll
-      for (int q = 0; q < P; ++q) {
-        const int j0 = cn[(c * P + b) * P + q], j1 = cn[(c * P + q) * P + a], j2 = cn[(q * P + b) * P + a];
-        const double A0 = d.A[a * P + q], A1 = d.A[b * P + q], A2 = d.A[c * P + q];
-        // the point q of a line through the node that is the node itself
-        // (q == a along x, ...) takes its value from the register, not memory
-        if (act) {
-          if (j0 < d.NE) {
-            double2 v;
-            if (q == a) v = ui;
-            else v = u[(int64_t)j0 * n + p];
-            s0.x += A0 * v.x; s0.y += A0 * v.y;
-            if (VEL) { const double Q = d.Qs[a * P + q]; t0.x += Q * v.x; t0.y += Q * v.y; }
-          }
-          if (j1 < d.NE) {
-            double2 v;
-            if (q == b) v = ui;
-            else v = u[(int64_t)j1 * n + p];
-            s1.x += A1 * v.x; s1.y += A1 * v.y;
-            if (VEL) { const double Q = d.Qs[b * P + q]; t1.x += Q * v.x; t1.y += Q * v.y; }
-          }
-          if (j2 < d.NE) {
-            double2 v;
-            if (q == c) v = ui;
-            else v = u[(int64_t)j2 * n + p];
-            s2.x += A2 * v.x; s2.y += A2 * v.y;
-            if (VEL) { const double Q = d.Qs[c * P + q]; t2.x += Q * v.x; t2.y += Q * v.y; }
-          }
-        }
-      }
-      const double hk = gbl(d.cell_hh)[K];  // h/2
-      int sc = 0, b0 = 0, b1 = 0, b2 = 0;    // scaled directions of the cell (complex scaling)
-      if (ecs_i) {
-        const int code = gbl(d.ecs_code)[K];
-        b0 = code & 1;
-        b1 = (code >> 1) & 1;
-        b2 = (code >> 2) & 1;
-        sc = b0 + b1 + b2;
-      }
-      if (stiff) {
-        const double hh = 0.5 * hk;  // (1/2) K with K_cell = (h/2)(...)
-        const double f0 = hh * d.w[b] * d.w[c], f1 = hh * d.w[a] * d.w[c], f2 = hh * d.w[a] * d.w[b];
-        if (ecs_i && sc) {
-          y = cadd(y, cscale(f0, cmul(pw(sc - 2 * b0), s0)));
-          y = cadd(y, cscale(f1, cmul(pw(sc - 2 * b1), s1)));
-          y = cadd(y, cscale(f2, cmul(pw(sc - 2 * b2), s2)));
-        } else {
-          y.x += f0 * s0.x + f1 * s1.x + f2 * s2.x;
-          y.y += f0 * s0.y + f1 * s1.y + f2 * s2.y;
-        }
-      }
-      if (VEL) {  // y += -i (h/2)^2 (ax Wb Wc t0 + ay Wa Wc t1 + az Wa Wb t2)
-        const double h2 = hk * hk;
-        const double g0 = h2 * ax * d.w[b] * d.w[c], g1 = h2 * ay * d.w[a] * d.w[c], g2 = h2 * az * d.w[a] * d.w[b];
-        if (ecs_i && sc) {
-          t0 = cmul(pw(sc - b0), t0);
-          t1 = cmul(pw(sc - b1), t1);
-          t2 = cmul(pw(sc - b2), t2);
-        }
-        y.x += g0 * t0.y + g1 * t1.y + g2 * t2.y;
-        y.y -= g0 * t0.x + g1 * t1.x + g2 * t2.x;
-      }
+      for (int h = 0; h < U; ++h) jn[h] = colp[min(beg + h * GR, end - 1)];   // a row holds its own node at least
     }
-    if (ecs_i && act) {
-      const auto* rho = gbl(d.ecs_rho);
-      y = cmul(make_double2(rho[2 * i], rho[2 * i + 1]), y);
-    }
-    if (diag_mode >= 1 && diag_mode <= 3 && act) {
-      if (ecs_i && diag_mode != 3) {
-        const auto* vc = gbl(d.ecs_v);
-        const auto* zc = gbl(d.ecs_mz);
-        const double2 dg = make_double2(vc[2 * i] + Elen * zc[2 * i], vc[2 * i + 1] + Elen * zc[2 * i + 1]);
-        y = cadd(y, cmul(dg, ui));
+    const double2 ui = ldg2(u, at);
+    double2 dg = make_double2(0.0, 0.0);
+    if (diag) {
+      if (cx && diag_mode != 3) {
+        const double2 vc = ldg2(d.ecs_v, i), zc = ldg2(d.ecs_mz, i);
+        dg = make_double2(vc.x + Elen * zc.x, vc.y + Elen * zc.y);
       } else {
-        const double dg = diag_mode == 3 ? gbl(d.mz)[i] : gbl(d.v)[i] + Elen * gbl(d.mz)[i];
-        y.x += dg * ui.x;
-        y.y += dg * ui.y;
+        dg.x = diag_mode == 3 ? gbl(d.mz)[i] : gbl(d.v)[i] + Elen * gbl(d.mz)[i];
       }
     }
-    if (diag_mode == 2) {
-      // z_p = sum_q U_pq u_q (U Hermitian, packed: Up[o][q] = Re U_oq, Up[q][o] = Im U_oq for o < q).
-      // The node's n^2 packed values are read by its L lanes in consecutive
-      // words and staged in the wave's LDS slice, where each lane then finds
-      // the entries of its row and column.
-      double* Up = &sU[threadIdx.x >> 6][((threadIdx.x & 63) / L) * (n * n)];
-      {
-        const auto* Ug = gbl(Upk) + i * n * n;
-        for (int f = (int)(threadIdx.x & (L - 1)); f < n * n; f += L) Up[f] = Ug[f];
+    double up[NQ], mass = 0.0;
+    if (MF) {
+#pragma unroll
+      for (int h = 0; h < NQ; ++h) up[h] = gbl(Upk)[(int64_t)i * (n * n) + min(h * GR + grp, n - 1) * n + pc];
+      mass = gbl(d.m)[i];
+    }
+    const bool dof = i < d.N;
+    const int mi = dof ? gbl(d.ma_index)[i] : -1;
+    const double im = dof && mi < 0 && mode != 0 ? gbl(d.inv_mass)[i] : 0.0;
+    // the row: y = sum k u, t = sum s u; the next round's nodes are requested
+    // before this round's gathers, entries past the end count zero
+    double2 y = make_double2(0.0, 0.0), t = y;
+    if (OP_K || OP_S) {
+      for (int e0 = beg; e0 - grp < end; e0 += U * GR) {
+        double2 k[U], sv[U], v[U];
+#pragma unroll
+        for (int h = 0; h < U; ++h) v[h] = ldg2(u, (int64_t)((unsigned)jn[h] * (unsigned)n + (unsigned)pc));
+#pragma unroll
+        for (int h = 0; h < U; ++h) {
+          const int e = e0 + h * GR, ec = min(e, end - 1);
+          const bool in = e < end;
+          if (OP_K) {
+            if (cx) k[h] = ldg2(d.or_kc, ec);
+            else k[h] = make_double2(kp[ec], 0.0);
+            k[h].x = in ? k[h].x : 0.0;
+            if (CX) k[h].y = in ? k[h].y : 0.0;
+          }
+          if (OP_S) {
+            if (cx) sv[h] = ldg2(d.or_sc, ec);
+            else sv[h] = make_double2(sp[ec], 0.0);
+            sv[h].x = in ? sv[h].x : 0.0;
+            if (CX) sv[h].y = in ? sv[h].y : 0.0;
+          }
+        }
+        if (e0 - grp + U * GR < end) {
+#pragma unroll
+          for (int h = 0; h < U; ++h) jn[h] = colp[min(e0 + (U + h) * GR, end - 1)];
+        }
+#pragma unroll
+        for (int h = 0; h < U; ++h) {
+          if (CX) {
+            if (OP_K) y = cadd(y, cmul(k[h], v[h]));
+            if (OP_S) t = cadd(t, cmul(sv[h], v[h]));
+          } else {
+            if (OP_K) y = cadd(y, cscale(k[h].x, v[h]));
+            if (OP_S) t = cadd(t, cscale(sv[h].x, v[h]));
+          }
+        }
+      }
+    }
+    if (OP_S) {  // -i a t
+      y.x += av * t.y;
+      y.y -= av * t.x;
+    }
+    // The groups split the sums over orbitals too: z_p = sum_q U_pq u_q (U
+    // Hermitian, packed: Up[o][q] = Re U_oq, Up[q][o] = Im U_oq for o < q),
+    // S^-1 z and u lambda.
+    double2 lm = make_double2(0.0, 0.0);
+    if (MF || mode == 2) {
+      if (grp == 0) Us[p] = ui;
+      if (MF) {
+#pragma unroll
+        for (int h = 0; h < NQ; ++h)
+          if (h * GR + grp < L) Up[(h * GR + grp) * LS + p] = up[h];
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       double2 z = make_double2(0.0, 0.0);
-      for (int q = 0; q < n; ++q) {
-        const double2 uq = make_double2(__shfl(ui.x, q, L), __shfl(ui.y, q, L));
-        if (act) {
-          double2 Upq;
-          if (p == q) Upq = make_double2(Up[p * n + p], 0.0);
-          else if (p < q) Upq = make_double2(Up[p * n + q], Up[q * n + p]);
-          else Upq = make_double2(Up[q * n + p], -Up[p * n + q]);
-          z = cadd(z, cmul(Upq, uq));
+#pragma unroll
+      for (int h = 0; h < NQ; ++h) {
+        const int q = h * GR + grp;
+        if (q < n) {
+          const double2 uq = Us[q];
+          if (MF) {
+            const double a = Up[p * LS + q], c = Up[q * LS + p];
+            z = cadd(z, cmul(make_double2(p <= q ? a : c, p < q ? c : (p > q ? -a : 0.0)), uq));
+          }
+          if (mode == 2) lm = cadd(lm, cmul(sl[q * L + p], uq));
         }
       }
-      __builtin_amdgcn_wave_barrier();  // the slice is rewritten for the wave's next nodes
-      double2 wv = make_double2(0.0, 0.0);
-      for (int oo = 0; oo < n; ++oo) {
-        const double2 zo = make_double2(__shfl(z.x, oo, L), __shfl(z.y, oo, L));
-        if (act) wv = cadd(wv, cmul(ginv[p * n + oo], zo));
+      if (MF) {
+#pragma unroll
+        for (int off = LR / 2; off >= L; off >>= 1) {
+          z.x += __shfl_xor(z.x, off, 64);
+          z.y += __shfl_xor(z.y, off, 64);
+        }
+        if (grp == 0) Zs[p] = z;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        double2 wv = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) {
+          const int q = h * GR + grp;
+          if (q < n) wv = cadd(wv, cmul(sg[q * L + p], Zs[q]));
+        }
+        y.x += mass * wv.x;
+        y.y += mass * wv.y;
       }
-      if (act) {
-        const double mi = gbl(d.m)[i];
-        y.x += mi * wv.x;
-        y.y += mi * wv.y;
-      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();  // the slices are rewritten for the wave's next nodes
     }
-    double2 lm = make_double2(0.0, 0.0);
-    if (mode == 2)
-      for (int q = 0; q < n; ++q) {
-        const double2 uq = make_double2(__shfl(ui.x, q, L), __shfl(ui.y, q, L));
-        if (act) lm = cadd(lm, cmul(lam[q * n + p], uq));
-      }
+    if (diag && grp == 0) y = cadd(y, cmul(dg, ui));
+    y = make_double2(im != 0.0 ? im * y.x - lm.x : y.x, im != 0.0 ? im * y.y - lm.y : y.y);
+#pragma unroll
+    for (int off = LR / 2; off >= L; off >>= 1) {
+      y.x += __shfl_xor(y.x, off, 64);
+      y.y += __shfl_xor(y.y, off, 64);
+    }
     if (!act) continue;
-    const bool dof = i < d.N;
-    const int mi = dof ? gbl(d.ma_index)[i] : -1;
-    if (dof && mi < 0) {
-      if (mode == 0) out[i * n + p] = y;
-      else out[i * n + p] = csub(cscale(gbl(d.inv_mass)[i], y), lm);
-    } else {
-      acc[i * n + p] = y;
-    }
+    if (dof && mi < 0) out[at] = y;
+    else acc[at] = y;
   }
+}
+
+template <int L, int GR>
+static void launch_orb_rows(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
+                            const double* ginv, int mode, const double* lam, double* out, double* acc, hipStream_t s) {
+  const bool vel = b.mx.gauge == 1 && (diag_mode == 1 || diag_mode == 2), cx = b.mx.ecs && diag_mode <= 2;
+  const bool mf = diag_mode == 2;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(b.mx.NE, NT / (L * GR), b.mx.grid_orb), b.ni), dim3(NT), 0, s, b.dm,
+                       (const double2*)u, Ef, diag_mode, Upk, (const double2*)ginv, mode, (const double2*)lam,
+                       (double2*)out, (double2*)acc);
+  };
+  if (diag_mode == 3) go(k_orb_rows<L, GR, false, false, false, false>);
+  else if (diag_mode == 4) go(k_orb_rows<L, GR, false, true, false, false>);
+  else if (vel && cx) mf ? go(k_orb_rows<L, GR, true, true, true, true>) : go(k_orb_rows<L, GR, true, true, true, false>);
+  else if (vel) mf ? go(k_orb_rows<L, GR, true, true, false, true>) : go(k_orb_rows<L, GR, true, true, false, false>);
+  else if (cx) mf ? go(k_orb_rows<L, GR, true, false, true, true>) : go(k_orb_rows<L, GR, true, false, true, false>);
+  else mf ? go(k_orb_rows<L, GR, true, false, false, true>) : go(k_orb_rows<L, GR, true, false, false, false>);
+}
+
+// Lane groups per node: rows of up to four orbitals are read by 8 lanes (their
+// entries then load in whole sectors); four groups where the nodes alone leave
+// the chip idle (below 2^20 lanes: four waves a SIMD).  Eight orbitals and 1.65 M
+// nodes: one group 736 us, two 720, four 810 (540 with the loads of lanes past
+// the last orbital unguarded, which left registers for four waves); 234,000
+// nodes of a Q1 mesh 178, 231, 203.
+void launch_stencil_orb(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
+                        const double* ginv, int mode, const double* lam, double* out, double* acc, hipStream_t s) {
+  const int n = b.mx.n, L = n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : 8;
+  const bool few = b.mx.NE * L * b.ni < (int64_t)1 << 20;
+  auto go = [&](auto f) { f(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, s); };
+  if (L == 1) go(launch_orb_rows<1, 8>);
+  else if (L == 2) go(launch_orb_rows<2, 4>);
+  else if (L == 4) few ? go(launch_orb_rows<4, 4>) : go(launch_orb_rows<4, 2>);
+  else few ? go(launch_orb_rows<8, 4>) : go(launch_orb_rows<8, 1>);
 }
 
 // Masters: load value = acc_k + sum_h c_hk acc_h (transposed constraints), a
@@ -288,75 +406,6 @@ __global__ void __launch_bounds__(NT) k_mass_direct(const DevMesh* __restrict__ 
     const int mi = gbl(d.ma_index)[k];
     if (mi < 0) out[o + idx] = cscale(gbl(d.inv_mass)[k], f[o + idx]);
     else ma_b[om + (int64_t)mi * n + (idx - k * n)] = f[o + idx];
-  }
-}
-
-static void launch_spmv_plain(const Batch& b, const double* x, int ncol, double* q, double* red, hipStream_t s);
-
-template <int P, int L>
-static void launch_stencil_orb_t(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
-                                 const double* ginv, int mode, const double* lam, double* out, double* acc,
-                                 const double* kq, hipStream_t s) {
-  const int grid = xcd_grid(b.mx.NE, NT / L, b.mx.grid_orb);
-  const bool vel = diag_mode == 4 || (b.mx.gauge == 1 && (diag_mode == 1 || diag_mode == 2));
-  const bool ecs = b.mx.ecs && diag_mode <= 2;
-  if (kq)
-    hipLaunchKernelGGL((k_stencil_orb<P, L, true, false, false>), dim3(grid, b.ni), dim3(NT), 0, s, b.dm,
-                       (const double2*)u, Ef, diag_mode, Upk, (const double2*)ginv, mode, (const double2*)lam,
-                       (double2*)out, (double2*)acc, (const double2*)kq);
-  else if (vel && ecs)
-    hipLaunchKernelGGL((k_stencil_orb<P, L, false, true, true>), dim3(grid, b.ni), dim3(NT), 0, s, b.dm,
-                       (const double2*)u, Ef, diag_mode, Upk, (const double2*)ginv, mode, (const double2*)lam,
-                       (double2*)out, (double2*)acc, (const double2*)nullptr);
-  else if (vel)
-    hipLaunchKernelGGL((k_stencil_orb<P, L, false, true, false>), dim3(grid, b.ni), dim3(NT), 0, s, b.dm,
-                       (const double2*)u, Ef, diag_mode, Upk, (const double2*)ginv, mode, (const double2*)lam,
-                       (double2*)out, (double2*)acc, (const double2*)nullptr);
-  else if (ecs)
-    hipLaunchKernelGGL((k_stencil_orb<P, L, false, false, true>), dim3(grid, b.ni), dim3(NT), 0, s, b.dm,
-                       (const double2*)u, Ef, diag_mode, Upk, (const double2*)ginv, mode, (const double2*)lam,
-                       (double2*)out, (double2*)acc, (const double2*)nullptr);
-  else
-    hipLaunchKernelGGL((k_stencil_orb<P, L, false, false, false>), dim3(grid, b.ni), dim3(NT), 0, s, b.dm,
-                       (const double2*)u, Ef, diag_mode, Upk, (const double2*)ginv, mode, (const double2*)lam,
-                       (double2*)out, (double2*)acc, (const double2*)nullptr);
-}
-
-template <int P>
-static void launch_stencil_orb_p(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
-                                 const double* ginv, int mode, const double* lam, double* out, double* acc,
-                                 const double* kq, hipStream_t s) {
-  const int n = b.mx.n;
-  if (n <= 1) launch_stencil_orb_t<P, 1>(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, kq, s);
-  else if (n <= 2) launch_stencil_orb_t<P, 2>(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, kq, s);
-  else if (n <= 4) launch_stencil_orb_t<P, 4>(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, kq, s);
-  else launch_stencil_orb_t<P, 8>(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, kq, s);
-}
-
-// Orbital schedule bit 2: the stiffness part by the assembled Poisson
-// operator K~ applied to the 2n real columns of the orbital array (the tuned
-// SpMV, long rows by waves), then the node pass adds the diagonal and
-// mean-field terms; kq [tE][n] and kred (RED_SLOTS x 2n per instance) are
-// scratch.
-void launch_stencil_orb(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
-                        const double* ginv, int mode, const double* lam, double* out, double* acc, double* kq,
-                        double* kred, hipStream_t s) {
-  // the velocity term, the momentum and complex scaling run node by node (their line sums
-  // share the stiffness's loads; the scaled stiffness is complex)
-  const bool vel = diag_mode == 4 || (b.mx.gauge == 1 && (diag_mode == 1 || diag_mode == 2));
-  const bool asm_k = (b.mx.sched_orb & 4) && kq && kred && !vel && !(b.mx.ecs && diag_mode <= 2);
-  if (asm_k && diag_mode != 3) {
-    // at 2n <= 16 columns the stiffness pass runs best on at most 8192
-    // workgroups, whatever cap the Poisson schedule of the pair columns takes
-    Batch bk = b;
-    bk.mx.grid_poi = std::min(b.mx.grid_poi, 8192);
-    launch_spmv_plain(bk, u, 2 * b.mx.n, kq, kred, s);
-  }
-  const double* q = asm_k ? kq : nullptr;
-  switch (b.mx.P) {
-    case 2: launch_stencil_orb_p<2>(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, q, s); break;
-    case 3: launch_stencil_orb_p<3>(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, q, s); break;
-    default: launch_stencil_orb_p<4>(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, q, s);
   }
 }
 
@@ -798,9 +847,6 @@ template <int L, int V, class T>
 static int launch_spmv_t(const Batch& b, const T* x, const T* pprev, T* pout, int ld, int nc, T* q, double* red,
                          int mode, int k, const PassExtra& ex, hipStream_t s) {
   switch (mode) {
-    case SP_PLAIN:
-      if constexpr (sizeof(T) == sizeof(double)) return launch_spmv_m<L, V, SP_PLAIN, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
-      return 0;
     case SP_CGJ:  // the residual itself: double only
       if constexpr (sizeof(T) == sizeof(double)) return launch_spmv_m<L, V, SP_CGJ, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
       return 0;
@@ -842,9 +888,6 @@ static int launch_spmv_mode(const Batch& b, const T* x, const T* pprev, T* pout,
   return launch_spmv_t<64, 1, T>(b, x, pprev, pout, ncol, ncol, q, red, mode, k, ex, s);
 }
 static PassExtra no_extra(int full = 0) { return PassExtra{nullptr, full}; }
-static void launch_spmv_plain(const Batch& b, const double* x, int ncol, double* q, double* red, hipStream_t s) {
-  launch_spmv_mode(b, x, x, q, ncol, q, red, SP_PLAIN, -1, s, no_extra());
-}
 
 // --------------------------------------------------------------------------
 // Jacobi-preconditioned CG, all columns of all instances at once with their

@@ -1,7 +1,7 @@
 """Autotuner for the launch schedules of the two operator kernels.
 
 Each candidate (sweep order, grid cap, and for the Poisson solve the long-row,
-fused-direction, column-block and multigrid options) is applied with ``Operator.tune`` and timed on the
+column-block and multigrid options) is applied with ``Operator.tune`` and timed on the
 caller's own inputs: the orbital operator by the library's event-pair kernel
 timing through ``rhs_apply`` (the frozen operator must be set), the Poisson
 solve by the wall time of a ``poisson_pairs`` solve from zero.  The
@@ -11,7 +11,7 @@ a JSON file) per (mesh signature, degree, orbitals, instances).
 import json
 import os
 
-ORB_CANDIDATES = [(s, g) for s in (1, 0, 5, 4) for g in (2048, 8192, 65536)]
+ORB_CANDIDATES = [(s, g) for s in (1, 0) for g in (2048, 8192, 65536)]
 POI_CANDIDATES = ([(s, g) for s in (13, 12, 5, 4, 9, 1, 45, 44, 37, 36) for g in (2048, 8192)]
                   + [(s, 8192) for s in (21, 20, 29, 53, 52, 85, 84, 117, 116, 373, 372, 629, 628)])
 # column blocking only changes anything at 32 or more columns (n >= 6 orbitals).
@@ -30,7 +30,7 @@ POI_CANDIDATES_WIDE = ([(13, 8192)]
                                                372, 628, 884)]
                        + [(s, g) for s in (117, 372, 373, 628) for g in (16384, 32768)])
 # grid caps are per instance: a batch fills the chip with fewer workgroups each
-ORB_CANDIDATES_BATCH = [(s, g) for s in (1, 0, 5, 4) for g in (256, 1024, 65536)]
+ORB_CANDIDATES_BATCH = [(s, g) for s in (1, 0) for g in (256, 1024, 65536)]
 POI_CANDIDATES_BATCH = ([(s, g) for s in (13, 12, 5, 4, 1, 45, 37, 36) for g in (256, 1024)]
                         + [(s, g) for s in (21, 20, 53, 52, 117, 116) for g in (256, 1024)]
                         + [(s, 2048) for s in (117, 116)])

@@ -106,7 +106,7 @@ def test_multigrid_cells_wide():
             assert np.abs(got[k] - ref[k]).max() <= 1e-10 * np.abs(ref[k]).max()
 
 
-def frozen(P, op, n, seed, E=0.013, copies=1):
+def frozen(P, op, n, seed, E=0.013, copies=1, one_body=None):
     """Oracle frozen operator and the library (a handle of `copies` equal instances) frozen on the same inputs."""
     from oracle.ci import CISpace
     from oracle.mctdhf import Frozen
@@ -117,7 +117,7 @@ def frozen(P, op, n, seed, E=0.013, copies=1):
     W = poisson_solver(P.ops).pair_potentials(c)
     rep = lambda a: dev(np.concatenate([a] * copies))  # noqa: E731
     op.freeze(rep(P.to_lib_orb(c)), rep(gam), rep(Gam), E, rep(P.W_to_lib(W, n)))
-    return c, Frozen(P.ops, c, gam, Gam, E, W)
+    return c, Frozen(one_body or P.ops, c, gam, Gam, E, W)
 
 
 def check_arnoldi(P, op, c, fr, tau, m, copies=1):
@@ -151,6 +151,34 @@ def test_arnoldi_vectors(n, m, copies):
         op = mh.Operator.batch([P.mesh] * copies, [P.w["nuclei"]] * copies, n, (n + 1) // 2, n // 2)
     c, fr = frozen(P, op, n, 60 + n, copies=copies)
     check_arnoldi(P, op, c, fr, 0.02, m, copies)
+
+
+@pytest.mark.parametrize("gauge", ["length", "velocity"])
+@pytest.mark.parametrize("n,copies", [(1, 1), (2, 1), (3, 1), (4, 1), (6, 1), (8, 1), (3, 43), (4, 43), (5, 22), (8, 22)])
+def test_orbital_rows(n, copies, gauge):
+    """G v by rows at every lane width, with four lane groups a node (one
+    instance) and with one or two (above 2^20 lanes: 22 or 43 instances)."""
+    import copy
+    import paper_2301_02387_amd as mh
+    import torch
+    from oracle.fem import Operators
+    from tests.lib_cases import rel_err_cols, max_rel_cols
+    P = copy.copy(pair("tiny_q3"))
+    kw = dict(gauge=gauge)
+    if copies == 1:
+        op = mh.Operator(P.mesh, P.w["nuclei"], n, (n + 1) // 2, n // 2, **kw)
+    else:
+        op = mh.Operator.batch([P.mesh] * copies, [P.w["nuclei"]] * copies, n, (n + 1) // 2, n // 2, **kw)
+    ops = P.ops if gauge == "length" else Operators(P.om, P.w["nuclei"], gauge="velocity")
+    _, fr = frozen(P, op, n, 100 + n, E=0.31, copies=copies, one_body=ops)
+    v = orbitals(P, n, 120 + n)
+    out = torch.zeros((P.NE * copies, n), dtype=torch.complex128, device="cuda")
+    op.rhs_apply(dev(np.concatenate([P.to_lib_orb(v)] * copies)), out)
+    torch.cuda.synchronize()
+    ref = fr.G(v)
+    for part in np.split(out.cpu().numpy(), copies):
+        got = P.from_lib_dof(part)
+        assert rel_err_cols(got, ref) < 1e-10 and max_rel_cols(got, ref) < 1e-10
 
 
 @pytest.mark.parametrize("copies", [1, 2])
