@@ -115,73 +115,74 @@ __global__ void __launch_bounds__(NT) k_cheb_finish(const DevMesh* __restrict__ 
   }
 }
 
-// Interface solve by the dense inverse (one instance): x = A^-1 b, one wave per
-// row, the lanes splitting the row's columns (four strides of 64 per round,
-// their loads in flight together); then the final value of each master DoF
-// as in k_cheb_finish.  NP: the orbital count rounded up (2, 4 or 8).
-template <int NP>
+// Interface solve by the dense inverse (one instance): x = A^-1 b, R rows per
+// workgroup, its four waves splitting the columns; then the final value of each
+// master DoF as in k_cheb_finish.  NP: the orbital count rounded up (2, 4 or 8).
+// Bound by the inverse (45 MB at H2's 2,382 masters).  A wave per row read b once
+// a row, four times the inverse's bytes, with nine waves a CU; here b is read
+// once for R rows: H2 (2,382 masters x 2 orbitals) 16.5 -> 11.9 us, three orbitals
+// on a Q2 mesh 12.2 -> 8.6 us.
+template <int NP, int R>
 __global__ void __launch_bounds__(NT) k_ma_dense(const DevMesh* __restrict__ dm, const double2* __restrict__ b,
                                                  const double2* __restrict__ v, const double2* __restrict__ lam,
                                                  double2* __restrict__ out) {
   INSTANCE;
-  const int n = d.n;
-  const int64_t nMa = d.nMa, o = d.oMa * n, oe = d.oE * n;
+  constexpr int W = NT / 64;
+  __shared__ double part[W][R * NP * 2];
+  const int n = d.n, nMa = (int)d.nMa;
+  const int64_t o = d.oMa * n, oe = d.oE * n;
   const auto* Ai = gbl(d.ma_inv);
-  const int lane = threadIdx.x & 63;
   const double2* L = lam ? lam + (int64_t)blockIdx.y * n * n : nullptr;
-  for (int64_t i = ((int64_t)blockIdx.x * NT + threadIdx.x) >> 6; i < nMa; i += ((int64_t)gridDim.x * NT) >> 6) {
-    double sx[NP], sy[NP];
+  for (int i0 = (int)blockIdx.x * R; i0 < nMa; i0 += (int)gridDim.x * R) {
+    double s[R * NP * 2];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) { sx[p] = 0.0; sy[p] = 0.0; }
-    const auto* row = Ai + i * nMa;
-    int64_t j = lane;
-    for (; j + 192 < nMa; j += 256) {
-      double a[4];
-      double2 bj[4][NP];
+    for (int k = 0; k < R * NP * 2; ++k) s[k] = 0.0;
+    int64_t row[R];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = row[j + 64 * u];
+    for (int r = 0; r < R; ++r) row[r] = (int64_t)min(i0 + r, nMa - 1) * nMa;
+    // two strides of the workgroup's columns in flight; columns past the end
+    // repeat the last one with coefficient zero
+    for (int j0 = (int)threadIdx.x; j0 < nMa; j0 += 2 * NT) {
+      double a[2][R];
+      double2 bj[2][NP];
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-          if (p < n) bj[u][p] = ldg2(b, o + (j + 64 * u) * n + p);
+      for (int u = 0; u < 2; ++u) {
+        const int j = j0 + u * NT, jc = min(j, nMa - 1);
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[u][r] = Ai[row[r] + jc];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) bj[u][p] = ldg2(b, o + (int64_t)jc * n + min(p, n - 1));
+        if (j >= nMa) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) a[u][r] = 0.0;
+        }
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-          if (p < n) {
-            sx[p] += a[u] * bj[u][p].x;
-            sy[p] += a[u] * bj[u][p].y;
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int p = 0; p < NP; ++p) {
+            s[(r * NP + p) * 2] += a[u][r] * bj[u][p].x;
+            s[(r * NP + p) * 2 + 1] += a[u][r] * bj[u][p].y;
           }
     }
-    for (; j < nMa; j += 64) {
-      const double a = row[j];
-#pragma unroll
-      for (int p = 0; p < NP; ++p)
-        if (p < n) {
-          const double2 bj = ldg2(b, o + j * n + p);
-          sx[p] += a * bj.x;
-          sy[p] += a * bj.y;
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-      for (int p = 0; p < NP; ++p)
-        if (p < n) {
-          sx[p] += __shfl_xor(sx[p], off, 64);
-          sy[p] += __shfl_xor(sy[p], off, 64);
-        }
-    if (lane < n) {
+    wave_sum_values(s, part[threadIdx.x >> 6]);
+    __syncthreads();
+    const int r = (int)threadIdx.x / NP, p = (int)threadIdx.x - r * NP, i = i0 + r;
+    if (r < R && p < n && i < nMa) {
       double2 xf = make_double2(0.0, 0.0);
 #pragma unroll
-      for (int p = 0; p < NP; ++p)
-        if (p == lane) xf = make_double2(sx[p], sy[p]);
+      for (int w = 0; w < W; ++w) {
+        xf.x += part[w][(r * NP + p) * 2];
+        xf.y += part[w][(r * NP + p) * 2 + 1];
+      }
       const int64_t k = d.ma_dof[i];
       if (L)
-        for (int q = 0; q < n; ++q) xf = csub(xf, cmul(L[q * n + lane], v[oe + k * n + q]));
-      out[oe + k * n + lane] = xf;
+        for (int q = 0; q < n; ++q) xf = csub(xf, cmul(L[q * n + p], v[oe + k * n + q]));
+      out[oe + k * n + p] = xf;
     }
+    __syncthreads();
   }
 }
 
@@ -221,16 +222,13 @@ void launch_ma_solve(const Batch& b, const double* ma_b, double* x, double* r, d
                      const double* v, const double* lam, double* out, hipStream_t s) {
   if (b.mx.nMa == 0) return;
   if (b.ni == 1 && b.mx.ma_inv && !(b.mx.sched_orb & 2)) {
-    const dim3 g(nblocks(b.mx.nMa * 64, NT, 8192), 1);
-    if (b.mx.n <= 2)
-      hipLaunchKernelGGL(k_ma_dense<2>, g, dim3(NT), 0, s, b.dm, (const double2*)ma_b, (const double2*)v,
-                         (const double2*)lam, (double2*)out);
-    else if (b.mx.n <= 4)
-      hipLaunchKernelGGL(k_ma_dense<4>, g, dim3(NT), 0, s, b.dm, (const double2*)ma_b, (const double2*)v,
-                         (const double2*)lam, (double2*)out);
-    else
-      hipLaunchKernelGGL(k_ma_dense<8>, g, dim3(NT), 0, s, b.dm, (const double2*)ma_b, (const double2*)v,
-                         (const double2*)lam, (double2*)out);
+    auto go = [&](auto kern, int rows) {
+      hipLaunchKernelGGL(kern, dim3(nblocks(b.mx.nMa, rows, 8192)), dim3(NT), 0, s, b.dm, (const double2*)ma_b,
+                         (const double2*)v, (const double2*)lam, (double2*)out);
+    };
+    if (b.mx.n <= 2) go(k_ma_dense<2, 4>, 4);
+    else if (b.mx.n <= 4) go(k_ma_dense<4, 4>, 4);
+    else go(k_ma_dense<8, 2>, 2);
     return;
   }
   const dim3 g(nblocks(b.mx.nMa * b.mx.n), b.ni);
