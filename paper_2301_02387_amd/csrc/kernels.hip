@@ -443,14 +443,41 @@ __global__ void __launch_bounds__(NT) k_xgram_small(const DevMesh* __restrict__ 
 }
 
 // out[i][o] = sum_b part[i][b][o]; one workgroup per (output, instance)
-__global__ void __launch_bounds__(NT) k_sum_parts(const double2* __restrict__ part, int nblk, int nout,
-                                                  double2* __restrict__ out) {
-  __shared__ double lds4[4];
-  const double* pi = (const double*)(part + (int64_t)blockIdx.y * nblk * nout);
-  const int o = blockIdx.x;
-  const double sx = sum_partials(pi, nblk, 2 * nout, 2 * o, lds4);
-  const double sy = sum_partials(pi, nblk, 2 * nout, 2 * o + 1, lds4);
-  if (threadIdx.x == 0) out[(int64_t)blockIdx.y * nout + o] = make_double2(sx, sy);
+// out[o] = sum over nblk partials [nblk][nout] (per instance): cw consecutive
+// outputs per workgroup, its NT / cw slices of the partials summed in turn (eight
+// loads in flight) and folded in LDS, so that a partial's outputs are read in
+// whole lines.  Bound by HBM on long partials, by the launch on short ones.  A
+// workgroup per output reading with the partials' stride -> this, at 8 orbitals:
+// moments (2,048 partials of 10,816) 234 us, pair integrals (8,192 outputs) and Gram
+// matrices (128) 55 us on average -> all 14 launches of two steps 1130 -> 145 us; 8
+// outputs 3.1 -> 3.0 us.
+__global__ void __launch_bounds__(NT) k_sum_parts(const double* __restrict__ part, int nblk, int nout, int cw,
+                                                  double* __restrict__ out) {
+  __shared__ double lds[NT];
+  const int c = (int)threadIdx.x % cw, g = (int)threadIdx.x / cw, G = NT / cw;
+  const int o = (int)blockIdx.x * cw + c, oc = min(o, nout - 1);
+  const auto* p = gbl(part + (int64_t)blockIdx.y * nblk * nout);
+  double s = 0.0;
+  for (int b = g; b < nblk; b += 8 * G) {
+    double v[8];
+#pragma unroll
+    for (int h = 0; h < 8; ++h) v[h] = p[(int64_t)min(b + h * G, nblk - 1) * nout + oc];
+#pragma unroll
+    for (int h = 0; h < 8; ++h) s += b + h * G < nblk ? v[h] : 0.0;
+  }
+  lds[threadIdx.x] = s;
+  __syncthreads();
+  for (int h = G / 2; h > 0; h >>= 1) {
+    if (g < h) lds[threadIdx.x] += lds[threadIdx.x + h * cw];
+    __syncthreads();
+  }
+  if (g == 0 && o < nout) out[(int64_t)blockIdx.y * nout + o] = lds[c];
+}
+// 16 outputs (a 128-byte line) a workgroup where that still gives a workgroup
+// per quarter of the chip, else 4: then a thread has one round of loads.
+static void launch_sum_parts(const double* part, int nblk, int nout, double* out, int ni, hipStream_t s) {
+  const int cw = nout >= 1024 ? 16 : 4;
+  hipLaunchKernelGGL(k_sum_parts, dim3((nout + cw - 1) / cw, ni), dim3(NT), 0, s, part, nblk, nout, cw, out);
 }
 
 int gram_blocks(int64_t rows) { return nblocks(rows, XG_CH, 512); }
@@ -464,8 +491,7 @@ void launch_gram(const Batch& b, const double* A, const double* B, int wsel, int
   else
     hipLaunchKernelGGL(k_xgram, dim3(nblk, b.ni), dim3(NT), 0, s, b.dm, wsel, rows, (const double2*)A, n,
                        (const double2*)B, n, (double2*)part);
-  hipLaunchKernelGGL(k_sum_parts, dim3(n * n, b.ni), dim3(NT), 0, s, (const double2*)part, nblk, n * n,
-                     (double2*)G);
+  launch_sum_parts(part, nblk, 2 * n * n, G, b.ni, s);
 }
 
 // Pair-product integrals: G[(p,q)][col] = sum_i m_i conj(phi_p) phi_q Wcol_i
@@ -698,8 +724,7 @@ void launch_gint_full(const Batch& b, const double* phi, const double* W, const 
   else
     hipLaunchKernelGGL(k_gint, dim3(nblk, b.ni), dim3(NT), 0, s, b.dm, (const double2*)phi, W, ncol,
                        (double2*)part);
-  hipLaunchKernelGGL(k_sum_parts, dim3(ncol * ncol, b.ni), dim3(NT), 0, s, (const double2*)part, nblk, ncol * ncol,
-                     (double2*)Gtmp);
+  launch_sum_parts(part, nblk, 2 * ncol * ncol, Gtmp, b.ni, s);
   hipLaunchKernelGGL(k_gint_assemble, dim3(nblocks(ncol * ncol), b.ni), dim3(NT), 0, s, (const double2*)Gtmp, n,
                      colmap, (double2*)g);
 }
@@ -1545,13 +1570,6 @@ __global__ void __launch_bounds__(NT) k_moments_mfma(const DevMesh* __restrict__
 }
 
 // out[i][o] = sum_b part[i][b][o]; one workgroup per (output, instance)
-__global__ void __launch_bounds__(NT) k_sum_parts_real(const double* __restrict__ part, int nblk, int nout,
-                                                       double* __restrict__ out) {
-  __shared__ double lds4[4];
-  const double s = sum_partials(part + (int64_t)blockIdx.y * nblk * nout, nblk, nout, blockIdx.x, lds4);
-  if (threadIdx.x == 0) out[(int64_t)blockIdx.y * nout + blockIdx.x] = s;
-}
-
 // W[NE + b][c] = sum_t table[b][t] Q[t][c]
 __global__ void k_bnd_eval(const DevMesh* __restrict__ dm, int nh, const double* __restrict__ Q, int ncol,
                            double* __restrict__ W) {
@@ -1730,7 +1748,7 @@ void launch_poisson_pipeline_moments(const Batch& b, const double* phi, const in
     hipLaunchKernelGGL(k_moments_rb, dim3(P.mblk, b.ni, nz), dim3(NT), 0, s, b.dm, ph, P.lmax, P.ncol, colinfo,
                        P.mpart);
   }
-  hipLaunchKernelGGL(k_sum_parts_real, dim3(nout, b.ni), dim3(NT), 0, s, P.mpart, P.mblk, nout, P.Q);
+  launch_sum_parts(P.mpart, P.mblk, nout, P.Q, b.ni, s);
 }
 
 void launch_bnd_eval(const Batch& b, PoissonWs& P, double* W, hipStream_t s) {
