@@ -1299,8 +1299,7 @@ extern "C" int mh_mass_solve(mh_op* op, const double* f, double* c, void* stream
   return guarded([&]() -> int {
     hipStream_t s = S(stream);
     const Batch& B = op->B;
-    launch_mass_direct(B, f, c, op->ma_b, s);
-    launch_ma_solve(B, op->ma_b, op->ma_x, op->ma_r, op->ma_d0, op->ma_d1, nullptr, nullptr, c, s);
+    launch_mass_solve(B, f, c, op->ma_b, op->ma_x, op->ma_r, op->ma_d0, op->ma_d1, s);
     launch_fill_orb(B, c, nullptr, s);
     HIPCHK(hipGetLastError());
     return MH_OK;
@@ -1326,8 +1325,7 @@ extern "C" int mh_mass_solve_noalloc(mh_op* op, const double* f, double* c, void
     // every scratch element the kernels read is written first in this call
     // (gather of the right-hand side, then the iteration's initial state)
     double* mb = base;
-    launch_mass_direct(B, f, c, mb, s);
-    launch_ma_solve(B, mb, mb + buf, mb + 2 * buf, mb + 3 * buf, mb + 4 * buf, nullptr, nullptr, c, s);
+    launch_mass_solve(B, f, c, mb, mb + buf, mb + 2 * buf, mb + 3 * buf, mb + 4 * buf, s);
     launch_fill_orb(B, c, nullptr, s);
     HIPCHK(hipGetLastError());
     return MH_OK;

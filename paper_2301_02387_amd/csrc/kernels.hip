@@ -122,18 +122,32 @@ __global__ void __launch_bounds__(NT) k_cheb_finish(const DevMesh* __restrict__ 
 // a row, four times the inverse's bytes, with nine waves a CU; here b is read
 // once for R rows: H2 (2,382 masters x 2 orbitals) 16.5 -> 11.9 us, three orbitals
 // on a Q2 mesh 12.2 -> 8.6 us.
-template <int NP, int R>
+// LOAD: the solve of a given load vector (b over extended rows): the right-hand
+// side is read through the masters' DoFs, and the workgroups from `dense` on
+// divide the other DoFs by their mass, which saves the gathering launch.
+template <int NP, int R, bool LOAD>
 __global__ void __launch_bounds__(NT) k_ma_dense(const DevMesh* __restrict__ dm, const double2* __restrict__ b,
                                                  const double2* __restrict__ v, const double2* __restrict__ lam,
-                                                 double2* __restrict__ out) {
+                                                 double2* __restrict__ out, int dense) {
   INSTANCE;
+  if (LOAD && (int)blockIdx.x >= dense) {
+    const int64_t total = d.N * d.n, od = d.oE * d.n;
+    for (int64_t e = (int64_t)((int)blockIdx.x - dense) * NT + threadIdx.x; e < total;
+         e += (int64_t)((int)gridDim.x - dense) * NT) {
+      const int64_t k = e / d.n;
+      const double2 f = ldg2(b, od + e);
+      const double im = gbl(d.inv_mass)[k];
+      if (gbl(d.ma_index)[k] < 0) out[od + e] = cscale(im, f);
+    }
+    return;
+  }
   constexpr int W = NT / 64;
   __shared__ double part[W][R * NP * 2];
   const int n = d.n, nMa = (int)d.nMa;
   const int64_t o = d.oMa * n, oe = d.oE * n;
   const auto* Ai = gbl(d.ma_inv);
   const double2* L = lam ? lam + (int64_t)blockIdx.y * n * n : nullptr;
-  for (int i0 = (int)blockIdx.x * R; i0 < nMa; i0 += (int)gridDim.x * R) {
+  for (int i0 = (int)blockIdx.x * R; i0 < nMa; i0 += dense * R) {
     double s[R * NP * 2];
 #pragma unroll
     for (int k = 0; k < R * NP * 2; ++k) s[k] = 0.0;
@@ -151,7 +165,8 @@ __global__ void __launch_bounds__(NT) k_ma_dense(const DevMesh* __restrict__ dm,
 #pragma unroll
         for (int r = 0; r < R; ++r) a[u][r] = Ai[row[r] + jc];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) bj[u][p] = ldg2(b, o + (int64_t)jc * n + min(p, n - 1));
+        for (int p = 0; p < NP; ++p)
+          bj[u][p] = ldg2(b, (LOAD ? oe + (int64_t)gbl(d.ma_dof)[jc] * n : o + (int64_t)jc * n) + min(p, n - 1));
         if (j >= nMa) {
 #pragma unroll
           for (int r = 0; r < R; ++r) a[u][r] = 0.0;
@@ -223,12 +238,13 @@ void launch_ma_solve(const Batch& b, const double* ma_b, double* x, double* r, d
   if (b.mx.nMa == 0) return;
   if (b.ni == 1 && b.mx.ma_inv && !(b.mx.sched_orb & 2)) {
     auto go = [&](auto kern, int rows) {
-      hipLaunchKernelGGL(kern, dim3(nblocks(b.mx.nMa, rows, 8192)), dim3(NT), 0, s, b.dm, (const double2*)ma_b,
-                         (const double2*)v, (const double2*)lam, (double2*)out);
+      const int g = nblocks(b.mx.nMa, rows, 8192);
+      hipLaunchKernelGGL(kern, dim3(g), dim3(NT), 0, s, b.dm, (const double2*)ma_b, (const double2*)v,
+                         (const double2*)lam, (double2*)out, g);
     };
-    if (b.mx.n <= 2) go(k_ma_dense<2, 4>, 4);
-    else if (b.mx.n <= 4) go(k_ma_dense<4, 4>, 4);
-    else go(k_ma_dense<8, 2>, 2);
+    if (b.mx.n <= 2) go(k_ma_dense<2, 4, false>, 4);
+    else if (b.mx.n <= 4) go(k_ma_dense<4, 4, false>, 4);
+    else go(k_ma_dense<8, 2, false>, 2);
     return;
   }
   const dim3 g(nblocks(b.mx.nMa * b.mx.n), b.ni);
@@ -248,6 +264,28 @@ void launch_ma_solve(const Batch& b, const double* ma_b, double* x, double* r, d
   }
   hipLaunchKernelGGL(k_cheb_finish, g, dim3(NT), 0, s, b.dm, (const double2*)x, (const double2*)din,
                      (const double2*)v, (const double2*)lam, (double2*)out);
+}
+
+// Mass solve of a load vector f (extended rows) on the DoFs: with a dense inverse
+// one launch, the non-masters' workgroups beside the dense rows'; in place, and on
+// the Chebyshev path, the masters' rows are gathered to ma_b first.  H atom (4,007
+// DoFs, 196 masters), hanging rows included: three launches -> two, 9.5 -> 6.8 us on
+// the device, 14.0 -> 11.0 us a call.
+void launch_mass_solve(const Batch& b, const double* f, double* out, double* ma_b, double* x, double* r, double* dbuf0,
+                       double* dbuf1, hipStream_t s) {
+  if (b.ni == 1 && b.mx.nMa > 0 && b.mx.ma_inv && !(b.mx.sched_orb & 2) && f != out) {
+    auto go = [&](auto kern, int rows) {
+      const int g = nblocks(b.mx.nMa, rows, 8192);
+      hipLaunchKernelGGL(kern, dim3(g + nblocks(b.mx.N * b.mx.n, NT, 8192)), dim3(NT), 0, s, b.dm, (const double2*)f,
+                         (const double2*)nullptr, (const double2*)nullptr, (double2*)out, g);
+    };
+    if (b.mx.n <= 2) go(k_ma_dense<2, 4, true>, 4);
+    else if (b.mx.n <= 4) go(k_ma_dense<4, 4, true>, 4);
+    else go(k_ma_dense<8, 2, true>, 2);
+    return;
+  }
+  launch_mass_direct(b, f, out, ma_b, s);
+  launch_ma_solve(b, ma_b, x, r, dbuf0, dbuf1, nullptr, nullptr, out, s);
 }
 
 // Hanging rows: x[h] = sum_k c_hk x[k] over DoF masters (boundary values of

@@ -161,6 +161,9 @@ void launch_ma_gather_orb(const Batch& b, const double* acc, int mode, double* o
 void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma_b, hipStream_t s);
 void launch_ma_solve(const Batch& b, const double* ma_b, double* x, double* r, double* dbuf0, double* dbuf1,
                      const double* v, const double* lam, double* out, hipStream_t s);
+// mass solve of a load vector on the DoFs (hanging rows of out not filled)
+void launch_mass_solve(const Batch& b, const double* f, double* out, double* ma_b, double* x, double* r, double* dbuf0,
+                       double* dbuf1, hipStream_t s);
 void launch_fill_orb(const Batch& b, double* x, double* acc, hipStream_t s);
 // In-place Gauss-Jordan inverse of a dense SPD matrix [n][n] (no pivoting), 3 n launches.
 void launch_dense_inverse(double* A, int64_t n, hipStream_t s);

@@ -181,6 +181,26 @@ def test_orbital_rows(n, copies, gauge):
         assert rel_err_cols(got, ref) < 1e-10 and max_rel_cols(got, ref) < 1e-10
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8])
+def test_mass_solve_in_place(n):
+    """The mass solve by the dense inverse at every orbital width, into another
+    array (one launch) and in place (masters gathered first): the same values,
+    and M c = f."""
+    import torch
+    from tests.lib_cases import rel_err_cols
+    P = pair("tiny_q3")
+    op = operator(P, n)
+    f = dev(P.to_lib_orb(orbitals(P, n, 140 + n)))
+    c = torch.zeros_like(f)
+    op.mass_solve(f, c)
+    g = f.clone()
+    op.mass_solve(g, g)
+    torch.cuda.synchronize()
+    assert torch.equal(c, g)
+    ref = P.from_lib_dof(f.cpu().numpy()[:P.N])
+    assert rel_err_cols(P.ops.M @ P.from_lib_dof(c.cpu().numpy()), ref) < 1e-10
+
+
 @pytest.mark.parametrize("copies", [1, 2])
 def test_arnoldi_second_pass(copies):
     """A start vector near an eigenvector of G: the first Gram-Schmidt pass
