@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(NT) k_mg_fill(const MgLevelDev* __restrict__ l
 // are requested together; a thread takes a column of a cell, or (SPLIT) of one of
 // its planes.  Rows -> cells, Q2 to
 // Q3 and Q1 to Q2 together: H2O (1.5 M and 429,000 fine rows x 64 columns) 1333 ->
-// 882 us (by planes 1066), 16 H2 (4 columns) 136 -> 68 us by planes (85 by cells).
+// 943 us (by planes 1066), 16 H2 (4 columns) 136 -> 68 us by planes (85 by cells).
 struct InterpTable {
   double B[12];
 };
