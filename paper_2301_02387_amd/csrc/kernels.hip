@@ -480,7 +480,6 @@ __global__ void __launch_bounds__(NT) k_xgram_small(const DevMesh* __restrict__ 
   }
 }
 
-// out[i][o] = sum_b part[i][b][o]; one workgroup per (output, instance)
 // out[o] = sum over nblk partials [nblk][nout] (per instance): cw consecutive
 // outputs per workgroup, its NT / cw slices of the partials summed in turn (eight
 // loads in flight) and folded in LDS, so that a partial's outputs are read in
@@ -1607,7 +1606,6 @@ __global__ void __launch_bounds__(NT) k_moments_mfma(const DevMesh* __restrict__
   }
 }
 
-// out[i][o] = sum_b part[i][b][o]; one workgroup per (output, instance)
 // W[NE + b][c] = sum_t table[b][t] Q[t][c]
 __global__ void k_bnd_eval(const DevMesh* __restrict__ dm, int nh, const double* __restrict__ Q, int ncol,
                            double* __restrict__ W) {
