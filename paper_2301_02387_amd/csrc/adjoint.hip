@@ -504,7 +504,7 @@ __global__ void __launch_bounds__(NT) k_colsq(const DevMesh* __restrict__ dm, co
   double s = 0.0;
   for (int64_t k = threadIdx.x; k < d.N; k += NT) s += y[k * ncol + c] * y[k * ncol + c];
   s = block_sum_all(s, lds4);
-  if (threadIdx.x == 0) sc[(int64_t)blockIdx.y * 8 * ncol + SC_BB * ncol + c] = s;
+  if (threadIdx.x == 0) sc[(int64_t)blockIdx.y * SC_SLOTS * ncol + SC_BB * ncol + c] = s;
 }
 void launch_adj_poisson_rhs(const Batch& b, const double* Kw, int ncol, double* y, double* sc, hipStream_t s) {
   hipLaunchKernelGGL(k_ctrans_real, dim3(nblocks(b.mx.N * ncol, NT, 8192), b.ni), dim3(NT), 0, s, b.dm, Kw, ncol, y);

@@ -117,7 +117,6 @@ struct mh_op {
   int* flag = nullptr;      // [ni]
   // multigrid preconditioner of the Poisson solves (built on first use)
   std::unique_ptr<MgDev> mg;
-  double* mg_red = nullptr;   // scratch accumulators of the level-0 operator passes
   int* cg_done = nullptr;     // [ni] convergence flags of a batch's multigrid CG (zero outside it)
   double* mg_part = nullptr;  // r.z partials
   int mg_levels = 0;
@@ -669,7 +668,7 @@ static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_de
   op->pmat = op->alloc<double>(ni * 2 * nn);
   op->obs = op->alloc<double>(ni * 8);
   op->Rinv = op->alloc<double>(ni * 2 * nn);
-  op->hostpin_len = (size_t)ni * std::max((8 + RED_SLOTS) * ncol, 64) + 4096;
+  op->hostpin_len = (size_t)ni * std::max((SC_SLOTS + RED_SLOTS) * ncol, 64) + 4096;
   HIPCHK(hipHostMalloc((void**)&op->hostpin, op->hostpin_len * sizeof(double), hipHostMallocDefault));
   // Poisson workspaces
   PoissonWs& P = op->P;
@@ -683,12 +682,12 @@ static mh_op* create_batch(const std::vector<InstanceSpec>& spec, const mh_op_de
   P.w = op->alloc<double>(tE * ncol);
   P.r = op->alloc<double>(tE * ncol);
   P.q = op->alloc<double>(tE * ncol);
-  P.sc = op->alloc<double>((size_t)ni * 8 * ncol);
-  launch_zero(P.sc, (size_t)ni * 8 * ncol, s);
+  P.sc = op->alloc<double>((size_t)ni * SC_SLOTS * ncol);
+  launch_zero(P.sc, (size_t)ni * SC_SLOTS * ncol, s);
   P.red = op->alloc<double>((size_t)ni * RED_SLOTS * ncol);
   launch_zero(P.red, (size_t)ni * RED_SLOTS * ncol, s);
   if (ni == 1) {  // the largest operator-pass grid (65,536 sweeping and up to 2,056 long-row workgroups)
-    B.spart_cap = (int64_t)(65536 + 4096) * std::max(ncol, 2 * n);
+    B.spart_cap = (int64_t)(65536 + 4096) * ncol;
     B.spart = op->alloc<double>((size_t)(B.spart_cap + SPART_RZ));
   }
   P.part_stride = (int64_t)8192 * 2 * ncol;
@@ -879,14 +878,14 @@ static void poisson_begin(mh_op* op, const double* phi, double* W, int warm, hip
 static int poisson_converged(mh_op* op, hipStream_t s) {
   const int ncol = op->ncol, ni = op->ni;
   double* hs = op->hostpin;
-  double* hr = hs + (size_t)ni * 8 * ncol;
-  HIPCHK(hipMemcpyAsync(hs, op->P.sc, (size_t)ni * 8 * ncol * sizeof(double), hipMemcpyDeviceToHost, s));
+  double* hr = hs + (size_t)ni * SC_SLOTS * ncol;
+  HIPCHK(hipMemcpyAsync(hs, op->P.sc, (size_t)ni * SC_SLOTS * ncol * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(hr, op->P.red, (size_t)ni * RED_SLOTS * ncol * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   const int rr_slot = op->P.it > 0 ? red_rr_slot(op->P.it) : -1;
   int conv = 1;
   for (int i = 0; i < ni; ++i) {
-    const double* sc = hs + (size_t)i * 8 * ncol;
+    const double* sc = hs + (size_t)i * SC_SLOTS * ncol;
     const double* rd = hr + (size_t)i * RED_SLOTS * ncol;
     double bb = 0.0;
     for (int c = 0; c < ncol; ++c) bb = std::max(bb, sc[SC_BB * ncol + c]);
@@ -987,7 +986,6 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
       MgLevelDev& L = rec[l][i];
       L.N = h.N;
       L.active = l + 1 < nl;
-      L.coarse = l + 1 == nl;
       if (l == 0) {
         L.a_ptr = dh.kt_ptr;
         L.a_col = dh.kt_col;
@@ -997,7 +995,6 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
         L.z = mg->z0 + off;
         L.t = mg->t0 + off;
         L.d = d0 + off;
-        L.rf = mg->rf + off;
         L.zf = mg->z0f + off;
         L.tf = mg->t0f + off;
       } else {
@@ -1071,7 +1068,6 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
   for (MgLevelDev& L : rec[0]) L.f32 = 1;
   mg->lv0_float = op->upload(rec[0], s);
   mg->coarse = op->upload(co, s);
-  op->mg_red = op->alloc<double>((size_t)ni * RED_SLOTS * ncol);
   op->mg_part = op->alloc<double>((size_t)ni * MG_RZ_BLOCKS * ncol);
   HIPCHK(hipStreamSynchronize(s));  // the host tables are temporaries
   op->mg_levels = nlev;
@@ -1115,7 +1111,7 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
   int zc = 0;
   MgLevel0Ops ops;
   if (f32) {
-    ops.resid = [&](hipStream_t st) { launch_mg_resid_f(B, mg.z0f, mg.rf, mg.t0f, ncol, op->mg_red, st); };
+    ops.resid = [&](hipStream_t st) { launch_mg_resid_f(B, mg.z0f, mg.rf, mg.t0f, ncol, st); };
     ops.cheb0 = [&](hipStream_t st) {
       zc = nu % 2;
       launch_mg_cheb0_f(B, mg.rf, zc ? mg.z0bf : mg.z0f, mg.d0f, P.red, rz_slot | (nu > 2 ? 0 : 256), ncol, st);
@@ -1127,7 +1123,7 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
       rz_rows = launch_mg_cheb_step_f(B, zi, mg.rf, zo, mg.d0f, P.red, ncol, k, rz ? rz_slot : -1, st);
     };
   } else {
-    ops.resid = [&](hipStream_t st) { launch_mg_resid(B, mg.z0, P.r, mg.t0, ncol, op->mg_red, st); };
+    ops.resid = [&](hipStream_t st) { launch_mg_resid(B, mg.z0, P.r, mg.t0, ncol, st); };
     ops.cheb0 = [&](hipStream_t st) {
       zc = nu % 2;
       launch_mg_cheb0(B, P.r, zc ? mg.z0b : mg.z0, mg.d0, P.red, rz_slot | (nu > 2 ? 0 : 256), ncol, st);

@@ -1160,7 +1160,6 @@ __global__ void __launch_bounds__(KT) k_orth_scale(const DevMesh* __restrict__ d
     if (!single && threadIdx.x < (unsigned)(nv - 1)) ((double*)H)[threadIdx.x] += hs[threadIdx.x];
     if (threadIdx.x == 0) {
       H[k + 1] = make_double2(hn, 0.0);
-      scal[1] = sc;
       if (brk && scal[4] > k + 1) scal[4] = k + 1;
     }
   }
@@ -1258,7 +1257,6 @@ __global__ void __launch_bounds__(KT) k_krylov_start(const DevMesh* __restrict__
     if (threadIdx.x == 0) {
       scal += 8 * i;
       scal[0] = beta;
-      scal[5] = ib;
       scal[4] = m;
       scal[3] = 0.0;
     }
@@ -1765,7 +1763,7 @@ __global__ void __launch_bounds__(NT) k_col_sum(const double* __restrict__ part,
   __shared__ double lds4[4];
   const int c = blockIdx.x;
   const double s = sum_partials(part + blockIdx.y * part_stride, nblk, ncol, c, lds4);
-  if (threadIdx.x == 0) sc[(int64_t)blockIdx.y * 8 * ncol + slot * ncol + c] = s;
+  if (threadIdx.x == 0) sc[(int64_t)blockIdx.y * SC_SLOTS * ncol + slot * ncol + c] = s;
 }
 
 static int rhs_blocks(const Batch& b, int ncol) { return nblocks(b.mx.N, NT / ncol, 1024); }

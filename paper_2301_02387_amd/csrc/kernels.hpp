@@ -196,7 +196,7 @@ void launch_build_U_full(const Batch& b, const double* W, const double* Gamma, c
 struct Krylov {
   int m_max = 0;
   double* H = nullptr;       // device c128 [ni][(m_max+1) x m_max], H[i + (m_max+1) j]
-  double* scal = nullptr;    // [ni][8]: [0]=beta [1]=last scale [2]=|w|^2 [3]=err [4]=m_eff [5]=1/beta [6]=one pass was enough
+  double* scal = nullptr;    // [ni][8]: [0]=beta [2]=|w|^2 [3]=err [4]=m_eff [6]=one pass was enough
   double* y = nullptr;       // device c128 [ni][m_max]
   double* part = nullptr;    // partial sums of the first and second pass [ni][value][nblk]
   double* part2 = nullptr;
@@ -225,7 +225,7 @@ struct PoissonWs {
   double* w = nullptr;     // [tE][ncol] K z
   double* r = nullptr;     // [tE][ncol]
   double* q = nullptr;     // [tE][ncol]
-  double* sc = nullptr;    // [ni][8][ncol] scalars
+  double* sc = nullptr;    // [ni][SC_SLOTS][ncol] scalars
   double* red = nullptr;   // [ni][RED_SLOTS][ncol] atomic accumulators (RED_*; see stencil.hip)
   int it = 0;              // CG iteration within the running solve
   double* part = nullptr;  // partials [ni][grid][2 ncol]
@@ -238,7 +238,8 @@ struct PoissonWs {
   hipEvent_t* ev = nullptr;
   int ev_cap = 0, ev_used = 0;
 };
-enum { SC_RZ = 0, SC_PQ = 1, SC_ALPHA = 2, SC_BETA = 3, SC_RR = 4, SC_BB = 5, SC_RZN = 6 };
+// r.r of the start and b.b
+enum { SC_RR = 0, SC_BB = 1, SC_SLOTS = 2 };
 // accumulator slots: r.z of iteration k in RED_RZ + k % 3, z.w in RED_PQ + k % 2,
 // r.r after iteration k in RED_RR + k % 2, p.q in RED_ETA + k % 2
 enum { RED_RZ = 0, RED_PQ = 3, RED_RR = 5, RED_ETA = 7, RED_SLOTS = 9 };
@@ -253,14 +254,14 @@ void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int
 void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s);
 // One iteration with another preconditioner: the operator pass on the
 // preconditioned residual z and the vector pass.  rz_rows: partial sums of r.z
-// left by launch_mg_cheb_step (0: r.z is in slot RED_RZ + k % 3).
+// left by launch_mg_cheb_step (0: r.z is in slot RED_RZ + k % 3).  rf (may be
+// null): a float copy of the updated residual (Poisson schedule bit 6).
 void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const double* z, float* rf, int rz_rows, int k,
                          hipStream_t s);
 void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const float* z, float* rf, int rz_rows, int k,
                          hipStream_t s);
 // After the last of `it` iterations: the solution update that is still open.
 void launch_cg_finish(const Batch& b, double* W, PoissonWs& P, int it, hipStream_t s);
-// rf (may be null): a float copy of the updated residual (Poisson schedule bit 6)
 // Batch CG convergence flags (DevMesh::cg_done, device int [ni]): set an
 // instance's flag once every column's r.r after iteration k is at most
 // rtol^2 times its largest column's b.b; clear all flags.
@@ -281,17 +282,14 @@ void launch_mg_cheb0(const Batch& b, const double* r, double* z, double* d, doub
                      hipStream_t s);
 int launch_mg_cheb_step(const Batch& b, const double* zin, const double* r, double* zout, double* d, double* red,
                          int ncol, int k, int rz_slot, hipStream_t s);
-//  - the residual t = r - K z that the restriction to the next level reads
-//    (red_scratch: accumulators the pass may touch, not the CG's).
-void launch_mg_resid(const Batch& b, const double* z, const double* r, double* t, int ncol, double* red_scratch,
-                     hipStream_t s);
+//  - the residual t = r - K z that the restriction to the next level reads.
+void launch_mg_resid(const Batch& b, const double* z, const double* r, double* t, int ncol, hipStream_t s);
 // Poisson schedule bit 6: the finest multigrid level's passes on float arrays
 void launch_mg_cheb0_f(const Batch& b, const float* r, float* z, float* d, double* red, int rz_slot, int ncol,
                        hipStream_t s);
 int launch_mg_cheb_step_f(const Batch& b, const float* zin, const float* r, float* zout, float* d, double* red,
                            int ncol, int k, int rz_slot, hipStream_t s);
-void launch_mg_resid_f(const Batch& b, const float* z, const float* r, float* t, int ncol, double* red_scratch,
-                       hipStream_t s);
+void launch_mg_resid_f(const Batch& b, const float* z, const float* r, float* t, int ncol, hipStream_t s);
 // Hanging rows of a real column array (xfull: x is over full rows, else extended).
 void launch_fill_real(const Batch& b, double* x, int xfull, int ncol, int with_bnd, double* acc, hipStream_t s);
 

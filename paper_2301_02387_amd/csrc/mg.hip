@@ -19,14 +19,12 @@ namespace mh {
 
 #define INSTANCE const DevMesh& d = dm[blockIdx.y]
 
-// sum of val[t] (x[col[t] ncol + c] - xm[col[t] ncol + c]) (SUB; else x alone)
-// over t = beg, beg + stride, ... < end, for end > beg.  Rounds of 8 entries:
+// sum of val[t] x[col[t] ncol + c] over t = beg, beg + stride, ... < end, for end > beg.  Rounds of 8 entries:
 // the indices and coefficients of the next round are requested before this
 // round's gathers, so each round waits for one memory latency.  Entries past
 // the end repeat the last one with coefficient 0 (in-bounds loads, no branch).
-template <bool SUB, class IP, class DP, class XP>
-__device__ __forceinline__ double row_gather_dot(IP col, DP val, int beg, int end, int stride, XP x, XP xm, int ncol,
-                                                 int c) {
+template <class IP, class DP, class XP>
+__device__ __forceinline__ double row_gather_dot(IP col, DP val, int beg, int end, int stride, XP x, int ncol, int c) {
   double s = 0.0;
   int jn[8];
   double an[8];
@@ -57,7 +55,7 @@ __device__ __forceinline__ double row_gather_dot(IP col, DP val, int beg, int en
 #pragma unroll
     for (int h = 0; h < 8; ++h) {
       const int64_t j = (int64_t)jc[h] * ncol + c;
-      s += ac[h] * (SUB ? (double)x[j] - (double)xm[j] : (double)x[j]);
+      s += ac[h] * (double)x[j];
     }
   }
   return s;
@@ -65,9 +63,9 @@ __device__ __forceinline__ double row_gather_dot(IP col, DP val, int beg, int en
 
 // The same with V adjacent columns per lane (c0 .. c0 + V, 16-byte loads;
 // ncol and c0 multiples of V): s[v] += the entries' sum for column c0 + v.
-template <int V, bool SUB, class IP, class DP, class XP>
-__device__ __forceinline__ void row_gather_v(IP col, DP val, int beg, int end, int stride, XP x, XP xm, int ncol,
-                                             int c0, double* s) {
+template <int V, class IP, class DP, class XP>
+__device__ __forceinline__ void row_gather_v(IP col, DP val, int beg, int end, int stride, XP x, int ncol, int c0,
+                                             double* s) {
   int jn[8];
   double an[8];
 #pragma unroll
@@ -96,15 +94,7 @@ __device__ __forceinline__ void row_gather_v(IP col, DP val, int beg, int end, i
     }
     double xv[8][V];
 #pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      load_vals<V>(x + (int64_t)jc[h] * ncol + c0, xv[h]);
-      if constexpr (SUB) {
-        double mv[V];
-        load_vals<V>(xm + (int64_t)jc[h] * ncol + c0, mv);
-#pragma unroll
-        for (int v = 0; v < V; ++v) xv[h][v] -= mv[v];
-      }
-    }
+    for (int h = 0; h < 8; ++h) load_vals<V>(x + (int64_t)jc[h] * ncol + c0, xv[h]);
 #pragma unroll
     for (int h = 0; h < 8; ++h)
 #pragma unroll
@@ -137,8 +127,8 @@ __global__ void __launch_bounds__(NT) k_mg_restrict(const MgLevelDev* __restrict
     if (c < ncol) {
       const int beg = ptr[w] + grp, end = ptr[w + 1];
       if (end > beg)
-        s = f32 ? row_gather_dot<false>(col, val, beg, end, ngrp, tf, tf, ncol, c)
-                : row_gather_dot<false>(col, val, beg, end, ngrp, t, t, ncol, c);
+        s = f32 ? row_gather_dot(col, val, beg, end, ngrp, tf, ncol, c)
+                : row_gather_dot(col, val, beg, end, ngrp, t, ncol, c);
     }
     for (int off = G / 2; off >= cw; off >>= 1) s += __shfl_xor(s, off, 64);
     if (grp == 0 && c < ncol) y[w * ncol + c] = s;
@@ -171,8 +161,8 @@ __global__ void __launch_bounds__(NT) k_mg_restrict_v(const MgLevelDev* __restri
     for (int v = 0; v < V; ++v) s[v] = 0.0;
     const int beg = ptr[w] + grp, end = ptr[w + 1];
     if (act && end > beg) {
-      if (f32) row_gather_v<V, false>(col, val, beg, end, ngrp, tf, tf, ncol, c0, s);
-      else row_gather_v<V, false>(col, val, beg, end, ngrp, t, t, ncol, c0, s);
+      if (f32) row_gather_v<V>(col, val, beg, end, ngrp, tf, ncol, c0, s);
+      else row_gather_v<V>(col, val, beg, end, ngrp, t, ncol, c0, s);
     }
     for (int off = 32; off >= cw; off >>= 1)
 #pragma unroll
@@ -207,7 +197,7 @@ __global__ void __launch_bounds__(NT) k_mg_prolong_v(const MgLevelDev* __restric
     double s[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) s[v] = 0.0;
-    row_gather_v<V, false>(col, val, beg, end, 1, x, x, ncol, c0, s);
+    row_gather_v<V>(col, val, beg, end, 1, x, ncol, c0, s);
     const int64_t e = i * ncol + c0;
     double zo[V];
     if (f32) {
@@ -241,7 +231,7 @@ __global__ void __launch_bounds__(NT) k_mg_prolong(const MgLevelDev* __restrict_
     const int c = (int)(e - i * ncol);
     const int beg = ptr[i], end = ptr[i + 1];
     if (end > beg) {
-      const double v = row_gather_dot<false>(col, val, beg, end, 1, x, x, ncol, c);
+      const double v = row_gather_dot(col, val, beg, end, 1, x, ncol, c);
       if (f32) zf[e] = (float)((double)zf[e] + v);
       else z[e] += v;
     }
@@ -365,7 +355,7 @@ __global__ void __launch_bounds__(NT) k_mg_level_pass(const MgLevelDev* __restri
       if constexpr (MODE == LP_STEP1) load_vals<V>((const __attribute__((address_space(1))) double*)dd + e, dv);
       if (MODE != LP_RES) di = dinv[i];
       const int beg = ptr[i] + grp, end = ptr[i + 1];
-      if (end > beg) row_gather_v<V, false>(col, val, beg, end, ngrp, x, x, ncol, col0, y);
+      if (end > beg) row_gather_v<V>(col, val, beg, end, ngrp, x, ncol, col0, y);
     }
     if constexpr (V == 1)
       for (int off = LN / 2; off >= cw; off >>= 1) y[0] += __shfl_xor(y[0], off, 64);
@@ -443,7 +433,7 @@ __global__ void __launch_bounds__(NT) k_mg_fill(const MgLevelDev* __restrict__ l
   for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
     const int64_t h = e / ncol;
     const int c = (int)(e - h * ncol), beg = ptr[h], end = ptr[h + 1];
-    gblw(L.z)[L.N * ncol + e] = end > beg ? row_gather_dot<false>(gbl(L.h_col), gbl(L.h_w), beg, end, 1, z, z, ncol, c) : 0.0;
+    gblw(L.z)[L.N * ncol + e] = end > beg ? row_gather_dot(gbl(L.h_col), gbl(L.h_w), beg, end, 1, z, ncol, c) : 0.0;
   }
 }
 

@@ -16,11 +16,10 @@ constexpr double MG_RANGE = 8.0;
 constexpr int MG_RZ_BLOCKS = 256;
 
 // One level of one instance.  `active`: smoothing and transfers run on this
-// level (it is not the instance's coarsest); `coarse`: the level is the
-// instance's coarsest, solved with the dense inverse cinv.
+// level; the instance's coarsest, solved with the dense inverse cinv, is not.
 struct MgLevelDev {
   int64_t N = 0;                                                   // unknowns of the level
-  int active = 0, coarse = 0;
+  int active = 0;
   const int32_t* a_ptr = nullptr; const int32_t* a_col = nullptr;   // operator (CSR)
   const double* a_val = nullptr;
   const double* a_vd = nullptr;                                    // levels from 1 on: values times 1 / diagonal of the column
@@ -42,11 +41,10 @@ struct MgLevelDev {
   double* z = nullptr;   // correction
   double* d = nullptr;   // Chebyshev direction
   double* t = nullptr;   // operator product scratch
-  // level 0 on float storage (Poisson schedule bit 6): the residual copy, the
-  // correction and the operator product the transfers read and write
+  // level 0 on float storage (Poisson schedule bit 6): the correction and the
+  // residual that the transfers read and write
   int f32 = 0;
   const int* done = nullptr;  // the instance's CG convergence flag (nonzero: skip)
-  const float* rf = nullptr;
   float* zf = nullptr;
   float* tf = nullptr;
 };

@@ -439,19 +439,19 @@ void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma
 // NT / L lane groups splitting the entries and an LDS reduction; the other
 // workgroups sweep the remaining rows.
 // --------------------------------------------------------------------------
-// Operator pass modes: plain q = K x (SP_PLAIN); the CG's operator pass on the
-// preconditioned residual (SP_CG: z given, SP_CGJ: z = D^-1 r formed on the
-// fly); and the two Chebyshev smoothing passes of the multigrid
-// cycle on the finest level, which replace q by the smoother's update:
+// Operator pass modes: the CG's operator pass on the preconditioned residual
+// (SP_CG: z given, SP_CGJ: z = D^-1 r formed on the fly); the residual r - K x
+// (SP_RES: of a CG start, and the one that the restriction to the next
+// multigrid level reads); and the Chebyshev smoothing passes of the multigrid
+// cycle on the finest level:
 // SP_CHEB0 runs the first two steps from z = 0 (its operand s0 D^-1 r is
 // formed on the fly), SP_CHEB runs one step on a given z into another array.
 // SP_CHEB_RZ is the second SP_CHEB step with r.z accumulated for the
-// multigrid-preconditioned CG.  SP_RES writes the residual r - K z that the
-// restriction to the next multigrid level reads.
-enum { SP_PLAIN = 0, SP_CG = 1, SP_CHEB0 = 2, SP_CHEB = 3, SP_CHEB_RZ = 4, SP_RES = 5, SP_CGJ = 6 };
+// multigrid-preconditioned CG.
+enum { SP_CG = 1, SP_CHEB0 = 2, SP_CHEB = 3, SP_CHEB_RZ = 4, SP_RES = 5, SP_CGJ = 6 };
 
 // Arrays of a pass beside its operand: w = K z of the CG's pass, double
-// whatever z is; full: the operand of SP_PLAIN or SP_RES is over full rows.
+// whatever z is; full: the operand of SP_RES is over full rows.
 struct PassExtra {
   double* w;
   int full;
@@ -511,8 +511,7 @@ __device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restr
   }
 }
 
-// Row i done, y = (K operand)_i.  SP_PLAIN: q_i = y.  SP_CG, SP_CGJ: w_i = y
-// and the z.w partial.
+// Row i done, y = (K operand)_i.  SP_CG, SP_CGJ: w_i = y and the z.w partial.
 // Chebyshev passes (x: the operand's source, pprev = r, pout = z out, q = d,
 // cf = the instance's coefficients s0, c1, c2; step k of SP_CHEB, step 1 for
 // SP_CHEB_RZ):
@@ -530,13 +529,9 @@ __device__ __forceinline__ void spmv_store(const DevMesh& d, T* __restrict__ q, 
                                            const double* beta, int64_t i, int ld, int c0, const double* y,
                                            double* pq, const double* cf, int k, const PassExtra& ex) {
   const auto* dinv = gbl(d.kdiag_inv);
-  if constexpr (MODE == SP_PLAIN) {
-    T* qo = q + i * ld + c0;
-#pragma unroll
-    for (int v = 0; v < V; ++v) qo[v] = (T)y[v];
-  } else if constexpr (MODE == SP_RES) {
+  if constexpr (MODE == SP_RES) {
     double rv[V];
-    operand_row<V, SP_PLAIN, T>(gbl(pprev), dinv, beta, i, ld, c0, rv);
+    load_vals<V>(gbl(pprev) + i * ld + c0, rv);
     T* qo = q + i * ld + c0;
 #pragma unroll
     for (int v = 0; v < V; ++v) qo[v] = (T)(rv[v] - y[v]);
@@ -544,10 +539,10 @@ __device__ __forceinline__ void spmv_store(const DevMesh& d, T* __restrict__ q, 
     const int step = MODE == SP_CHEB_RZ ? k >> 4 : k;
     const double di = dinv[i];
     double rv[V], xv[V], dv[V];
-    operand_row<V, SP_PLAIN, T>(gbl(pprev), dinv, beta, i, ld, c0, rv);
+    load_vals<V>(gbl(pprev) + i * ld + c0, rv);
     if constexpr (MODE != SP_CHEB0) {
-      operand_row<V, SP_PLAIN, T>(gbl(x), dinv, beta, i, ld, c0, xv);
-      if (step > 0) operand_row<V, SP_PLAIN, T>(gbl((const T*)q), dinv, beta, i, ld, c0, dv);
+      load_vals<V>(gbl(x) + i * ld + c0, xv);
+      if (step > 0) load_vals<V>(gbl((const T*)q) + i * ld + c0, dv);
     }
     T* qo = q + i * ld + c0;
     T* po = pout + i * ld + c0;
@@ -642,7 +637,7 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
   // one workgroup per column block clears the slots below (workgroup 0 of the
   // block's z slice; with bit 7 workgroups 0 .. nb_col - 1, one per block)
   const bool first_wg = aff ? (int)blockIdx.x < nb_col : blockIdx.x == 0;
-  x += ((MODE == SP_PLAIN || MODE == SP_RES) && ex.full ? d.oF : d.oE) * ld + col0;
+  x += (MODE == SP_RES && ex.full ? d.oF : d.oE) * ld + col0;
   q += d.oE * ld + col0;
   pprev += d.oE * ld + col0;
   pout += d.oE * ld + col0;
@@ -739,7 +734,7 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
       spmv_store<V, MODE, T>(d, q, pout, x, pprev, beta, i, ld, c0, y, pq, cf, k, ex);
     }
   }
-  if constexpr (MODE == SP_PLAIN || MODE == SP_CHEB0 || MODE == SP_CHEB || MODE == SP_RES) {
+  if constexpr (MODE == SP_CHEB0 || MODE == SP_CHEB || MODE == SP_RES) {
     if (MODE == SP_CHEB0 && first_wg && threadIdx.x < (unsigned)nc) red[(k & 255) * ld + threadIdx.x] = 0.0;
     return;
   }
@@ -891,7 +886,8 @@ static PassExtra no_extra(int full = 0) { return PassExtra{nullptr, full}; }
 
 // --------------------------------------------------------------------------
 // Jacobi-preconditioned CG, all columns of all instances at once with their
-// own alpha and beta.  Scalars sc[i][slot][c] (SC_* in kernels.hpp).
+// own alpha and beta.  Scalars sc[i][slot][c] (SC_*) and red[i][slot][c] (RED_*)
+// in kernels.hpp.
 // --------------------------------------------------------------------------
 // One CG iteration is two launches beside its preconditioner: the operator
 // pass, w = K z with z.w, and the vector pass,
@@ -1017,14 +1013,13 @@ __global__ void __launch_bounds__(NT) k_rz_start(const double* __restrict__ part
   __shared__ double lds4[4];
   const int c = blockIdx.x;
   part += blockIdx.y * part_stride;
-  sc += (int64_t)blockIdx.y * 8 * ncol;
+  sc += (int64_t)blockIdx.y * SC_SLOTS * ncol;
   red += (int64_t)blockIdx.y * RED_SLOTS * ncol;
   const double s = sum_partials(part, nblk, 2 * ncol, c, lds4);
   const double u = sum_partials(part, nblk, 2 * ncol, ncol + c, lds4);
   if (threadIdx.x == 0) {
     for (int slot = 0; slot < RED_SLOTS; ++slot) red[slot * ncol + c] = 0.0;
     red[RED_RZ * ncol + c] = s;
-    sc[SC_RZ * ncol + c] = s;
     sc[SC_RR * ncol + c] = u;
   }
 }
@@ -1140,13 +1135,11 @@ void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int
 // pass (the spmv_store comment gives the updates): the first two steps from
 // zero (z, d from r), and one further step from zin into zout.
 // t = r - K z on the finest level (the residual the restriction reads)
-void launch_mg_resid(const Batch& b, const double* z, const double* r, double* t, int ncol, double* red_scratch,
-                     hipStream_t s) {
-  launch_spmv_mode(b, z, r, t, ncol, t, red_scratch, SP_RES, -1, s, no_extra());
+void launch_mg_resid(const Batch& b, const double* z, const double* r, double* t, int ncol, hipStream_t s) {
+  launch_spmv_mode<double>(b, z, r, t, ncol, t, nullptr, SP_RES, -1, s, no_extra());
 }
-void launch_mg_resid_f(const Batch& b, const float* z, const float* r, float* t, int ncol, double* red_scratch,
-                       hipStream_t s) {
-  launch_spmv_mode<float>(b, z, r, t, ncol, t, red_scratch, SP_RES, -1, s, no_extra());
+void launch_mg_resid_f(const Batch& b, const float* z, const float* r, float* t, int ncol, hipStream_t s) {
+  launch_spmv_mode<float>(b, z, r, t, ncol, t, nullptr, SP_RES, -1, s, no_extra());
 }
 void launch_mg_cheb0(const Batch& b, const double* r, double* z, double* d, double* red, int rz_slot, int ncol,
                      hipStream_t s) {
@@ -1185,7 +1178,7 @@ __global__ void k_cg_done(const DevMesh* __restrict__ dm, const double* __restri
                           int ncol, int k, double rtol2) {
   INSTANCE;
   if (!d.cg_done || *d.cg_done) return;
-  sc += (int64_t)blockIdx.y * 8 * ncol;
+  sc += (int64_t)blockIdx.y * SC_SLOTS * ncol;
   red += (int64_t)blockIdx.y * RED_SLOTS * ncol;
   const int c = threadIdx.x;
   double bb = c < ncol ? sc[SC_BB * ncol + c] : 0.0;
