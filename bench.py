@@ -71,16 +71,19 @@ def stored_matrix_bytes(N, nnz, n_inst):
     return 12 * nnz + 4 * (N + n_inst)
 
 
-def poisson_algorithmic_bytes(info, op, float_operand=False):
+def poisson_algorithmic_bytes(info, op, float_operand=False, warm_share=0.0):
     """Matrix-free bytes of one Poisson operator application on the pair
     columns (the Laplacian applied cell by cell from the 1D Gauss-Lobatto
     tables): operand rows read and result rows written once (8 B per column
     each; 4 B for the operand where the finest multigrid level keeps floats,
     schedule bits 4 and 6), the cell->node maps (int32), the hanging-node
-    constraint rows (int32 index + weight) and h per cell."""
+    constraint rows (int32 index + weight) and h per cell.  warm_share: the
+    share of the launches that form the residual of a warm start, which read
+    the right-hand side too (three double rows)."""
     P3 = (info["p"] + 1) ** 3
     N, ncol, nC = op.n_dof, op.n_pair_cols, info["n_cells"]
-    return (12 if float_operand else 16) * ncol * N + 4 * P3 * nC + 12 * info["hang_nnz"] + 8 * nC
+    row = (1.0 - warm_share) * (12 if float_operand else 16) + warm_share * 24
+    return row * ncol * N + 4 * P3 * nC + 12 * info["hang_nnz"] + 8 * nC
 
 
 def rhs_algorithmic_bytes(info, op, ecs=False):
@@ -313,7 +316,8 @@ def run_single(name, args, torch, with_adjoint, with_cpu):
             "poisson_spmv": {"avg_ms": k_poi[0], "count": k_poi[1]}}
     dom = max(kern, key=lambda k: kern[k]["avg_ms"] * kern[k]["count"])
     if dom == "poisson_spmv":
-        byts = poisson_algorithmic_bytes(info, op, (sched["poisson"][0] & 80) == 80)
+        # one warm start per step
+        byts = poisson_algorithmic_bytes(info, op, (sched["poisson"][0] & 80) == 80, args.steps / k_poi[1])
         over = stored_matrix_bytes(op.n_dof, op.n_poisson_nnz, op.n_inst)
     else:
         byts, over = orbital_pass_bytes(info, op, bool(ecs)), 0
@@ -687,7 +691,7 @@ def run_batch(args):
     # matrix-free bytes summed over the instances (one aggregate mesh record)
     agg = {"p": w0["p"], "n_cells": n_cells, "hang_nnz": sum(mm.info["hang_nnz"] for mm in meshes),
            "n_full": sum(mm.info["n_full"] for mm in meshes)}
-    spmv_b = poisson_algorithmic_bytes(agg, op, (sched["poisson"][0] & 80) == 80)
+    spmv_b = poisson_algorithmic_bytes(agg, op, (sched["poisson"][0] & 80) == 80, args.steps / max(k_poi[1], args.steps))
     spmv_over = stored_matrix_bytes(op.n_dof, op.n_poisson_nnz, op.n_inst)
     P3 = (w0["p"] + 1) ** 3
     NE, N, n = op.n_ext, op.n_dof, op.n_orb

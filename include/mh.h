@@ -401,7 +401,9 @@ int mh_batch_layout(const mh_op* op, int64_t* layout);
  * over its launches since the last call, from HIP event pairs recorded on
  * the launch stream around each launch (no synchronisation while
  * recording; at most 4096 launches are recorded).  which: 0 = orbital
- * operator kernel (one-body + mean field), 1 = Poisson operator kernel.
+ * operator kernel (one-body + mean field), 1 = Poisson operator kernel (one
+ * launch per CG iteration, and one for the residual of a warm start; the
+ * multigrid preconditioner's own passes are not recorded).
  * enable: keep recording after this call.  Launches inside a captured
  * graph are not recorded.  Synchronises the device. */
 int mh_kernel_timing(mh_op* op, int32_t which, int32_t enable, double* avg_ms, int64_t* count);

@@ -1064,20 +1064,27 @@ static int cg_blocks(const Batch& b, int ncol) {
   return nblocks(b.mx.N, NT / ncol, (int)want);
 }
 
-// The CG's operator pass with optional event timing on the launch stream.
-template <class T>
-static int cg_pass(const Batch& b, PoissonWs& P, const T* z, int mode, int k, hipStream_t s) {
+// An operator pass of the CG (one per iteration, and the residual of a warm
+// start) with optional event timing on the launch stream.
+template <class F>
+static int timed_pass(PoissonWs& P, hipStream_t s, F&& pass) {
   const bool rec = P.ev && P.ev_used + 2 <= P.ev_cap;
   if (rec) {
     (void)hipEventRecord(P.ev[P.ev_used], s);
     t_pass_end = P.ev[P.ev_used + 1];
   }
-  const int rows = launch_spmv_mode<T>(b, z, z, nullptr, P.ncol, nullptr, P.red, mode, k, s, PassExtra{P.w, 0});
+  const int rows = pass();
   if (rec) {
     t_pass_end = nullptr;
     P.ev_used += 2;
   }
   return rows;
+}
+template <class T>
+static int cg_pass(const Batch& b, PoissonWs& P, const T* z, int mode, int k, hipStream_t s) {
+  return timed_pass(P, s, [&] {
+    return launch_spmv_mode<T>(b, z, z, nullptr, P.ncol, nullptr, P.red, mode, k, s, PassExtra{P.w, 0});
+  });
 }
 // How the solution update of iteration k is taken (k_cg_vectors).
 static int cg_xmode(const Batch& b, int k) { return b.ni > 1 ? 1 : (k % 2 ? 2 : 0); }
@@ -1124,7 +1131,10 @@ void launch_cg_finish(const Batch& b, double* W, PoissonWs& P, int it, hipStream
 void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int warm, hipStream_t s) {
   const int ncol = P.ncol;
   // warm: r = rhs - K x0, x0 = the DoF rows of W (full rows)
-  if (warm) launch_spmv_mode<double>(b, W, rhs_r, rhs_r, ncol, rhs_r, P.red, SP_RES, -1, s, no_extra(1));
+  if (warm)
+    timed_pass(P, s, [&] {
+      return launch_spmv_mode<double>(b, W, rhs_r, rhs_r, ncol, rhs_r, P.red, SP_RES, -1, s, no_extra(1));
+    });
   const int nb = cg_blocks(b, ncol);
   hipLaunchKernelGGL(k_cg_start2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, rhs_r, ncol, warm, P.part_stride, P.part);
   hipLaunchKernelGGL(k_rz_start, dim3(ncol, b.ni), dim3(NT), 0, s, P.part, P.part_stride, nb, ncol, P.sc, P.red);
