@@ -12,8 +12,9 @@ import json
 import os
 
 ORB_CANDIDATES = [(s, g) for s in (1, 0) for g in (2048, 8192, 65536)]
-POI_CANDIDATES = ([(s, g) for s in (13, 12, 5, 4, 9, 1, 45, 44, 37, 36) for g in (2048, 8192)]
-                  + [(s, 8192) for s in (21, 20, 29, 53, 52, 85, 84, 117, 116, 373, 372, 629, 628)])
+# Poisson bit 3 and orbital bit 2 are accepted and without effect: no candidate has them
+POI_CANDIDATES = ([(s, g) for s in (5, 4, 1, 37, 36) for g in (2048, 8192)]
+                  + [(s, 8192) for s in (21, 20, 53, 52, 85, 84, 117, 116, 373, 372, 629, 628)])
 # column blocking only changes anything at 32 or more columns (n >= 6 orbitals).
 # On such wide column sets a Jacobi-preconditioned solve from zero takes
 # seconds (about 1,000 iterations on the 1.5M-unknown water mesh, against
@@ -25,13 +26,13 @@ POI_CANDIDATES = ([(s, g) for s in (13, 12, 5, 4, 9, 1, 45, 44, 37, 36) for g in
 # XCD-contiguous (bit 0): without it the operator pass fetches 9.2 instead of
 # 6.7 GB per launch in the same time (the extra bytes come from the last-level
 # cache), and the tuner's short solves from zero do not tell the two apart.
-POI_CANDIDATES_WIDE = ([(13, 8192)]
+POI_CANDIDATES_WIDE = ([(5, 8192)]
                        + [(s, 8192) for s in (22, 20, 23, 21, 54, 52, 55, 53, 118, 116, 119, 117, 182, 214, 246,
                                                372, 628, 884)]
                        + [(s, g) for s in (117, 372, 373, 628) for g in (16384, 32768)])
 # grid caps are per instance: a batch fills the chip with fewer workgroups each
 ORB_CANDIDATES_BATCH = [(s, g) for s in (1, 0) for g in (256, 1024, 65536)]
-POI_CANDIDATES_BATCH = ([(s, g) for s in (13, 12, 5, 4, 1, 45, 37, 36) for g in (256, 1024)]
+POI_CANDIDATES_BATCH = ([(s, g) for s in (5, 4, 1, 37, 36) for g in (256, 1024)]
                         + [(s, g) for s in (21, 20, 53, 52, 117, 116) for g in (256, 1024)]
                         + [(s, 2048) for s in (117, 116)])
 _CACHE = {}
