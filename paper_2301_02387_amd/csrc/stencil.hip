@@ -605,7 +605,10 @@ __device__ __forceinline__ void fold_cols(const double* __restrict__ part, int r
 }
 // Largest number of partial sums that the launch that needs them folds itself:
 // each of its workgroups reads them (64 KB from L2), which costs less than a
-// launch; more are folded by k_fold_parts.
+// launch; more are folded by k_fold_parts.  64 iterations of a solve with the
+// bound at half, once, twice and four times this: 66,635 rows x 16 columns 3.35,
+// 3.32, 3.36 and 3.54 ms; 4,394 x 25 3.53, 3.54, 3.62 and 3.62; x 64 2.87, 2.87,
+// 2.87 and 3.08.
 constexpr int64_t FOLD_MAX = 8192;
 
 // Columns [col0, col0 + nc) of arrays with ld columns per row, col0 = blockIdx.z * nc
@@ -763,15 +766,27 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
 // dst[c] += sum over the rows workgroups w of part[w][c] (one instance): the
 // per-workgroup sums of an operator pass, added with a few hundred atomics
 // where the pass itself would issue one per workgroup and column, all on the
-// same nc addresses.
+// same nc addresses.  Bound by latency: eight loads in flight a thread (one after
+// the other: 280 sums x 36 columns 6.7 -> 2.9 us).
 __global__ void __launch_bounds__(NT) k_fold_parts(const double* __restrict__ part, int rows, int nc,
                                                    double* __restrict__ dst) {
   __shared__ double lds[NT];
-  const int per = NT / nc;
+  const int per = NT / nc, step = (int)gridDim.x * per;
   const int g = (int)threadIdx.x / nc, c = (int)threadIdx.x - g * nc;
+  const auto* pg = gbl(part);
   double s = 0.0;
   if (g < per)
-    for (int64_t w = (int64_t)blockIdx.x * per + g; w < rows; w += (int64_t)gridDim.x * per) s += part[w * nc + c];
+    for (int w = (int)blockIdx.x * per + g; w < rows; w += 8 * step) {
+      double t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int ww = w + u * step;
+        const double v = pg[(int64_t)(ww < rows ? ww : w) * nc + c];
+        t[u] = ww < rows ? v : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += t[u];
+    }
   lds[threadIdx.x] = s;
   col_tree(lds, per, nc);
   if (threadIdx.x < (unsigned)nc) atomicAdd(dst + threadIdx.x, lds[threadIdx.x]);
@@ -829,7 +844,7 @@ static int launch_spmv_m(const Batch& b, const T* x, const T* pprev, T* pout, in
   if (later) return gx;
   if (part) {
     const int slot = MODE == SP_CHEB_RZ ? (k & 15) : RED_PQ + k % 2;
-    const int fb = (int)std::max<int64_t>(1, std::min<int64_t>(256, (int64_t)gx / (NT / nc * 16)));
+    const int fb = (int)std::max<int64_t>(1, std::min<int64_t>(256, (int64_t)gx / (NT / nc * 8)));
     hipLaunchKernelGGL(k_fold_parts, dim3(fb), dim3(NT), 0, s, part, gx, nc, red + (int64_t)slot * ld);
   }
   return 0;
