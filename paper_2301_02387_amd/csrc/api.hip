@@ -916,13 +916,14 @@ static void ensure_mg(mh_op* op, hipStream_t s) {
   const int max_coarse = ni == 1 ? 2048 : 400;
   std::vector<MgHost> H(ni);
   {
-    const int nthr = std::max(1, std::min<int>(ni, std::min(16u, std::max(1u, std::thread::hardware_concurrency()))));
+    const int hw = (int)std::min(16u, std::max(1u, std::thread::hardware_concurrency()));
+    const int nthr = std::min(ni, hw), each = hw / nthr;   // instances in parallel, then the rows of each
     std::vector<std::thread> pool;
     std::vector<std::string> errs(nthr);
     for (int t = 0; t < nthr; ++t)
       pool.emplace_back([&, t]() {
         try {
-          for (int i = t; i < ni; i += nthr) build_multigrid(op->Ms[i], op->Hs[i], H[i], max_coarse);
+          for (int i = t; i < ni; i += nthr) build_multigrid(op->Ms[i], op->Hs[i], H[i], max_coarse, each);
         } catch (const std::exception& e) {
           errs[t] = e.what();
         }

@@ -1,7 +1,12 @@
 // Host-side data of the octree mesh and the operator set-up.
 #pragma once
+#include <condition_variable>
 #include <cstdint>
+#include <exception>
+#include <functional>
+#include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 namespace mh {
@@ -117,6 +122,39 @@ struct OpHost {
 void build_operator(const Mesh& mesh, const std::vector<Nucleus>& nuc, const double pol[3],
                     int lmax, OpHost& op, const EcsReq* ecs = nullptr);
 
+// Threads of one set-up, started once and given work range by range (a thread
+// started for each of many short passes costs more than the pass).  At most n
+// threads work, the caller among them; fewer where the system gives fewer.
+class Crew {
+ public:
+  explicit Crew(int n);
+  ~Crew();
+  Crew(const Crew&) = delete;
+  Crew& operator=(const Crew&) = delete;
+  // threads for `work` (in units of about 5 ns), about a millisecond each at least
+  int parts(int64_t work) const;
+  // f(c, lo, hi) over n items cut into `parts` ranges in order, c = 0 .. parts - 1
+  // (at most the threads there are); the first exception of a range is thrown again
+  void ranges(int64_t n, int parts, const std::function<void(int, int64_t, int64_t)>& f);
+
+ private:
+  void work(int c);
+  void run(int c);
+  std::vector<std::thread> pool_;
+  std::mutex mu_;
+  std::condition_variable go_, done_;
+  uint64_t round_ = 0;
+  bool stop_ = false;
+  int parts_ = 0, left_ = 0;
+  int64_t n_ = 0;
+  const std::function<void(int, int64_t, int64_t)>* f_ = nullptr;
+  std::vector<std::exception_ptr> err_;
+};
+
+// The assembled Poisson operator and its diagonal alone (kt_*, kdiag_inv, equal to
+// build_operator's, and what they are made from).
+void build_poisson(const Mesh& mesh, OpHost& op, Crew& crew);
+
 // Geometric multigrid hierarchy for the assembled pair Poisson operator
 // (homogeneous Dirichlet problem on the DoFs).  Level 0 is the operator's own
 // mesh; below Q3 comes Q2 on the same leaves, then Q1 on them, then Q1 with every
@@ -149,8 +187,8 @@ struct MgHost {
   std::vector<double> coarse_dense;        // the coarsest operator, dense row-major
 };
 // Levels stop at the first with at most max_coarse unknowns (or at the
-// coarsest base grid of the plan).
-void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_coarse = 400);
+// coarsest base grid of the plan).  threads: threads it may use itself.
+void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_coarse = 400, int threads = 1);
 
 // Multipole harmonics shared by set-up and kernels: the order of the
 // (l, m, cos/sin) terms.  Term count for lmax: (lmax+1)^2.

@@ -3,7 +3,6 @@
 // between consecutive levels, smoother bounds and the dense coarsest inverse.
 #include <algorithm>
 #include <cmath>
-#include <map>
 #include <stdexcept>
 #include <unordered_map>
 
@@ -36,7 +35,7 @@ int64_t locate(const Mesh& C, const std::unordered_map<uint64_t, int64_t>& leave
 
 // Prolongation rows: for each DoF node of F, the coarse function's value there
 // as a combination of C's DoFs.
-void prolongation(const Mesh& F, const Mesh& C, MgLevel& out) {
+void prolongation(const Mesh& F, const Mesh& C, MgLevel& out, Crew& crew) {
   std::unordered_map<uint64_t, int64_t> leaves;
   leaves.reserve(C.n_cells * 2);
   for (int64_t e = 0; e < C.n_cells; ++e)
@@ -44,39 +43,68 @@ void prolongation(const Mesh& F, const Mesh& C, MgLevel& out) {
   const int P = C.P;
   const int64_t NEc = C.N + C.Nh;
   out.p_ptr.assign(F.N + 1, 0);
-  out.p_col.clear();
-  out.p_val.clear();
-  std::map<int64_t, double> row;
-  for (int64_t i = 0; i < F.N; ++i) {
-    const double* x = &F.xyz[3 * i];
-    const int64_t e = locate(C, leaves, x);
-    if (e < 0) throw std::runtime_error("multigrid: fine node outside the coarse mesh");
-    double w1[3][4];
-    for (int d = 0; d < 3; ++d) {
-      const double xi = 2.0 * (x[d] - C.cell_org[3 * e + d]) / C.cell_h[e] - 1.0;
-      for (int a = 0; a < P; ++a) w1[d][a] = lagrange(C.gll.x, a, xi);
-    }
-    row.clear();
-    for (int c = 0; c < P; ++c)
-      for (int b = 0; b < P; ++b)
-        for (int a = 0; a < P; ++a) {
-          const double w = w1[0][a] * w1[1][b] * w1[2][c];
-          if (std::fabs(w) < 1e-15) continue;
-          const int64_t nd = C.cell_nodes[(e * P + c) * P * P + b * P + a];
-          if (nd < C.N) {
-            row[nd] += w;
-          } else if (nd < NEc) {  // hanging: its constraint row (boundary masters carry zero)
-            const int64_t h = nd - C.N;
-            for (int64_t t = C.hang_ptr[h]; t < C.hang_ptr[h + 1]; ++t)
-              if (C.hang_col[t] < C.N) row[C.hang_col[t]] += w * C.hang_w[t];
-          }
-        }
-    for (const auto& kv : row)
-      if (std::fabs(kv.second) > 1e-14) {
-        out.p_col.push_back((int32_t)kv.first);
-        out.p_val.push_back(kv.second);
+  struct Part {
+    std::vector<int32_t> col;
+    std::vector<double> val;
+  };
+  const int parts = crew.parts(2 * F.N * P * P * P);
+  std::vector<Part> part(parts);
+  crew.ranges(F.N, parts, [&](int c0, int64_t lo, int64_t hi) {
+    Part& po = part[c0];
+    std::vector<std::pair<int32_t, double>> row;   // sums by column, in order of first appearance
+    for (int64_t i = lo; i < hi; ++i) {
+      const double* x = &F.xyz[3 * i];
+      const int64_t e = locate(C, leaves, x);
+      if (e < 0) throw std::runtime_error("multigrid: fine node outside the coarse mesh");
+      double w1[3][4];
+      for (int d = 0; d < 3; ++d) {
+        const double xi = 2.0 * (x[d] - C.cell_org[3 * e + d]) / C.cell_h[e] - 1.0;
+        for (int a = 0; a < P; ++a) w1[d][a] = lagrange(C.gll.x, a, xi);
       }
-    out.p_ptr[i + 1] = (int32_t)out.p_col.size();
+      row.clear();
+      auto add = [&](int64_t c, double w) {
+        for (auto& r : row)
+          if (r.first == c) {
+            r.second += w;
+            return;
+          }
+        row.push_back({(int32_t)c, w});
+      };
+      for (int c = 0; c < P; ++c)
+        for (int b = 0; b < P; ++b)
+          for (int a = 0; a < P; ++a) {
+            const double w = w1[0][a] * w1[1][b] * w1[2][c];
+            if (std::fabs(w) < 1e-15) continue;
+            const int64_t nd = C.cell_nodes[(e * P + c) * P * P + b * P + a];
+            if (nd < C.N) {
+              add(nd, w);
+            } else if (nd < NEc) {  // hanging: its constraint row (boundary masters carry zero)
+              const int64_t h = nd - C.N;
+              for (int64_t t = C.hang_ptr[h]; t < C.hang_ptr[h + 1]; ++t)
+                if (C.hang_col[t] < C.N) add(C.hang_col[t], w * C.hang_w[t]);
+            }
+          }
+      std::sort(row.begin(), row.end());
+      const size_t beg = po.col.size();
+      for (const auto& kv : row)
+        if (std::fabs(kv.second) > 1e-14) {
+          po.col.push_back(kv.first);
+          po.val.push_back(kv.second);
+        }
+      out.p_ptr[i + 1] = (int32_t)(po.col.size() - beg);
+    }
+  });
+  int64_t nnz = 0;
+  for (int64_t i = 0; i < F.N; ++i) {
+    nnz += out.p_ptr[i + 1];
+    if (nnz >= INT32_MAX) throw std::runtime_error("multigrid: prolongation too large");
+    out.p_ptr[i + 1] = (int32_t)nnz;
+  }
+  out.p_col.swap(part[0].col);
+  out.p_val.swap(part[0].val);
+  for (int c = 1; c < parts; ++c) {
+    out.p_col.insert(out.p_col.end(), part[c].col.begin(), part[c].col.end());
+    out.p_val.insert(out.p_val.end(), part[c].val.begin(), part[c].val.end());
   }
   // transpose
   const int64_t Nc = C.N;
@@ -94,30 +122,26 @@ void prolongation(const Mesh& F, const Mesh& C, MgLevel& out) {
     }
 }
 
-void csr_apply(const MgLevel& L, const std::vector<double>& x, std::vector<double>& y) {
-  y.assign(L.N, 0.0);
-  for (int64_t i = 0; i < L.N; ++i) {
-    double s = 0.0;
-    for (int32_t t = L.k_ptr[i]; t < L.k_ptr[i + 1]; ++t) s += L.k_val[t] * x[L.k_col[t]];
-    y[i] = s;
-  }
-}
-
 // Largest eigenvalue of D^-1 K by power iteration (a fixed seed-free start).
-double lambda_max(const MgLevel& L) {
-  std::vector<double> x(L.N), y;
+double lambda_max(const MgLevel& L, Crew& crew) {
+  std::vector<double> x(L.N), y(L.N);
   for (int64_t i = 0; i < L.N; ++i) x[i] = 1.0 + 0.5 * std::sin(0.7 * (double)i);
-  double lam = 0.0;
+  const int parts = crew.parts((int64_t)L.k_col.size());
+  double lam = 0.0, nrm = 1.0;
   for (int it = 0; it < 40; ++it) {
-    csr_apply(L, x, y);
-    double nrm = 0.0;
+    crew.ranges(L.N, parts, [&](int, int64_t lo, int64_t hi) {
+      for (int64_t i = lo; i < hi; ++i) {
+        double s = 0.0;
+        for (int32_t t = L.k_ptr[i]; t < L.k_ptr[i + 1]; ++t) s += L.k_val[t] * x[L.k_col[t]];
+        y[i] = s * L.dinv[i];
+      }
+    });
+    double yn = 0.0, xn = 0.0;
     for (int64_t i = 0; i < L.N; ++i) {
-      y[i] *= L.dinv[i];
-      nrm += y[i] * y[i];
+      yn += y[i] * y[i];
+      xn += x[i] * x[i];
     }
-    nrm = std::sqrt(nrm);
-    double xn = 0.0;
-    for (double v : x) xn += v * v;
+    nrm = std::sqrt(yn);
     lam = nrm / std::sqrt(xn);
     for (int64_t i = 0; i < L.N; ++i) x[i] = y[i] / nrm;
   }
@@ -249,7 +273,8 @@ void galerkin(const MgLevel& F, int64_t Nc, MgLevel& L) {
 // Iterations of the CG from zero to 1e-12, Q1 straight below Q3 and collocated
 // operators -> these: H2 (Q3) 20 -> 11, a Q2 mesh of 50,429 unknowns 16 -> 12, a
 // Q1 mesh of 14,205 17 -> 13.
-void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_coarse) {
+void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_coarse, int threads) {
+  Crew crew(threads);
   mg.lv.clear();
   std::vector<Mesh> meshes;
   meshes.push_back(fine);
@@ -285,7 +310,6 @@ void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_co
     nc /= 2;
     plan.push_back({nc, 1, {}, -1});
   }
-  const double pol[3] = {0.0, 0.0, 1.0};
   for (size_t pi = 0; pi < plan.size(); ++pi) {
     const auto& pl = plan[pi];
     Mesh C;
@@ -299,13 +323,13 @@ void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_co
     // coarsening much; skip it (the meshes are nested, so the next one still is)
     if (pi + 1 < plan.size() && (double)C.N > 0.6 * (double)mg.lv.back().N) continue;
     if (C.N == 0) break;
-    prolongation(F, C, mg.lv.back());
+    prolongation(F, C, mg.lv.back(), crew);
     MgLevel LC;
     if (pl.p == 1) {
       galerkin(mg.lv.back(), C.N, LC);
     } else {
       OpHost HC;
-      build_operator(C, {}, pol, 0, HC);
+      build_poisson(C, HC, crew);
       take_operator(HC, C.N, LC);
     }
     if (F.n_cells == C.n_cells && F.nc == C.nc && F.p == C.p + 1) cell_transfer(F, C, mg.lv.back(), LC);
@@ -313,7 +337,7 @@ void build_multigrid(const Mesh& fine, const OpHost& fop, MgHost& mg, int max_co
     meshes.push_back(std::move(C));
     if (mg.lv.back().N <= max_coarse) break;  // small enough for the dense solve
   }
-  for (MgLevel& L : mg.lv) L.lmax = 1.05 * lambda_max(L);
+  for (MgLevel& L : mg.lv) L.lmax = 1.05 * lambda_max(L, crew);
   // the coarsest operator as a dense row-major matrix (inverted on the device)
   const MgLevel& Lc = mg.lv.back();
   const int64_t n = Lc.N;

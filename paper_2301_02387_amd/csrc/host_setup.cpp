@@ -16,6 +16,7 @@
 #include <functional>
 #include <map>
 #include <stdexcept>
+#include <system_error>
 
 #include "host.hpp"
 
@@ -199,7 +200,261 @@ std::vector<double> sym_eigs(std::vector<double> a, int n) {
   return ev;
 }
 
+// Node -> incident cells (at most 8: one leaf per octant around a point).
+void node_incidence(const Mesh& M, std::vector<int32_t>& inc) {
+  const int64_t NE = M.N + M.Nh;
+  const int P3 = M.P * M.P * M.P;
+  inc.assign((size_t)NE * 8, -1);
+  std::vector<uint8_t> cnt(NE, 0);
+  for (int64_t e = 0; e < M.n_cells; ++e)
+    for (int t = 0; t < P3; ++t) {
+      int32_t nd = M.cell_nodes[e * P3 + t];
+      if (nd >= NE) continue;
+      if (cnt[nd] >= 8) throw std::runtime_error("a node lies in more than 8 cells");
+      inc[(size_t)nd * 8 + cnt[nd]++] = (int32_t)(e * 64 + t);
+    }
+}
+
+// Assembled Poisson operator K~ = C^T K_full C on the DoFs, from the nodes'
+// incident cells and the hanging rows of each master (op.node_inc, ma_index, ct_*).
+// Row k of K_full is the sum over k's cells of its three line couplings
+// (h/2) A (x) W (x) W etc.; rows of masters also collect c_hk times the
+// rows of the hanging nodes they constrain; columns are expanded through
+// C onto DoFs (boundary columns drop: the CG unknowns are homogeneous).
+// Rows, and the cells' shares of the diagonal, in ranges over the threads; the
+// shares are added in the cells' order whatever their number.
+void assemble_poisson(const Mesh& M, OpHost& op, Crew& crew) {
+  const int P = M.P, P3 = P * P * P;
+  const int64_t nC = M.n_cells, N = M.N, NE = M.N + M.Nh;
+  const std::vector<double>& w = M.gll.w;
+  const std::vector<double>& A = M.gll.A;
+  typedef std::pair<int32_t, double> Entry;
+  struct Part {
+    std::vector<int32_t> len, col;
+    std::vector<double> val;
+    std::vector<Entry> diag;
+  };
+  const int threads = crew.parts(24 * nC * P3);
+  std::vector<Part> part(threads);
+  crew.ranges(N, threads, [&](int c0, int64_t lo, int64_t hi) {
+    Part& out = part[c0];
+    std::vector<Entry> ent;
+    auto add_row = [&](int64_t nd, double s) {
+      for (int t = 0; t < 8; ++t) {
+        const int32_t code = op.node_inc[(size_t)nd * 8 + t];
+        if (code < 0) break;
+        const int64_t e = code >> 6;
+        const int loc = code & 63;
+        const int a = loc % P, b = (loc / P) % P, c = loc / (P * P);
+        const int32_t* cn = &M.cell_nodes[e * P3];
+        const double hh = 0.5 * M.cell_h[e];
+        for (int q = 0; q < P; ++q) {
+          const int32_t js[3] = {cn[(c * P + b) * P + q], cn[(c * P + q) * P + a], cn[(q * P + b) * P + a]};
+          const double cf[3] = {hh * A[a * P + q] * w[b] * w[c], hh * w[a] * A[b * P + q] * w[c],
+                                hh * w[a] * w[b] * A[c * P + q]};
+          for (int l = 0; l < 3; ++l) {
+            const int64_t j = js[l];
+            const double v = s * cf[l];
+            if (j < N) {
+              ent.push_back({(int32_t)j, v});
+            } else if (j < NE) {
+              for (int64_t r = M.hang_ptr[j - N]; r < M.hang_ptr[j - N + 1]; ++r)
+                if (M.hang_col[r] < N) ent.push_back({(int32_t)M.hang_col[r], v * M.hang_w[r]});
+            }
+          }
+        }
+      }
+    };
+    out.len.reserve(hi - lo);
+    for (int64_t k = lo; k < hi; ++k) {
+      ent.clear();
+      add_row(k, 1.0);
+      const int32_t mi = op.ma_index[k];
+      if (mi >= 0)
+        for (int32_t t = op.ct_ptr[mi]; t < op.ct_ptr[mi + 1]; ++t) add_row(op.ct_row[t], op.ct_w[t]);
+      std::sort(ent.begin(), ent.end(), [](const Entry& x, const Entry& y) { return x.first < y.first; });
+      const size_t beg = out.col.size();
+      for (size_t t = 0; t < ent.size();) {
+        size_t u = t;
+        double v = 0.0;
+        while (u < ent.size() && ent[u].first == ent[t].first) v += ent[u++].second;
+        out.col.push_back(ent[t].first);
+        out.val.push_back(v);
+        t = u;
+      }
+      out.len.push_back((int32_t)(out.col.size() - beg));
+      if (out.col.size() >= (size_t)INT32_MAX) throw std::runtime_error("Poisson operator too large");
+    }
+  });
+  size_t nnz = 0;
+  for (const Part& p : part) nnz += p.col.size();
+  if (nnz >= (size_t)INT32_MAX) throw std::runtime_error("Poisson operator too large");
+  op.kt_ptr.assign(N + 1, 0);
+  op.kt_col.swap(part[0].col);
+  op.kt_val.swap(part[0].val);
+  if (threads > 1) {
+    op.kt_col.reserve(nnz);
+    op.kt_val.reserve(nnz);
+  }
+  int64_t k = 0;
+  for (int c = 0; c < threads; ++c) {
+    Part& p = part[c];
+    for (int32_t l : p.len) {
+      op.kt_ptr[k + 1] = op.kt_ptr[k] + l;
+      ++k;
+    }
+    if (c == 0) continue;
+    op.kt_col.insert(op.kt_col.end(), p.col.begin(), p.col.end());
+    op.kt_val.insert(op.kt_val.end(), p.val.begin(), p.val.end());
+    p = Part();
+  }
+
+  // diagonal of C^T K_full C, cell by cell
+  std::vector<double> kdiag(N, 0.0);
+  crew.ranges(nC, threads, [&](int c0, int64_t lo, int64_t hi) {
+    std::vector<Entry>& out = part[c0].diag;
+    std::vector<double> y(P3);
+    auto add = [&](int64_t n, double s) {
+      if (threads == 1) kdiag[n] += s;
+      else out.push_back({(int32_t)n, s});
+    };
+    for (int64_t e = lo; e < hi; ++e) {
+      const int32_t* cn = &M.cell_nodes[e * P3];
+      bool simple = true;
+      for (int t = 0; t < P3; ++t)
+        if (cn[t] >= N && cn[t] < NE) simple = false;
+      if (simple) {
+        // element diagonal: (h/2)(A_aa w_b w_c + w_a A_bb w_c + w_a w_b A_cc)
+        for (int c = 0; c < P; ++c)
+          for (int b = 0; b < P; ++b)
+            for (int a = 0; a < P; ++a) {
+              int32_t n = cn[(c * P + b) * P + a];
+              if (n >= N) continue;
+              add(n, 0.5 * M.cell_h[e] *
+                         (A[a * P + a] * w[b] * w[c] + w[a] * A[b * P + b] * w[c] + w[a] * w[b] * A[c * P + c]));
+            }
+        continue;
+      }
+      // DoFs reached from this cell, with their local weight vectors
+      std::map<int64_t, std::vector<double>> wk;
+      for (int t = 0; t < P3; ++t) {
+        int64_t n = cn[t];
+        if (n < N) {
+          auto& vv = wk[n];
+          if (vv.empty()) vv.assign(P3, 0.0);
+          vv[t] += 1.0;
+        } else if (n < NE) {
+          for (int64_t a = M.hang_ptr[n - N]; a < M.hang_ptr[n - N + 1]; ++a) {
+            int64_t j = M.hang_col[a];
+            if (j >= N) continue;
+            auto& vv = wk[j];
+            if (vv.empty()) vv.assign(P3, 0.0);
+            vv[t] += M.hang_w[a];
+          }
+        }
+      }
+      for (auto& kv : wk) {
+        elem_stiff(P, A, w, M.cell_h[e], kv.second.data(), y.data());
+        double s = 0.0;
+        for (int t = 0; t < P3; ++t) s += kv.second[t] * y[t];
+        add(kv.first, s);
+      }
+    }
+  });
+  for (const Part& p : part)
+    for (const Entry& d : p.diag) kdiag[d.first] += d.second;
+  op.kdiag_inv.assign(N, 0.0);
+  for (int64_t i = 0; i < N; ++i) op.kdiag_inv[i] = 1.0 / kdiag[i];
+}
+
 }  // namespace
+
+Crew::Crew(int n) {
+  err_.resize(std::max(1, n));
+  pool_.reserve(std::max(0, n - 1));
+  for (int c = 1; c < n; ++c) {
+    try {
+      pool_.emplace_back([this, c] { work(c); });
+    } catch (const std::system_error&) {   // no more threads to be had
+      break;
+    }
+  }
+}
+Crew::~Crew() {
+  {
+    std::lock_guard<std::mutex> lock(mu_);
+    stop_ = true;
+  }
+  go_.notify_all();
+  for (auto& t : pool_) t.join();
+}
+int Crew::parts(int64_t work) const {
+  return (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)pool_.size() + 1, work / 200000));
+}
+void Crew::run(int c) {
+  try {
+    (*f_)(c, n_ * c / parts_, n_ * (c + 1) / parts_);
+  } catch (...) {
+    err_[c] = std::current_exception();
+  }
+}
+void Crew::work(int c) {
+  uint64_t seen = 0;
+  for (;;) {
+    {
+      std::unique_lock<std::mutex> lock(mu_);
+      go_.wait(lock, [&] { return stop_ || round_ != seen; });
+      if (stop_) return;
+      seen = round_;
+      if (c >= parts_) continue;
+    }
+    run(c);
+    std::lock_guard<std::mutex> lock(mu_);
+    if (--left_ == 0) done_.notify_one();
+  }
+}
+void Crew::ranges(int64_t n, int parts, const std::function<void(int, int64_t, int64_t)>& f) {
+  {
+    std::lock_guard<std::mutex> lock(mu_);
+    n_ = n;
+    f_ = &f;
+    parts_ = std::min(parts, (int)pool_.size() + 1);
+    left_ = parts_ - 1;
+    ++round_;
+  }
+  if (parts_ > 1) go_.notify_all();
+  run(0);
+  std::unique_lock<std::mutex> lock(mu_);
+  done_.wait(lock, [&] { return left_ == 0; });
+  std::exception_ptr first;
+  for (int c = 0; c < parts_; ++c) {
+    if (err_[c] && !first) first = err_[c];
+    err_[c] = nullptr;
+  }
+  if (first) std::rethrow_exception(first);
+}
+
+void build_poisson(const Mesh& M, OpHost& op, Crew& crew) {
+  node_incidence(M, op.node_inc);
+  const int64_t nMa = (int64_t)M.masters.size();
+  op.ma_index.assign(M.N, -1);
+  for (int64_t i = 0; i < nMa; ++i) op.ma_index[M.masters[i]] = (int32_t)i;
+  op.ct_ptr.assign(nMa + 1, 0);
+  for (int64_t a : M.hang_col)
+    if (a < M.N) op.ct_ptr[op.ma_index[a] + 1]++;
+  for (int64_t i = 0; i < nMa; ++i) op.ct_ptr[i + 1] += op.ct_ptr[i];
+  op.ct_row.resize(op.ct_ptr[nMa]);
+  op.ct_w.resize(op.ct_ptr[nMa]);
+  std::vector<int32_t> at(op.ct_ptr.begin(), op.ct_ptr.end() - 1);
+  for (int64_t h = 0; h < M.Nh; ++h)
+    for (int64_t t = M.hang_ptr[h]; t < M.hang_ptr[h + 1]; ++t)
+      if (M.hang_col[t] < M.N) {
+        const int32_t i = at[op.ma_index[M.hang_col[t]]]++;
+        op.ct_row[i] = (int32_t)(M.N + h);
+        op.ct_w[i] = M.hang_w[t];
+      }
+  assemble_poisson(M, op, crew);
+}
 
 void build_operator(const Mesh& M, const std::vector<Nucleus>& nuc, const double pol[3], int lmax, OpHost& op,
                     const EcsReq* ecs) {
@@ -299,18 +554,7 @@ void build_operator(const Mesh& M, const std::vector<Nucleus>& nuc, const double
       }
   }
 
-  // ---- node -> incident cells (at most 8: one leaf per octant around a point)
-  op.node_inc.assign((size_t)NE * 8, -1);
-  {
-    std::vector<uint8_t> cnt(NE, 0);
-    for (int64_t e = 0; e < nC; ++e)
-      for (int t = 0; t < P3; ++t) {
-        int32_t nd = M.cell_nodes[e * P3 + t];
-        if (nd >= NE) continue;
-        if (cnt[nd] >= 8) throw std::runtime_error("a node lies in more than 8 cells");
-        op.node_inc[(size_t)nd * 8 + cnt[nd]++] = (int32_t)(e * 64 + t);
-      }
-  }
+  node_incidence(M, op.node_inc);
 
   // ---- interface block of the mass matrix ------------------------------------
   const int64_t nMa = (int64_t)M.masters.size();
@@ -495,116 +739,8 @@ void build_operator(const Mesh& M, const std::vector<Nucleus>& nuc, const double
     }
   }
 
-  // ---- assembled Poisson operator K~ = C^T K_full C on the DoFs --------------
-  // Row k of K_full is the sum over k's cells of its three line couplings
-  // (h/2) A (x) W (x) W etc.; rows of masters also collect c_hk times the
-  // rows of the hanging nodes they constrain; columns are expanded through
-  // C onto DoFs (boundary columns drop: the CG unknowns are homogeneous).
-  {
-    const std::vector<double>& A = M.gll.A;
-    op.kt_ptr.assign(N + 1, 0);
-    op.kt_col.clear();
-    op.kt_val.clear();
-    std::vector<std::pair<int32_t, double>> ent;
-    auto add_row = [&](int64_t nd, double s) {
-      for (int t = 0; t < 8; ++t) {
-        const int32_t code = op.node_inc[(size_t)nd * 8 + t];
-        if (code < 0) break;
-        const int64_t e = code >> 6;
-        const int loc = code & 63;
-        const int a = loc % P, b = (loc / P) % P, c = loc / (P * P);
-        const int32_t* cn = &M.cell_nodes[e * P3];
-        const double hh = 0.5 * M.cell_h[e];
-        for (int q = 0; q < P; ++q) {
-          const int32_t js[3] = {cn[(c * P + b) * P + q], cn[(c * P + q) * P + a], cn[(q * P + b) * P + a]};
-          const double cf[3] = {hh * A[a * P + q] * w[b] * w[c], hh * w[a] * A[b * P + q] * w[c],
-                                hh * w[a] * w[b] * A[c * P + q]};
-          for (int l = 0; l < 3; ++l) {
-            const int64_t j = js[l];
-            const double v = s * cf[l];
-            if (j < N) {
-              ent.push_back({(int32_t)j, v});
-            } else if (j < NE) {
-              for (int64_t r = M.hang_ptr[j - N]; r < M.hang_ptr[j - N + 1]; ++r)
-                if (M.hang_col[r] < N) ent.push_back({(int32_t)M.hang_col[r], v * M.hang_w[r]});
-            }
-          }
-        }
-      }
-    };
-    for (int64_t k = 0; k < N; ++k) {
-      ent.clear();
-      add_row(k, 1.0);
-      const int32_t mi = op.ma_index[k];
-      if (mi >= 0)
-        for (int32_t t = op.ct_ptr[mi]; t < op.ct_ptr[mi + 1]; ++t) add_row(op.ct_row[t], op.ct_w[t]);
-      std::sort(ent.begin(), ent.end(),
-                [](const std::pair<int32_t, double>& x, const std::pair<int32_t, double>& y) {
-                  return x.first < y.first;
-                });
-      for (size_t t = 0; t < ent.size();) {
-        size_t u = t;
-        double v = 0.0;
-        while (u < ent.size() && ent[u].first == ent[t].first) v += ent[u++].second;
-        op.kt_col.push_back(ent[t].first);
-        op.kt_val.push_back(v);
-        t = u;
-      }
-      if (op.kt_col.size() >= (size_t)INT32_MAX) throw std::runtime_error("Poisson operator too large");
-      op.kt_ptr[k + 1] = (int32_t)op.kt_col.size();
-    }
-  }
-
-  // ---- Jacobi diagonal of C^T K_full C --------------------------------------
-  {
-    std::vector<double> kdiag(N, 0.0);
-    std::vector<double> x(P3), y(P3);
-    for (int64_t e = 0; e < nC; ++e) {
-      const int32_t* cn = &M.cell_nodes[e * P3];
-      bool simple = true;
-      for (int t = 0; t < P3; ++t)
-        if (cn[t] >= N && cn[t] < NE) simple = false;
-      if (simple) {
-        // element diagonal: (h/2)(A_aa w_b w_c + w_a A_bb w_c + w_a w_b A_cc)
-        for (int c = 0; c < P; ++c)
-          for (int b = 0; b < P; ++b)
-            for (int a = 0; a < P; ++a) {
-              int32_t n = cn[(c * P + b) * P + a];
-              if (n >= N) continue;
-              kdiag[n] += 0.5 * M.cell_h[e] *
-                          (M.gll.A[a * P + a] * w[b] * w[c] + w[a] * M.gll.A[b * P + b] * w[c] +
-                           w[a] * w[b] * M.gll.A[c * P + c]);
-            }
-        continue;
-      }
-      // DoFs reached from this cell, with their local weight vectors
-      std::map<int64_t, std::vector<double>> wk;
-      for (int t = 0; t < P3; ++t) {
-        int64_t n = cn[t];
-        if (n < N) {
-          auto& vv = wk[n];
-          if (vv.empty()) vv.assign(P3, 0.0);
-          vv[t] += 1.0;
-        } else if (n < NE) {
-          for (int64_t a = M.hang_ptr[n - N]; a < M.hang_ptr[n - N + 1]; ++a) {
-            int64_t k = M.hang_col[a];
-            if (k >= N) continue;
-            auto& vv = wk[k];
-            if (vv.empty()) vv.assign(P3, 0.0);
-            vv[t] += M.hang_w[a];
-          }
-        }
-      }
-      for (auto& kv : wk) {
-        elem_stiff(P, M.gll.A, w, M.cell_h[e], kv.second.data(), y.data());
-        double s = 0.0;
-        for (int t = 0; t < P3; ++t) s += kv.second[t] * y[t];
-        kdiag[kv.first] += s;
-      }
-    }
-    op.kdiag_inv.assign(N, 0.0);
-    for (int64_t k = 0; k < N; ++k) op.kdiag_inv[k] = 1.0 / kdiag[k];
-  }
+  Crew alone(1);
+  assemble_poisson(M, op, alone);
 
   // ---- cells that see boundary values -----------------------------------------
   op.bnd_cells.clear();
