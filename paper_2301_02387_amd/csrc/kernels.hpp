@@ -156,10 +156,9 @@ struct Batch {
 // *Ef (times each instance's E0).
 void launch_stencil_orb(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
                         const double* ginv, int mode, const double* lam, double* out, double* acc, hipStream_t s);
-// rows of the one-body operator: entries per row into cnt [NE] (instance inst), then the entries
-void launch_orb_row_count(const Batch& b, int inst, int32_t* cnt, hipStream_t s);
-void launch_orb_row_fill(const Batch& b, int inst, int32_t* col, double* k, double* sv, double* kc, double* sc,
-                         hipStream_t s);
+// rows of the one-body operator, all instances: the entries of row i into or_ptr[i + 1], then the entries
+void launch_orb_row_count(const Batch& b, hipStream_t s);
+void launch_orb_row_fill(const Batch& b, hipStream_t s);
 // Masters: acc_k + sum_h c_hk acc_h -> out (mode 0) or the interface rhs ma_b.
 void launch_ma_gather_orb(const Batch& b, const double* acc, int mode, double* out, double* ma_b, hipStream_t s);
 void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma_b, hipStream_t s);

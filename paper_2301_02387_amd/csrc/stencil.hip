@@ -73,9 +73,12 @@ __device__ __forceinline__ void orb_entry_add(const DevMesh& d, int64_t i, int e
   }
 }
 template <int P, bool FILL>
-__global__ void __launch_bounds__(NT) k_orb_row_build(const DevMesh* __restrict__ dm, int inst, int32_t* cnt,
-                                                      int32_t* col, double* k, double* sv, double2* kc, double2* sc) {
-  const DevMesh& d = dm[inst];
+__global__ void __launch_bounds__(NT) k_orb_row_build(const DevMesh* __restrict__ dm) {
+  INSTANCE;
+  int32_t* col = const_cast<int32_t*>(d.or_col);
+  double* k = const_cast<double*>(d.or_k);
+  double* sv = const_cast<double*>(d.or_s);
+  double2 *kc = (double2*)const_cast<double*>(d.or_kc), *sc = (double2*)const_cast<double*>(d.or_sc);
   constexpr int E = 24 * P;
   for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < d.NE; i += (int64_t)gridDim.x * NT) {
     int cols[E], m = 0;
@@ -106,27 +109,20 @@ __global__ void __launch_bounds__(NT) k_orb_row_build(const DevMesh* __restrict_
       }
       ++m;
     }
-    if (!FILL) cnt[i] = m;
+    if (!FILL) const_cast<int32_t*>(d.or_ptr)[i + 1] = m;
   }
 }
 template <bool FILL>
-static void orb_row_build(const Batch& b, int inst, int32_t* cnt, int32_t* col, double* k, double* sv, double* kc,
-                          double* sc, hipStream_t s) {
+static void orb_row_build(const Batch& b, hipStream_t s) {
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(nblocks(b.mx.NE, NT, 4096)), dim3(NT), 0, s, b.dm, inst, cnt, col, k, sv,
-                       (double2*)kc, (double2*)sc);
+    hipLaunchKernelGGL(kern, dim3(nblocks(b.mx.NE, NT, 4096), b.ni), dim3(NT), 0, s, b.dm);
   };
   if (b.mx.P == 2) go(k_orb_row_build<2, FILL>);
   else if (b.mx.P == 3) go(k_orb_row_build<3, FILL>);
   else go(k_orb_row_build<4, FILL>);
 }
-void launch_orb_row_count(const Batch& b, int inst, int32_t* cnt, hipStream_t s) {
-  orb_row_build<false>(b, inst, cnt, nullptr, nullptr, nullptr, nullptr, nullptr, s);
-}
-void launch_orb_row_fill(const Batch& b, int inst, int32_t* col, double* k, double* sv, double* kc, double* sc,
-                         hipStream_t s) {
-  orb_row_build<true>(b, inst, nullptr, col, k, sv, kc, sc, s);
-}
+void launch_orb_row_count(const Batch& b, hipStream_t s) { orb_row_build<false>(b, s); }
+void launch_orb_row_fill(const Batch& b, hipStream_t s) { orb_row_build<true>(b, s); }
 
 // --------------------------------------------------------------------------
 // Orbital operator.  mode 0: F = load vector; 1: M^-1 F; 2: M^-1 F - v lam.
