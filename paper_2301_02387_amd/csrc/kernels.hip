@@ -368,10 +368,16 @@ void launch_ma_solve(const Batch& b, const double* ma_b, double* x, double* r, d
 // one launch, the non-masters' workgroups beside the dense rows'; in place, and on
 // the Chebyshev path, the masters' rows are gathered to ma_b first.  H atom (4,007
 // DoFs, 196 masters), hanging rows included: three launches -> two, 9.5 -> 6.8 us on
-// the device, 14.0 -> 11.0 us a call.
+// the device, 14.0 -> 11.0 us a call.  Each workgroup then gathers the masters' rows of
+// f through their DoFs, so with many of them the launch that lays them out first
+// is the cheaper: masters x orbitals of 670 x 8 12.4 us against 15.0 laid out, 1,220 x 4
+// 11.4 against 13.3, 2,382 x 2 18.7 against 18.2, 1,220 x 5 19.5 against 15.0, 2,382 x 3
+// 23.2 against 21.0, x 5 53.1 against 39.7.
+constexpr int64_t MA_LOAD_MAX = 5400;
 void launch_mass_solve(const Batch& b, const double* f, double* out, double* ma_b, double* x, double* r, double* dbuf0,
                        double* dbuf1, hipStream_t s) {
-  if (b.ni == 1 && b.mx.nMa > 0 && b.mx.ma_inv && !(b.mx.sched_orb & 2) && f != out) {
+  if (b.ni == 1 && b.mx.nMa > 0 && b.mx.ma_inv && !(b.mx.sched_orb & 2) && f != out &&
+      b.mx.nMa * b.mx.n <= MA_LOAD_MAX) {
     auto go = [&](auto kern, int rows) {
       const int g = nblocks(b.mx.nMa, rows, 8192);
       hipLaunchKernelGGL(kern, dim3(g + nblocks(b.mx.N * b.mx.n, NT, 8192)), dim3(NT), 0, s, b.dm, (const double2*)f,

@@ -49,3 +49,20 @@ def test_coarsest_level_alone(n_coarse):
     torch.cuda.synchronize()
     assert op.n_dof == (n_coarse - 1) ** 3
     assert rc == 0 and it <= 2
+
+
+@pytest.mark.parametrize("n", [3, 4, 5, 8])
+def test_load_vector_gathered_or_laid_out(n):
+    """1,220 masters on both sides of 5,400 values: the mass solve into another array
+    (masters' rows gathered by every workgroup, or laid out first) and in place."""
+    import torch
+    P = pair("kelly_q2")
+    op = operator(P, n)
+    f = dev(P.to_lib_orb(orbitals(P, n, 180 + n)))
+    c, g = torch.zeros_like(f), f.clone()
+    op.mass_solve(f, c)
+    op.mass_solve(g, g)
+    torch.cuda.synchronize()
+    assert torch.equal(c, g)
+    ref = P.from_lib_dof(f.cpu().numpy()[:P.N])
+    assert rel_err_cols(P.ops.M @ P.from_lib_dof(c.cpu().numpy()), ref) < 1e-13
