@@ -1184,30 +1184,6 @@ static int mg_pcg(mh_op* op, double* W, int* iters, hipStream_t s, int fixed = 0
   return conv;
 }
 
-// Values times D^-1 of their columns for the Jacobi CG's operator pass (K D^-1 r
-// gathers r alone), made on the device by the first solve that takes them.
-static void ensure_jacobi(mh_op* op, hipStream_t s) {
-  const bool sell = op->B.mx.sched_poi & 32;
-  bool made = false;
-  for (int i = 0; i < op->ni; ++i) {
-    DevMesh& d = op->dh[i];
-    if (!d.kt_vd) {
-      const int64_t nnz = (int64_t)op->Hs[i].kt_col.size();
-      double* vd = op->alloc<double>(nnz);
-      launch_scale_entries(d.kt_val, d.kt_col, d.kdiag_inv, nnz, vd, s);
-      d.kt_vd = vd;
-      made = true;
-    }
-    if (sell && !d.sell_vd) {
-      double* vd = op->alloc<double>(d.sell_nnz);
-      launch_scale_entries(d.sell_val, d.sell_col, d.kdiag_inv, d.sell_nnz, vd, s);
-      d.sell_vd = vd;
-      made = true;
-    }
-  }
-  if (made) upload_instances(op, s);
-}
-
 // CG iterations after launch_cg_start, to the residual target or the cap:
 // multigrid-preconditioned (Poisson schedule bit 4), else
 // Jacobi launch by launch with a convergence check every 8 iterations.
@@ -1219,7 +1195,6 @@ static int cg_iterate(mh_op* op, double* W, int* iters, hipStream_t s) {
     ensure_mg(op, s);
     return mg_pcg(op, W, iters, s);
   }
-  ensure_jacobi(op, s);
   int it = 0, conv = 0;
   const int check = 8;
   while (it < op->maxit) {
@@ -1751,7 +1726,6 @@ static void build_sell(mh_op* op, int i, hipStream_t s) {
   const std::vector<float> valf(val.begin(), val.end());
   d.sell_valf = op->upload(valf, s);
   d.n_slices = (int64_t)ptr.size() - 1;
-  d.sell_nnz = (int64_t)col.size();
   HIPCHK(hipStreamSynchronize(s));  // the host tables are temporaries
 }
 

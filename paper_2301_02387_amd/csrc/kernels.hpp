@@ -76,16 +76,12 @@ struct DevMesh {
   const int32_t* sell_row = nullptr;    // [n_slices][SELL_H] row of each slot, -1 for none
   const int32_t* sell_col = nullptr;
   const double* sell_val = nullptr;
-  int64_t n_slices = 0, sell_nnz = 0;
+  int64_t n_slices = 0;
   // the same values rounded to float, read by the passes of the multigrid
   // preconditioner's finest level on float storage (Poisson schedule bit 6);
   // the CG's own operator pass reads the double values
   const float* kt_valf = nullptr;
   const float* sell_valf = nullptr;
-  // values times D^-1 of their columns: K D^-1 for the Jacobi CG's operator pass
-  // on r (made by its first solve)
-  const double* kt_vd = nullptr;
-  const double* sell_vd = nullptr;
   const int32_t* bnd_cells = nullptr;
   int64_t n_bnd_cells = 0;
   const double* bnd_table = nullptr;    // [Nb][nharm] multipole boundary table
@@ -255,9 +251,6 @@ void launch_poisson_rhs_full(const Batch& b, const double* phi, double* W, const
                              PoissonWs& P, hipStream_t s);
 void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int warm, hipStream_t s);
 void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s);
-// vd = val times dinv of the entry's column, nnz entries
-void launch_scale_entries(const double* val, const int32_t* col, const double* dinv, int64_t nnz, double* vd,
-                          hipStream_t s);
 // One iteration with another preconditioner: the operator pass on the
 // preconditioned residual z and the vector pass.  rz_rows: partial sums of r.z
 // left by launch_mg_cheb_step (0: r.z is in slot RED_RZ + k % 3).  rf (may be

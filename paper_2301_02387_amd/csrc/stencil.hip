@@ -436,7 +436,7 @@ void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma
 // workgroups sweep the remaining rows.
 // --------------------------------------------------------------------------
 // Operator pass modes: the CG's operator pass on the preconditioned residual
-// (SP_CG: z given, SP_CGJ: z = D^-1 r, D^-1 held in the values); the residual r - K x
+// (SP_CG: z given, SP_CGJ: z = D^-1 r formed on the fly); the residual r - K x
 // (SP_RES: of a CG start, and the one that the restriction to the next
 // multigrid level reads); and the Chebyshev smoothing passes of the multigrid
 // cycle on the finest level:
@@ -453,8 +453,8 @@ struct PassExtra {
   int full;
 };
 
-// Value gathered at row j, columns c0 .. c0+V: x itself; (SP_CHEB0) beta D^-1_j
-// x_j (x = r, beta = s0).
+// Value of the operand at row j, columns c0 .. c0+V: x itself; (SP_CGJ) D^-1_j
+// x_j; (SP_CHEB0) beta D^-1_j x_j (x = r, beta = s0).
 // T: storage type of the operand arrays (double; float for the finest-level
 // multigrid arrays of Poisson schedule bit 6).  Arithmetic is in double.
 template <int V, int MODE, class T>
@@ -467,6 +467,11 @@ __device__ __forceinline__ void operand_row(const __attribute__((address_space(1
 #pragma unroll
     for (int v = 0; v < V; ++v) out[v] = beta[v] * dj * out[v];
   }
+  if constexpr (MODE == SP_CGJ) {
+    const double dj = dinv[j];
+#pragma unroll
+    for (int v = 0; v < V; ++v) out[v] = dj * out[v];
+  }
 }
 
 // y += sum over entries t = beg, beg + stride, ... < end of val[t] operand(col[t]);
@@ -477,7 +482,7 @@ template <int V, int MODE, class T>
 __device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restrict__ x, const double* beta, int ld,
                                               int c0, int beg, int end, int stride, double* y) {
   const auto* kcol = gbl(d.kt_col);
-  const auto* kval = gbl(MODE == SP_CGJ ? d.kt_vd : d.kt_val);
+  const auto* kval = gbl(d.kt_val);
   const auto* kvalf = gbl(d.kt_valf);   // the preconditioner's float passes read the float copy, the CG's own pass the doubles
   const auto* xg = gbl(x);
   const auto* dinv = gbl(d.kdiag_inv);
@@ -555,13 +560,12 @@ __device__ __forceinline__ void spmv_store(const DevMesh& d, T* __restrict__ q, 
     }
   } else {
     double zi[V];
-    load_vals<V>(gbl(x) + i * ld + c0, zi);
-    const double di = MODE == SP_CGJ ? dinv[i] : 1.0;
+    operand_row<V, MODE, T>(gbl(x), dinv, beta, i, ld, c0, zi);
     auto* wo = gblw(ex.w) + i * ld + c0;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       wo[v] = y[v];
-      pq[v] += (MODE == SP_CGJ ? di * zi[v] : zi[v]) * y[v];
+      pq[v] += zi[v] * y[v];
     }
   }
 }
@@ -685,7 +689,7 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
     const auto* sptr = gbl(d.sell_ptr);
     const auto* srow = gbl(d.sell_row);
     const auto* scol = gbl(d.sell_col);
-    const auto* sval = gbl(MODE == SP_CGJ ? d.sell_vd : d.sell_val);
+    const auto* sval = gbl(d.sell_val);
     const auto* svalf = gbl(d.sell_valf);   // as in spmv_row_part
     const auto* xg = gbl(x);
     const auto* dinv = gbl(d.kdiag_inv);
@@ -1121,22 +1125,6 @@ void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const float* z
                          hipStream_t s) {
   cg_iteration(b, W, P, z, rf, rz_rows, k, s);
 }
-// The Jacobi pass gathers r itself against values times D^-1 of their columns
-// (8 B an entry more memory).  D^-1 gathered beside r, one more dependent load an
-// entry -> this: 66,635 rows x 4 columns 20.4 -> 17.0 us, four times that in a
-// batch 53.7 -> 46.0 (sliced-ELL 48.1 -> 40.2), 4,394 x 25 43.2 -> 38.0, 66,635 x 64
-// in blocks of 16 columns 197 -> 150.
-__global__ void __launch_bounds__(NT) k_scale_entries(const double* __restrict__ val, const int32_t* __restrict__ col,
-                                                      const double* __restrict__ dinv, int64_t nnz,
-                                                      double* __restrict__ vd) {
-  for (int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x; t < nnz; t += (int64_t)gridDim.x * NT)
-    vd[t] = val[t] * dinv[col[t]];
-}
-void launch_scale_entries(const double* val, const int32_t* col, const double* dinv, int64_t nnz, double* vd,
-                          hipStream_t s) {
-  if (nnz > 0) hipLaunchKernelGGL(k_scale_entries, dim3(nblocks(nnz, NT, 8192)), dim3(NT), 0, s, val, col, dinv, nnz, vd);
-}
-
 // One Jacobi-preconditioned iteration.
 void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s) {
   const int k = P.it;
