@@ -219,7 +219,7 @@ void launch_combine(const Batch& b, double* const* V, int m, double* phi, Krylov
 // offset oE), the potentials W over full rows (offset oF).
 struct PoissonWs {
   int ncol = 0, nharm = 0, lmax = 0;
-  double* acc = nullptr;   // [tE][ncol]
+  double* acc = nullptr;   // [tE][ncol] boundary lift of the right-hand side, then z = D^-1 r of the Jacobi CG
   double* p = nullptr;     // [tE][ncol] search direction
   double* w = nullptr;     // [tE][ncol] K z
   double* r = nullptr;     // [tE][ncol]

@@ -435,8 +435,8 @@ void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma
 // NT / L lane groups splitting the entries and an LDS reduction; the other
 // workgroups sweep the remaining rows.
 // --------------------------------------------------------------------------
-// Operator pass modes: the CG's operator pass on the preconditioned residual
-// (SP_CG: z given, SP_CGJ: z = D^-1 r formed on the fly); the residual r - K x
+// Operator pass modes: the CG's operator pass on the preconditioned residual z
+// (SP_CG); the residual r - K x
 // (SP_RES: of a CG start, and the one that the restriction to the next
 // multigrid level reads); and the Chebyshev smoothing passes of the multigrid
 // cycle on the finest level:
@@ -444,7 +444,7 @@ void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma
 // formed on the fly), SP_CHEB runs one step on a given z into another array.
 // SP_CHEB_RZ is the second SP_CHEB step with r.z accumulated for the
 // multigrid-preconditioned CG.
-enum { SP_CG = 1, SP_CHEB0 = 2, SP_CHEB = 3, SP_CHEB_RZ = 4, SP_RES = 5, SP_CGJ = 6 };
+enum { SP_CG = 1, SP_CHEB0 = 2, SP_CHEB = 3, SP_CHEB_RZ = 4, SP_RES = 5 };
 
 // Arrays of a pass beside its operand: w = K z of the CG's pass, double
 // whatever z is; full: the operand of SP_RES is over full rows.
@@ -453,8 +453,8 @@ struct PassExtra {
   int full;
 };
 
-// Value of the operand at row j, columns c0 .. c0+V: x itself; (SP_CGJ) D^-1_j
-// x_j; (SP_CHEB0) beta D^-1_j x_j (x = r, beta = s0).
+// Value of the operand at row j, columns c0 .. c0+V: x itself; (SP_CHEB0) beta
+// D^-1_j x_j (x = r, beta = s0).
 // T: storage type of the operand arrays (double; float for the finest-level
 // multigrid arrays of Poisson schedule bit 6).  Arithmetic is in double.
 template <int V, int MODE, class T>
@@ -466,11 +466,6 @@ __device__ __forceinline__ void operand_row(const __attribute__((address_space(1
     const double dj = dinv[j];
 #pragma unroll
     for (int v = 0; v < V; ++v) out[v] = beta[v] * dj * out[v];
-  }
-  if constexpr (MODE == SP_CGJ) {
-    const double dj = dinv[j];
-#pragma unroll
-    for (int v = 0; v < V; ++v) out[v] = dj * out[v];
   }
 }
 
@@ -507,7 +502,7 @@ __device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restr
   }
 }
 
-// Row i done, y = (K operand)_i.  SP_CG, SP_CGJ: w_i = y and the z.w partial.
+// Row i done, y = (K operand)_i.  SP_CG: w_i = y and the z.w partial.
 // Chebyshev passes (x: the operand's source, pprev = r, pout = z out, q = d,
 // cf = the instance's coefficients s0, c1, c2; step k of SP_CHEB, step 1 for
 // SP_CHEB_RZ):
@@ -616,7 +611,7 @@ constexpr int64_t FOLD_MAX = 8192;
 // sliced-ELL copy, a wave taking 64 / L slots of one slice (one width for all
 // its rows), so each round of entries is read as consecutive words.
 // MODE: SP_*; red: the CG accumulators ([ni][RED_SLOTS][ld]); k: the CG
-// iteration (SP_CG, SP_CGJ), the smoothing step (SP_CHEB) or the r.z slot (SP_CHEB0 clears it, SP_CHEB_RZ
+// iteration (SP_CG), the smoothing step (SP_CHEB) or the r.z slot (SP_CHEB0 clears it, SP_CHEB_RZ
 // accumulates into slot k & 15 at step k >> 4).
 template <int L, int V, int MODE, bool SELL, class T>
 __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__ dm, const T* __restrict__ x,
@@ -624,7 +619,7 @@ __global__ void __launch_bounds__(NT) k_spmv_poisson(const DevMesh* __restrict__
                                                      int ld, int nc, T* __restrict__ q, int nlb,
                                                      double* __restrict__ red, int k, double* __restrict__ part,
                                                      PassExtra ex) {
-  constexpr bool CG = MODE == SP_CG || MODE == SP_CGJ;
+  constexpr bool CG = MODE == SP_CG;
   INSTANCE;
   if (d.cg_done && *d.cg_done) return;  // converged instance of a batch CG (batches take no partials)
   __shared__ double lds[NT * V];
@@ -835,7 +830,7 @@ static int launch_spmv_m(const Batch& b, const T* x, const T* pprev, T* pout, in
   // that needs them or, where they are many, by one of their own
   double* part = nullptr;
   bool later = false;
-  if constexpr (MODE == SP_CG || MODE == SP_CGJ || MODE == SP_CHEB_RZ)
+  if constexpr (MODE == SP_CG || MODE == SP_CHEB_RZ)
     if (b.spart && b.ni == 1 && nc == ld && (int64_t)gx * nc <= b.spart_cap) {
       later = (int64_t)gx * nc <= FOLD_MAX;
       part = later && MODE == SP_CHEB_RZ ? b.spart + b.spart_cap : b.spart;   // both are folded by the update pass
@@ -853,9 +848,6 @@ template <int L, int V, class T>
 static int launch_spmv_t(const Batch& b, const T* x, const T* pprev, T* pout, int ld, int nc, T* q, double* red,
                          int mode, int k, const PassExtra& ex, hipStream_t s) {
   switch (mode) {
-    case SP_CGJ:  // the residual itself: double only
-      if constexpr (sizeof(T) == sizeof(double)) return launch_spmv_m<L, V, SP_CGJ, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
-      return 0;
     case SP_CG: return launch_spmv_m<L, V, SP_CG, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
     case SP_CHEB0: return launch_spmv_m<L, V, SP_CHEB0, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
     case SP_CHEB: return launch_spmv_m<L, V, SP_CHEB, T>(b, x, pprev, pout, ld, nc, q, red, k, ex, s);
@@ -923,8 +915,14 @@ static PassExtra no_extra(int full = 0) { return PassExtra{nullptr, full}; }
 // each pass clears only slots that no workgroup of the same launch reads, so
 // no launch overwrites a value its own workgroups use.
 
-// The vector pass.  JAC: z = D^-1 r, and r.D^-1 r of the new r is accumulated
-// for the next iteration.  xmode 0: x left for the next pass; 1: x += alpha p;
+// The vector pass.  JAC: z = D^-1 r, formed here and, of the new r, written for the
+// next operator pass (zj); r.D^-1 r of the new r is accumulated for the next
+// iteration.  With D^-1 gathered beside r in the operator pass instead of the store
+// here, that pass waited for one more dependent load an entry: 66,635 rows x 4
+// columns 20.4 -> 16.5 us (this pass 12.0 -> 12.4), four times that in a batch 48.1 ->
+// 40.2 (19.2 -> 19.9), 4,394 x 25 43.2 -> 37.6 (9.4 both), 66,635 x 64 in blocks of 16
+// columns 197 -> 149 (53.6 -> 60.3).
+// xmode 0: x left for the next pass; 1: x += alpha p;
 // 2: also the previous iteration's term.  zw_rows, rz_rows > 0: z.w and r.z are
 // folded here from the partial sums of the passes that formed them.
 // A thread takes one column and U rows at a time, all their loads in flight
@@ -934,7 +932,7 @@ __global__ void __launch_bounds__(NT) k_cg_vectors(const DevMesh* __restrict__ d
                                                    double* __restrict__ r, const Z* __restrict__ z,
                                                    double* __restrict__ p, const double* __restrict__ w,
                                                    double* __restrict__ q, int ncol, double* __restrict__ red, int k,
-                                                   float* __restrict__ rf, int xmode,
+                                                   float* __restrict__ rf, double* __restrict__ zj, int xmode,
                                                    const double* __restrict__ zw_part, int zw_rows,
                                                    const double* __restrict__ rz_part, int rz_rows) {
   INSTANCE;
@@ -943,7 +941,8 @@ __global__ void __launch_bounds__(NT) k_cg_vectors(const DevMesh* __restrict__ d
   x += d.oF * ncol;
   if (rf) rf += d.oE * ncol;
   r += d.oE * ncol;
-  if (!JAC) z += d.oE * ncol;
+  if (JAC) zj += d.oE * ncol;
+  else z += d.oE * ncol;
   p += d.oE * ncol;
   w += d.oE * ncol;
   q += d.oE * ncol;
@@ -1001,7 +1000,10 @@ __global__ void __launch_bounds__(NT) k_cg_vectors(const DevMesh* __restrict__ d
         const double rn = ro[u] - al * qn;
         r[e] = rn;
         if (rf) rf[e] = (float)rn;  // the finest multigrid level's float copy (Poisson schedule bit 6)
-        if (JAC) rz += rn * rn * di[u];
+        if (JAC) {
+          zj[e] = di[u] * rn;
+          rz += rn * rn * di[u];
+        }
         rr += rn * rn;
       }
     }
@@ -1036,13 +1038,15 @@ __global__ void __launch_bounds__(NT) k_rz_start(const double* __restrict__ part
 }
 
 // start: partial rz, rr of the first residual r (cold: x = 0).  x over full rows.
+// z: null, or D^-1 r for the Jacobi CG's first operator pass.
 __global__ void __launch_bounds__(NT) k_cg_start2(const DevMesh* __restrict__ dm, double* __restrict__ x,
-                                                  const double* __restrict__ r, int ncol, int warm,
-                                                  int64_t part_stride, double* __restrict__ part) {
+                                                  const double* __restrict__ r, double* __restrict__ z, int ncol,
+                                                  int warm, int64_t part_stride, double* __restrict__ part) {
   INSTANCE;
   __shared__ double lds[2 * NT];
   x += d.oF * ncol;
   r += d.oE * ncol;
+  if (z) z += d.oE * ncol;
   const int groups = NT / ncol;
   const int g = threadIdx.x / ncol, c = threadIdx.x - g * ncol;
   const bool act = g < groups;
@@ -1053,6 +1057,7 @@ __global__ void __launch_bounds__(NT) k_cg_start2(const DevMesh* __restrict__ dm
       const double rn = r[e];
       if (!warm) x[e] = 0.0;
       const double di = gbl(d.kdiag_inv)[k];
+      if (z) z[e] = di * rn;
       rz += rn * rn * di;
       rr += rn * rn;
     }
@@ -1092,9 +1097,9 @@ static int timed_pass(PoissonWs& P, hipStream_t s, F&& pass) {
   return rows;
 }
 template <class T>
-static int cg_pass(const Batch& b, PoissonWs& P, const T* z, int mode, int k, hipStream_t s) {
+static int cg_pass(const Batch& b, PoissonWs& P, const T* z, int k, hipStream_t s) {
   return timed_pass(P, s, [&] {
-    return launch_spmv_mode<T>(b, z, z, nullptr, P.ncol, nullptr, P.red, mode, k, s, PassExtra{P.w, 0});
+    return launch_spmv_mode<T>(b, z, z, nullptr, P.ncol, nullptr, P.red, SP_CG, k, s, PassExtra{P.w, 0});
   });
 }
 // How the solution update of iteration k is taken (k_cg_vectors).
@@ -1106,7 +1111,7 @@ static void cg_vectors(const Batch& b, double* W, PoissonWs& P, const Z* z, floa
                        hipStream_t s) {
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(cg_blocks(b, P.ncol), b.ni), dim3(NT), 0, s, b.dm, W, P.r, z, P.p,
-                       (const double*)P.w, P.q, P.ncol, P.red, k, rf, cg_xmode(b, k), (const double*)b.spart, zw_rows,
+                       (const double*)P.w, P.q, P.ncol, P.red, k, rf, JAC ? P.acc : nullptr, cg_xmode(b, k), (const double*)b.spart, zw_rows,
                        (const double*)(b.spart ? b.spart + b.spart_cap : nullptr), rz_rows);
   };
   go(k_cg_vectors<Z, JAC, CG_ROWS>);
@@ -1114,7 +1119,7 @@ static void cg_vectors(const Batch& b, double* W, PoissonWs& P, const Z* z, floa
 template <class Z>
 static void cg_iteration(const Batch& b, double* W, PoissonWs& P, const Z* z, float* rf, int rz_rows, int k,
                          hipStream_t s) {
-  const int rows = cg_pass<Z>(b, P, z, SP_CG, k, s);
+  const int rows = cg_pass<Z>(b, P, z, k, s);
   cg_vectors<Z, false>(b, W, P, z, rf, rows, rz_rows, k, s);
 }
 void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const double* z, float* rf, int rz_rows, int k,
@@ -1128,7 +1133,7 @@ void launch_cg_iteration(const Batch& b, double* W, PoissonWs& P, const float* z
 // One Jacobi-preconditioned iteration.
 void launch_cg_step(const Batch& b, double* W, PoissonWs& P, hipStream_t s) {
   const int k = P.it;
-  const int rows = cg_pass<double>(b, P, P.r, SP_CGJ, k, s);
+  const int rows = cg_pass<double>(b, P, P.acc, k, s);
   cg_vectors<double, true>(b, W, P, nullptr, nullptr, rows, 0, k, s);
   P.it = k + 1;
 }
@@ -1147,7 +1152,8 @@ void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int
       return launch_spmv_mode<double>(b, W, rhs_r, rhs_r, ncol, rhs_r, P.red, SP_RES, -1, s, no_extra(1));
     });
   const int nb = cg_blocks(b, ncol);
-  hipLaunchKernelGGL(k_cg_start2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, rhs_r, ncol, warm, P.part_stride, P.part);
+  hipLaunchKernelGGL(k_cg_start2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, rhs_r,
+                     b.mx.sched_poi & 16 ? nullptr : P.acc, ncol, warm, P.part_stride, P.part);
   hipLaunchKernelGGL(k_rz_start, dim3(ncol, b.ni), dim3(NT), 0, s, P.part, P.part_stride, nb, ncol, P.sc, P.red);
   P.it = 0;
 }
