@@ -530,7 +530,11 @@ static void prolong_cells(const MgDev& mg, int l, int ni, int ncol, hipStream_t 
   InterpTable tab{};
   for (int a = 0; a < pf; ++a)
     for (int b = 0; b < pc; ++b) tab.B[a * pc + b] = mg.interp[l][a * pc + b];
-  // a thread per plane where the cells alone leave the chip idle (below 2^19 lanes)
+  // a thread per plane where the cells alone leave the chip idle (below 2^19 lanes;
+  // between 2^17 and 2^20 it is much the same).  Cells, planes, Q2 to Q3: 11,300 lanes
+  // (4 columns) 26.8, 10.6 us; 45,000 (16) 26.4, 12.9; 180,000 (64) 34.7, 39.6 and, 16
+  // instances of 4 columns, 47.5, 50.8; 233,000 (4) 79.9, 63.5; 450,000 (40 instances)
+  // 124, 116; 934,000 (16) 213, 224
   const bool split = mg.max_cells[l] * ncol * ni < (int64_t)1 << 19;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(xcd_grid(mg.max_cells[l] * (split ? pf : 1), NT / ncol, 65536), ni), dim3(NT), 0, s,
@@ -562,8 +566,10 @@ void mg_vcycle(const MgDev& mg, int ni, int ncol, const MgLevel0Ops& ops, hipStr
       int cw = 1;
       while (cw < ncol) cw *= 2;
       // lanes per row: four groups of them share its entries where the rows alone
-      // fill the chip (at least 16 lanes), else the whole wave
-      const int G = mg.max_n[l + 1] * ni >= 8192 ? std::min(64, std::max(16, 4 * cw)) : 64;
+      // fill the chip (at least 16 lanes), else the whole wave.  Whole wave, four
+      // groups: 1,153 rows x 4 columns 4.9, 8.1 us; 1,979 4.6, 5.4; 7,916 8.8, 6.9;
+      // 18,719 15.0, 13.7; 74,900 49.9, 33.4
+      const int G = mg.max_n[l + 1] * ni >= 4096 ? std::min(64, std::max(16, 4 * cw)) : 64;
       hipLaunchKernelGGL(k_mg_restrict, dim3(xcd_grid(mg.max_n[l + 1], NT / G, 16384), ni), dim3(NT), 0, s, mg.lv[l],
                          mg.lv[l + 1], ncol, cw, G);
     }

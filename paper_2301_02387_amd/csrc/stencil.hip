@@ -346,20 +346,30 @@ static void launch_orb_rows(const Batch& b, const double* u, const double* Ef, i
   else mf ? go(k_orb_rows<L, GR, true, false, false, true>) : go(k_orb_rows<L, GR, true, false, false, false>);
 }
 
-// Lane groups per node: rows of up to four orbitals are read by 8 lanes (their
-// entries then load in whole sectors); four groups where the nodes alone leave
-// the chip idle (below 2^20 lanes: four waves a SIMD).  Eight orbitals and 1.65 M
-// nodes: one group 736 us, two 720, four 810 (540 with the loads of lanes past
-// the last orbital unguarded, which left registers for four waves); 234,000
-// nodes of a Q1 mesh 178, 231, 203.
+// Lane groups per node: four (of one orbital eight) while the lanes of a single
+// group leave the chip idle, below 2^17 (one orbital 2^14, two 2^18), since a
+// node's entries are then a chain; above that one, with one and two orbitals as many
+// as read a node's entries in whole sectors.  Measured with 1, 2, 4, 8 groups, us:
+// 8 orbitals  4,583 nodes 9.3, 6.4, 5.9, 6.4;  12,468 10.1, 9.3, 9.4, 10.9;  24,936
+//   14.3, 15.0, 16.7, 19.6;  75,875 28.6, 32.9, 38.8, 47.1;  1.65 M 551, 655, 733, 818;
+//   234,000 of a Q1 mesh, velocity gauge with complex scaling 106, 133, 211, 240
+// 4 orbitals  6,234 nodes 7.0, 5.3, 5.2, 5.8;  24,936 9.3, 9.5, 9.8, 10.9;  49,872 13.7,
+//   14.1, 15.5, 19.7;  75,875 16.8, 17.7, 19.0, 26.2;  1.65 M 273, 360, 360, 438
+// 2 orbitals  6,234 nodes 7.0, 5.2, 4.9, 4.9;  49,872 11.0, 9.0, 9.7, 12.3;  75,875 13.1,
+//   12.9, 13.4, 17.0 (in whole Arnoldi steps the same within the runs' spread);
+//   151,750 18.8, 19.3, 21.1, 27.4;  1.65 M 173, 194, 217, 257 (velocity gauge 253, 235,
+//   275, 307)
+// 1 orbital   6,234 nodes 7.3, 5.8, 4.8, 4.6;  24,936 8.4, 5.9, 5.4, 6.0;  75,875 12.5,
+//   10.4, 10.1, 11.4;  1.65 M 118, 127, 126, 159 (Q1 mesh as above 65, 26, 30, 36)
 void launch_stencil_orb(const Batch& b, const double* u, const double* Ef, int diag_mode, const double* Upk,
                         const double* ginv, int mode, const double* lam, double* out, double* acc, hipStream_t s) {
   const int n = b.mx.n, L = n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : 8;
-  const bool few = b.mx.NE * L * b.ni < (int64_t)1 << 20;
+  const int64_t lanes = b.mx.NE * L * b.ni;
+  const bool few = lanes < (int64_t)1 << (L == 1 ? 14 : L == 2 ? 18 : 17);
   auto go = [&](auto f) { f(b, u, Ef, diag_mode, Upk, ginv, mode, lam, out, acc, s); };
-  if (L == 1) go(launch_orb_rows<1, 8>);
-  else if (L == 2) go(launch_orb_rows<2, 4>);
-  else if (L == 4) few ? go(launch_orb_rows<4, 4>) : go(launch_orb_rows<4, 2>);
+  if (L == 1) few ? go(launch_orb_rows<1, 8>) : go(launch_orb_rows<1, 4>);
+  else if (L == 2) few ? go(launch_orb_rows<2, 4>) : go(launch_orb_rows<2, 2>);
+  else if (L == 4) few ? go(launch_orb_rows<4, 4>) : go(launch_orb_rows<4, 1>);
   else few ? go(launch_orb_rows<8, 4>) : go(launch_orb_rows<8, 1>);
 }
 

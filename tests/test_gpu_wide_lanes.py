@@ -1,4 +1,4 @@
-"""Launches above 2^20 lanes, where a row or node is taken by fewer lane groups
+"""Launches of many lanes, where a row or node is taken by fewer lane groups
 (batches of equal small meshes), and the complex-scaled orbital rows at every
 lane width.  Bars as in test_gpu_orbital_counts: 1e-10 against the oracle."""
 import copy
@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("gauge", ["length", "velocity"])
-@pytest.mark.parametrize("n,copies", [(1, 1), (4, 1), (5, 1), (8, 1), (4, 39), (5, 20), (8, 20)])
+@pytest.mark.parametrize("n,copies", [(1, 1), (2, 1), (4, 1), (5, 1), (8, 1), (1, 3), (2, 20), (4, 39), (5, 20), (8, 20)])
 def test_scaled_orbital_rows(n, copies, gauge):
-    """G v under complex scaling, four lane groups a node (one instance) and one or
-    two (20 or 39 instances of 6,770 nodes), v reaching into the scaled cells."""
+    """G v under complex scaling, eight or four lane groups a node (one instance) and
+    four, two or one (3 to 39 instances of 6,770 nodes), v reaching into the scaled
+    cells."""
     import paper_2301_02387_amd as mh
     import torch
     from oracle.ecs import ECS
@@ -35,6 +36,28 @@ def test_scaled_orbital_rows(n, copies, gauge):
     _, fr = frozen(P, op, n, 190 + n, E=0.27, copies=copies, one_body=ope)
     xyz = P.om.xyz[P.om.dof_nodes]
     v = broad_orbitals(xyz, n, 200 + n, float(min(e["inner"])), n_gauss=n + 4)
+    out = torch.zeros((P.NE * copies, n), dtype=torch.complex128, device="cuda")
+    op.rhs_apply(dev(np.concatenate([P.to_lib_orb(v)] * copies)), out)
+    torch.cuda.synchronize()
+    ref = fr.G(v)
+    for part in np.split(out.cpu().numpy(), copies):
+        got = P.from_lib_dof(part)
+        assert rel_err_cols(got, ref) < 1e-10 and max_rel_cols(got, ref) < 1e-10
+
+
+@pytest.mark.parametrize("gauge", ["length", "velocity"])
+@pytest.mark.parametrize("n,copies", [(1, 2), (1, 3), (2, 21), (2, 22), (3, 5), (3, 6), (7, 2), (7, 3)])
+def test_orbital_rows_bound(n, copies, gauge):
+    """G v on both sides of the lane counts (2^14 lanes of one orbital, 2^18 of two, else 2^17)
+    where a node is taken by fewer lane groups."""
+    import paper_2301_02387_amd as mh
+    import torch
+    from oracle.fem import Operators
+    P = copy.copy(pair("tiny_q3"))
+    op = mh.Operator.batch([P.mesh] * copies, [P.w["nuclei"]] * copies, n, (n + 1) // 2, n // 2, gauge=gauge)
+    ops = P.ops if gauge == "length" else Operators(P.om, P.w["nuclei"], gauge="velocity")
+    _, fr = frozen(P, op, n, 220 + n, E=0.31, copies=copies, one_body=ops)
+    v = orbitals(P, n, 230 + n)
     out = torch.zeros((P.NE * copies, n), dtype=torch.complex128, device="cuda")
     op.rhs_apply(dev(np.concatenate([P.to_lib_orb(v)] * copies)), out)
     torch.cuda.synchronize()
