@@ -101,15 +101,47 @@ def rhs_algorithmic_bytes(info, op, ecs=False):
 
 
 def orbital_pass_bytes(info, op, ecs=False):
-    """Algorithmic bytes of the orbital operator's node pass alone (kernel
-    timing slot 0): orbitals in and out, U, the node tables (with complex
-    scaling also the complex row factor, potential and field weights and the
-    cells' scaled directions)."""
+    """Matrix-free bytes of the orbital operator's pass alone (kernel timing
+    slot 0): orbitals in and out, U, the node tables, the cell->node maps and h
+    per cell (with complex scaling also the row factor, the complex potential
+    and field weights and the cells' scaled directions).  The kernel reads
+    assembled rows instead of the cell maps: orbital_row_bytes."""
     P = info["p"] + 1
     nC, NE, N, n = info["n_cells"], op.n_ext, op.n_dof, op.n_orb
-    meta = 32 * NE + 4 * P ** 3 * nC + 8 * nC + 4 * N
+    meta = 4 * P ** 3 * nC + 8 * nC + 4 * N
     extra = 32 * NE + nC if ecs else 0
     return 32 * n * NE + 8 * n * n * NE + 24 * NE + 8 * N + meta + extra
+
+
+def orbital_row_entries(mesh):
+    """Entries of the orbital operator's rows: the pairs of extended nodes (DoFs,
+    hanging nodes) on one coordinate line of a cell, each node with itself."""
+    import numpy as np
+    nodes = mesh.cells()[0].astype(np.int64)
+    NE = mesh.info["n_dof"] + mesh.info["n_hang"]
+    P = mesh.info["p"] + 1
+    grid = nodes.reshape(-1, P, P, P)
+    keys = []
+    for axis in (1, 2, 3):
+        lines = np.moveaxis(grid, axis, 3).reshape(-1, P)
+        for a in range(P):
+            for b in range(a + 1, P):
+                i, j = lines[:, a], lines[:, b]
+                ok = (i < NE) & (j < NE)
+                keys.append(np.minimum(i[ok], j[ok]) * NE + np.maximum(i[ok], j[ok]))
+    return NE + 2 * len(np.unique(np.concatenate(keys)))
+
+
+def orbital_row_bytes(entries, n_ext, n_inst=1, velocity=False, ecs=False):
+    """Bytes of those rows read by one pass: row pointers, a column and the
+    stiffness value per entry, in the velocity gauge the derivative's too (complex
+    values with complex scaling): overhead of the assembled form, not part of the
+    algorithmic bytes."""
+    return 4 * (n_ext + n_inst) + entries * (4 + (16 if ecs else 8) * (2 if velocity else 1))
+
+
+ALGORITHMIC_BYTES = {"poisson_spmv": "matrix-free: operand and result rows, cell maps, constraint rows, h",
+                     "stencil_orb": "matrix-free: orbitals in and out, mean field, node tables, cell maps, h"}
 
 
 def copy_bandwidth(torch, gib=2, reps=10):
@@ -315,12 +347,13 @@ def run_single(name, args, torch, with_adjoint, with_cpu):
     kern = {"stencil_orb": {"avg_ms": k_orb[0], "count": k_orb[1]},
             "poisson_spmv": {"avg_ms": k_poi[0], "count": k_poi[1]}}
     dom = max(kern, key=lambda k: kern[k]["avg_ms"] * kern[k]["count"])
+    orb_over = orbital_row_bytes(orbital_row_entries(mesh), op.n_ext, 1, gauge == "velocity", bool(ecs))
     if dom == "poisson_spmv":
         # one warm start per step
         byts = poisson_algorithmic_bytes(info, op, (sched["poisson"][0] & 80) == 80, args.steps / k_poi[1])
         over = stored_matrix_bytes(op.n_dof, op.n_poisson_nnz, op.n_inst)
     else:
-        byts, over = orbital_pass_bytes(info, op, bool(ecs)), 0
+        byts, over = orbital_pass_bytes(info, op, bool(ecs)), orb_over
     sched_tag = "/".join(map(str, sched["poisson"] if dom == "poisson_spmv" else sched["orbital"]))
     ach = byts / (kern[dom]["avg_ms"] * 1e-3) / 1e9 if kern[dom]["avg_ms"] > 0 else 0.0
     wl = (f"{name}_{op.n_dof}dof_{op.n_orb}orb" if name.endswith(f"_q{w['p']}")
@@ -365,17 +398,18 @@ def run_single(name, args, torch, with_adjoint, with_cpu):
                      "traffic": measured_traffic(dom, wl, schedule=sched_tag),
                      "schedule": sched_tag,
                      "algorithmic_bytes_per_launch": byts,
-                     "algorithmic_bytes": "matrix-free: operand and result rows, cell maps, constraint rows, h",
+                     "algorithmic_bytes": ALGORITHMIC_BYTES[dom],
                      "stored_operator_bytes_per_launch": over},
         # one whole G application (node pass, stiffness, interface mass solve,
         # hanging fill) against B_G, by event pairs around each call
         "roofline_rhs": {"kernel": "rhs_apply (all launches of one G application)", "bound": "hbm",
                          "achieved": rhs_ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": rhs_ach / HBM_PEAK_GBS,
                          "algorithmic_bytes_per_launch": bg},
-        # the orbital operator's node pass of every G application
+        # the orbital operator's pass of every G application
         "roofline_orbital": {"kernel": "stencil_orb", "bound": "hbm", "achieved": orb_ach, "peak": HBM_PEAK_GBS,
                              "unit": "GB/s", "frac": orb_ach / HBM_PEAK_GBS,
-                             "schedule": "/".join(map(str, sched["orbital"])), "algorithmic_bytes_per_launch": orb_b},
+                             "schedule": "/".join(map(str, sched["orbital"])), "algorithmic_bytes_per_launch": orb_b,
+                             "stored_operator_bytes_per_launch": orb_over},
     }
     if with_adjoint:
         line["fwd_adjoint_vs_plain"] = adjoint_ratio(op, phi, Ci, w)
@@ -693,9 +727,8 @@ def run_batch(args):
            "n_full": sum(mm.info["n_full"] for mm in meshes)}
     spmv_b = poisson_algorithmic_bytes(agg, op, (sched["poisson"][0] & 80) == 80, args.steps / max(k_poi[1], args.steps))
     spmv_over = stored_matrix_bytes(op.n_dof, op.n_poisson_nnz, op.n_inst)
-    P3 = (w0["p"] + 1) ** 3
-    NE, N, n = op.n_ext, op.n_dof, op.n_orb
-    orb_bytes = 32 * n * NE + 8 * n * n * NE + 24 * NE + 8 * N + 32 * NE + 4 * P3 * n_cells + 8 * n_cells + 4 * N
+    orb_bytes = orbital_pass_bytes(agg, op)
+    orb_over = orbital_row_bytes(sum(orbital_row_entries(mm) for mm in meshes), op.n_ext, op.n_inst)
     kern = {"stencil_orb": {"avg_ms": k_orb[0], "count": k_orb[1], "algorithmic_bytes": orb_bytes},
             "poisson_spmv": {"avg_ms": k_poi[0], "count": k_poi[1], "algorithmic_bytes": spmv_b}}
     dom = max(kern, key=lambda k: kern[k]["avg_ms"] * kern[k]["count"])
@@ -738,13 +771,14 @@ def run_batch(args):
                      "traffic": measured_traffic(dom, f"h2x{op.n_inst}_q3_{op.n_dof}dof_{op.n_orb}orb",
                                                  schedule=batch_tag),
                      "schedule": batch_tag, "algorithmic_bytes_per_launch": byts,
-                     "algorithmic_bytes": "matrix-free: operand and result rows, cell maps, constraint rows, h",
-                     "stored_operator_bytes_per_launch": spmv_over if dom == "poisson_spmv" else 0},
+                     "algorithmic_bytes": ALGORITHMIC_BYTES[dom],
+                     "stored_operator_bytes_per_launch": spmv_over if dom == "poisson_spmv" else orb_over},
         "roofline_orbital": {"kernel": "stencil_orb", "bound": "hbm",
                              "achieved": (orb_bytes / (k_orb[0] * 1e-3) / 1e9) if k_orb[0] > 0 else 0.0,
                              "peak": HBM_PEAK_GBS, "unit": "GB/s",
                              "frac": ((orb_bytes / (k_orb[0] * 1e-3) / 1e9) if k_orb[0] > 0 else 0.0) / HBM_PEAK_GBS,
-                             "algorithmic_bytes_per_launch": orb_bytes},
+                             "algorithmic_bytes_per_launch": orb_bytes,
+                             "stored_operator_bytes_per_launch": orb_over},
     }
     print(json.dumps(line))
 
