@@ -146,7 +146,7 @@ void launch_orb_row_fill(const Batch& b, hipStream_t s) { orb_row_build<true>(b,
 // assembled Poisson operator on 2n real columns and a second pass over the nodes.
 // Measured, before -> rows: H2O (1.65 M nodes x 8 orbitals) 353 + 462 -> 539 us,
 // its momentum 1650 -> 359; on the Q1 mesh, velocity gauge with complex scaling
-// (234,000 x 8) 274 -> 113; 16 H2 (75,900 x 2 each) 144 + 52 -> 158; H2 14.0 +
+// (234,000 x 8) 274 -> 113; 16 H2 (75,900 x 2 each) 144 + 52 -> 148; H2 14.0 +
 // 6.6 -> 12.9; 3 orbitals in the velocity gauge (Q2) 27 -> 10.4 us.
 // --------------------------------------------------------------------------
 template <int L, int GR, bool OP_K, bool OP_S, bool CX, bool MF>
