@@ -400,7 +400,7 @@ def run_single(name, args, torch, with_adjoint, with_cpu):
                      "algorithmic_bytes_per_launch": byts,
                      "algorithmic_bytes": ALGORITHMIC_BYTES[dom],
                      "stored_operator_bytes_per_launch": over},
-        # one whole G application (node pass, stiffness, interface mass solve,
+        # one whole G application (rows, masters, interface mass solve,
         # hanging fill) against B_G, by event pairs around each call
         "roofline_rhs": {"kernel": "rhs_apply (all launches of one G application)", "bound": "hbm",
                          "achieved": rhs_ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": rhs_ach / HBM_PEAK_GBS,

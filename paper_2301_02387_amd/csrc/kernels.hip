@@ -997,7 +997,7 @@ void launch_build_U_full(const Batch& b, const double* W, const double* Gamma, c
 // =====================================================================
 // Krylov (Arnoldi) pieces.  M-inner product over the packed orbital vector:
 // <u,v> = sum_i m_i sum_p conj(u_ip) v_ip on rows [0, NE) of each instance.
-// Per-instance strides: H (m_max+1) m_max, hcur m_max+1, y m_max, scal 8,
+// Per-instance strides: H (m_max+1) m_max, y m_max, scal 8,
 // partials nblk (2 (m_max+1) + 1).
 // =====================================================================
 constexpr int KMAX = 25;
