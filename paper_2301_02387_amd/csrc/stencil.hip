@@ -457,7 +457,8 @@ void launch_mass_direct(const Batch& b, const double* f, double* out, double* ma
 enum { SP_CG = 1, SP_CHEB0 = 2, SP_CHEB = 3, SP_CHEB_RZ = 4, SP_RES = 5 };
 
 // Arrays of a pass beside its operand: w = K z of the CG's pass, double
-// whatever z is; full: the operand of SP_RES is over full rows.
+// whatever z is; full: the operand of SP_RES is over full rows, and q holds r
+// before the pass (the residual of a CG start, in place).
 struct PassExtra {
   double* w;
   int full;
@@ -523,7 +524,7 @@ __device__ __forceinline__ void spmv_row_part(const DevMesh& d, const T* __restr
 //             partial (in pq), its step being k >> 4 (its slot k & 15); it is
 //             the last step of a smoothing, so d is not stored.
 // cf: s0, then (c1, c2) of each step from 1 on.
-// SP_RES (x = z, pprev = r): q_i = r_i - y.
+// SP_RES (x = z, pprev = r; ex.full: r in q): q_i = r_i - y.
 template <int V, int MODE, class T>
 __device__ __forceinline__ void spmv_store(const DevMesh& d, T* __restrict__ q, T* __restrict__ pout,
                                            const T* __restrict__ x, const T* __restrict__ pprev,
@@ -532,7 +533,7 @@ __device__ __forceinline__ void spmv_store(const DevMesh& d, T* __restrict__ q, 
   const auto* dinv = gbl(d.kdiag_inv);
   if constexpr (MODE == SP_RES) {
     double rv[V];
-    load_vals<V>(gbl(pprev) + i * ld + c0, rv);
+    load_vals<V>(gbl(ex.full ? (const T*)q : pprev) + i * ld + c0, rv);
     T* qo = q + i * ld + c0;
 #pragma unroll
     for (int v = 0; v < V; ++v) qo[v] = (T)(rv[v] - y[v]);
@@ -1163,7 +1164,7 @@ void launch_cg_start(const Batch& b, double* W, double* rhs_r, PoissonWs& P, int
   // warm: r = rhs - K x0, x0 = the DoF rows of W (full rows)
   if (warm)
     timed_pass(P, s, [&] {
-      return launch_spmv_mode<double>(b, W, rhs_r, rhs_r, ncol, rhs_r, P.red, SP_RES, -1, s, no_extra(1));
+      return launch_spmv_mode<double>(b, W, nullptr, nullptr, ncol, rhs_r, P.red, SP_RES, -1, s, no_extra(1));
     });
   const int nb = cg_blocks(b, ncol);
   hipLaunchKernelGGL(k_cg_start2, dim3(nb, b.ni), dim3(NT), 0, s, b.dm, W, rhs_r,
