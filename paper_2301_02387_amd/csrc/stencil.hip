@@ -401,9 +401,9 @@ __global__ void __launch_bounds__(NT) k_ma_gather_orb(const DevMesh* __restrict_
   }
 }
 
-// Mass solve of a given load vector: non-masters 1/m, masters to ma_b.
-__global__ void __launch_bounds__(NT) k_mass_direct(const DevMesh* __restrict__ dm, const double2* __restrict__ f,
-                                                    double2* __restrict__ out, double2* __restrict__ ma_b) {
+// Mass solve of a given load vector: non-masters 1/m, masters to ma_b.  out may be f.
+__global__ void __launch_bounds__(NT) k_mass_direct(const DevMesh* __restrict__ dm, const double2* f, double2* out,
+                                                    double2* __restrict__ ma_b) {
   INSTANCE;
   const int n = d.n;
   const int64_t total = d.N * n, o = d.oE * n, om = d.oMa * n;
