@@ -1,7 +1,7 @@
 // Geometric multigrid preconditioner for the pair Poisson solves: a V-cycle
 // per instance over the hierarchy built by build_multigrid (the operator's own
-// Q_p space, Q2 (below Q3) and Q1 on the same leaves, Q1 on shallower refinements, coarser base
-// grids, a dense inverse at the bottom), with Chebyshev smoothing
+// Q_p space, Q2 below Q3 and Q1 on the same leaves, Q1 on shallower refinements,
+// coarser base grids, a dense inverse at the bottom), with Chebyshev smoothing
 // preconditioned by the diagonal.  All n^2 real pair columns go through every
 // pass together ([rows][ncol] arrays), and every pass covers all instances of
 // a batch in one launch: blockIdx.y selects the instance's level record, and
